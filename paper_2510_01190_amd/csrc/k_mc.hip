@@ -35,6 +35,8 @@
 // are independent -- the closed form's model, which it converges to on every
 // cell, boundary cells included (where the paper's vector-level sampling
 // shares grid points between the one-sided differences).
+#include <algorithm>
+
 #include "mc_rank.hpp"
 #include "pdiv_device.hpp"
 #include "pdiv_internal.hpp"
@@ -82,6 +84,32 @@ __device__ __forceinline__ uint32_t rank_of(float d, const float* tree, float to
   return (a >> 2) - uint32_t(K) + (d >= top ? 1u : 0u);
 }
 
+// A cell's crossings at one isovalue over this block's samples: the finished
+// probability when the block took all of them, else added as an integer into
+// the map, which then holds counts until mc_finish_kernel (integer sums, so
+// the order in which the splits arrive does not matter and the maps are
+// bitwise those of one run over all samples).
+__device__ __forceinline__ void put_count(float* o, uint32_t n, float n_samples) {
+  if (gridDim.z == 1)
+    *o = static_cast<float>(n) / n_samples;
+  else
+    atomicAdd(reinterpret_cast<uint32_t*>(o), n);
+}
+
+__global__ __launch_bounds__(kBlock) void mc_zero_kernel(uint32_t* __restrict__ counts,
+                                                         int64_t n) {
+  for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n;
+       i += int64_t(gridDim.x) * kBlock)
+    counts[i] = 0u;
+}
+
+__global__ __launch_bounds__(kBlock) void mc_finish_kernel(float* __restrict__ out, int64_t n,
+                                                           float n_samples) {
+  for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n;
+       i += int64_t(gridDim.x) * kBlock)
+    out[i] = static_cast<float>(__float_as_uint(out[i])) / n_samples;
+}
+
 // RANK (8 or 16 isovalue slots, at most 65535 samples): the ranked crossing
 // test; the divergence slots hold each vertex's rank instead of its value.
 template <int KC, bool RANK, typename T>
@@ -90,9 +118,9 @@ __global__ __launch_bounds__(kBlock) void mc_kernel(const T* __restrict__ mu,
                                                     const T* __restrict__ mv,
                                                     const T* __restrict__ vv, int ny, int nx,
                                                     StencilCoef k, IsoChunk iso, RankTable rt,
-                                                    int n_store, int n_samples, uint32_t key0,
-                                                    uint32_t key1, float* __restrict__ out,
-                                                    int64_t plane) {
+                                                    int n_store, int n_samples, int per_split,
+                                                    uint32_t key0, uint32_t key1,
+                                                    float* __restrict__ out, int64_t plane) {
   static_assert(!RANK || KC == 8 || KC == 16, "the ranked test takes 8 or 16 slots");
   constexpr int kPer = 32 / KC;             // ranked: cells per counter word
   constexpr int kWords = RANK ? CPT / kPer : 1;
@@ -137,8 +165,10 @@ __global__ __launch_bounds__(kBlock) void mc_kernel(const T* __restrict__ mu,
 #pragma unroll
   for (int w = 0; w < kWords; ++w) sliced_clear(sl[w]);
 
-  const int n_pairs = (n_samples + 1) >> 1;
-  for (int pr = 0; pr < n_pairs; ++pr) {
+  // this block's run of sample pairs
+  const int first = int(blockIdx.z) * per_split;
+  const int last = min(first + per_split, (n_samples + 1) >> 1);
+  for (int pr = first; pr < last; ++pr) {
     // 1. draw both samples of the pair at every point of tile + halo
 #pragma unroll
     for (int m = 0; m < PPT; ++m) {
@@ -216,7 +246,7 @@ __global__ __launch_bounds__(kBlock) void mc_kernel(const T* __restrict__ mu,
       }
 #pragma unroll
       for (int w = 0; w < kWords; ++w) sliced_add2(sl[w], word[0][w], word[1][w]);
-      if (pr % 7 == 6) {
+      if ((pr - first) % 7 == 6) {
 #pragma unroll
         for (int w = 0; w < kWords; ++w) sliced_flush(sl[w]);
       }
@@ -260,10 +290,9 @@ __global__ __launch_bounds__(kBlock) void mc_kernel(const T* __restrict__ mu,
       for (int q = 0; q < KC; ++q) {
         if (q < n_store) {
           if constexpr (RANK)
-            o[rt.perm[q] * plane] =
-                static_cast<float>(sliced_count(sl[m / kPer], q + KC * (m % kPer))) / fs;
+            put_count(o + rt.perm[q] * plane, sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
           else
-            o[q * plane] = static_cast<float>(cnt[m][q]) / fs;
+            put_count(o + q * plane, cnt[m][q], fs);
         }
       }
     }
@@ -283,7 +312,8 @@ __global__ __launch_bounds__(kBlock) void mc_vertex_kernel(const T* __restrict__
                                                            const T* __restrict__ vv, int ny,
                                                            int nx, StencilCoef k, IsoChunk iso,
                                                            int n_store, int n_samples,
-                                                           uint32_t key0, uint32_t key1,
+                                                           int per_split, uint32_t key0,
+                                                           uint32_t key1,
                                                            RankTable rt,
                                                            float* __restrict__ out,
                                                            int64_t plane) {
@@ -342,8 +372,10 @@ __global__ __launch_bounds__(kBlock) void mc_vertex_kernel(const T* __restrict__
     __syncthreads();
   }
 
-  const int n_groups = (n_samples + 3) >> 2;
-  for (int gr = 0; gr < n_groups; ++gr) {
+  // this block's run of sample groups
+  const int first = int(blockIdx.z) * per_split;
+  const int last = min(first + per_split, (n_samples + 3) >> 2);
+  for (int gr = first; gr < last; ++gr) {
 #pragma unroll
     for (int m = 0; m < VPT; ++m) {
       if (vin[m]) {
@@ -394,7 +426,7 @@ __global__ __launch_bounds__(kBlock) void mc_vertex_kernel(const T* __restrict__
         sliced_add2(sl[w], word[0][w], word[1][w]);
         sliced_add2(sl[w], word[2][w], word[3][w]);
       }
-      if (gr % 3 == 2) {
+      if ((gr - first) % 3 == 2) {
 #pragma unroll
         for (int w = 0; w < kWords; ++w) sliced_flush(sl[w]);
       }
@@ -438,10 +470,9 @@ __global__ __launch_bounds__(kBlock) void mc_vertex_kernel(const T* __restrict__
       for (int q = 0; q < KC; ++q) {
         if (q < n_store) {
           if constexpr (RANK)
-            o[rt.perm[q] * plane] =
-                static_cast<float>(sliced_count(sl[m / kPer], q + KC * (m % kPer))) / fs;
+            put_count(o + rt.perm[q] * plane, sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
           else
-            o[q * plane] = static_cast<float>(cnt[m][q]) / fs;
+            put_count(o + q * plane, cnt[m][q], fs);
         }
       }
     }
@@ -470,42 +501,83 @@ __global__ __launch_bounds__(kBlock) void mc_sample_kernel(const T* __restrict__
   vs[p] = draw(ld(mv, p), __fsqrt_rn(ld(vv, p)), z.y);
 }
 
+// How the samples of a launch are split over blocks.  A block walks its
+// tile's sample steps (pairs, or groups of four) one after another, so a grid
+// of few tiles leaves most of the chip idle, and one of just over a multiple
+// of the resident blocks runs a nearly empty last round.  `splits` blocks per
+// tile share the steps; kSlots blocks run at once (4 per CU on 256 CUs) and a
+// block costs kSetup steps to start and finish, so a launch takes about
+// ceil(tiles * splits / kSlots) * (per_split + kSetup) steps.  Splitting adds
+// two small launches and the counters' atomics, so it has to promise a tenth.
+// Measured, one block per tile against split: 128x128, 1 isovalue, 2000
+// samples (16 tiles) 2215 against 71 us; 721x1440, 8 isovalues, 1000 samples
+// (1035 tiles, 11 past a full round) 2513 against 2103 us.
+struct McSplit {
+  int splits, per_split;
+};
+
+McSplit mc_split(int64_t tiles, int steps) {
+  constexpr int64_t kSlots = 1024, kSetup = 4, kMaxSplits = 256;
+  McSplit best{1, steps};
+  const double whole = double((tiles + kSlots - 1) / kSlots) * double(steps + kSetup);
+  double least = 0.9 * whole - 4.0;
+  for (int64_t z = 2; z <= kMaxSplits && z * kSetup <= steps; ++z) {
+    const int per = int((steps + z - 1) / z);
+    const int64_t used = (steps + per - 1) / per;  // splits that have work
+    const double cost = double((tiles * used + kSlots - 1) / kSlots) * double(per + kSetup);
+    if (cost < least) {
+      least = cost;
+      best = {int(used), per};
+    }
+  }
+  return best;
+}
+
 template <int KC, typename T>
 hipError_t launch_kc(const void* mu, const void* vu, const void* mv, const void* vv, int ny,
                      int nx, const StencilCoef& k, const IsoChunk& iso, int kc, int n_samples,
                      uint64_t seed, bool vertex, float* out, hipStream_t s) {
-  dim3 grid(static_cast<unsigned>(mc_tiles_x(nx)), static_cast<unsigned>(mc_tiles_y(ny)));
   const int64_t plane = static_cast<int64_t>(ny - 1) * (nx - 1);
-  RankTable rt{};
-  if constexpr (KC == 8 || KC == 16) {
-    if (n_samples <= 65535 && rank_table(iso.c, kc, KC, &rt)) {
-      if (vertex)
-        hipLaunchKernelGGL((mc_vertex_kernel<KC, true, T>), grid, dim3(kBlock), 0, s,
-                           static_cast<const T*>(mu), static_cast<const T*>(vu),
-                           static_cast<const T*>(mv), static_cast<const T*>(vv), ny, nx, k, iso,
-                           kc, n_samples, static_cast<uint32_t>(seed),
-                           static_cast<uint32_t>(seed >> 32), rt, out, plane);
-      else
-        hipLaunchKernelGGL((mc_kernel<KC, true, T>), grid, dim3(kBlock), 0, s,
-                           static_cast<const T*>(mu), static_cast<const T*>(vu),
-                           static_cast<const T*>(mv), static_cast<const T*>(vv), ny, nx, k, iso,
-                           rt, kc, n_samples, static_cast<uint32_t>(seed),
-                           static_cast<uint32_t>(seed >> 32), out, plane);
-      return hipGetLastError();
-    }
+  const int steps = vertex ? (n_samples + 3) / 4 : (n_samples + 1) / 2;
+  const McSplit sp = mc_split(mc_tiles_x(nx) * mc_tiles_y(ny), steps);
+  const dim3 grid(static_cast<unsigned>(mc_tiles_x(nx)), static_cast<unsigned>(mc_tiles_y(ny)),
+                  static_cast<unsigned>(sp.splits));
+  const int64_t n_out = plane * kc;
+  const dim3 fill_grid(static_cast<unsigned>(std::min<int64_t>((n_out + kBlock - 1) / kBlock, 4096)));
+  uint32_t* const counts = reinterpret_cast<uint32_t*>(out);
+  if (sp.splits > 1) {
+    hipLaunchKernelGGL(mc_zero_kernel, fill_grid, dim3(kBlock), 0, s, counts, n_out);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  if (vertex)
-    hipLaunchKernelGGL((mc_vertex_kernel<KC, false, T>), grid, dim3(kBlock), 0, s,
-                       static_cast<const T*>(mu), static_cast<const T*>(vu),
-                       static_cast<const T*>(mv), static_cast<const T*>(vv), ny, nx, k, iso, kc,
-                       n_samples, static_cast<uint32_t>(seed),
-                       static_cast<uint32_t>(seed >> 32), rt, out, plane);
-  else
-    hipLaunchKernelGGL((mc_kernel<KC, false, T>), grid, dim3(kBlock), 0, s,
-                       static_cast<const T*>(mu), static_cast<const T*>(vu),
-                       static_cast<const T*>(mv), static_cast<const T*>(vv), ny, nx, k, iso, rt,
-                       kc, n_samples, static_cast<uint32_t>(seed),
-                       static_cast<uint32_t>(seed >> 32), out, plane);
+  const T* const m0 = static_cast<const T*>(mu);
+  const T* const v0 = static_cast<const T*>(vu);
+  const T* const m1 = static_cast<const T*>(mv);
+  const T* const v1 = static_cast<const T*>(vv);
+  const uint32_t key0 = static_cast<uint32_t>(seed), key1 = static_cast<uint32_t>(seed >> 32);
+  RankTable rt{};
+  bool ranked = false;
+  if constexpr (KC == 8 || KC == 16) {
+    ranked = n_samples <= 65535 && rank_table(iso.c, kc, KC, &rt);
+    if (ranked && vertex)
+      hipLaunchKernelGGL((mc_vertex_kernel<KC, true, T>), grid, dim3(kBlock), 0, s, m0, v0, m1, v1,
+                         ny, nx, k, iso, kc, n_samples, sp.per_split, key0, key1, rt, out, plane);
+    else if (ranked)
+      hipLaunchKernelGGL((mc_kernel<KC, true, T>), grid, dim3(kBlock), 0, s, m0, v0, m1, v1, ny,
+                         nx, k, iso, rt, kc, n_samples, sp.per_split, key0, key1, out, plane);
+  }
+  if (!ranked && vertex)
+    hipLaunchKernelGGL((mc_vertex_kernel<KC, false, T>), grid, dim3(kBlock), 0, s, m0, v0, m1, v1,
+                       ny, nx, k, iso, kc, n_samples, sp.per_split, key0, key1, rt, out, plane);
+  else if (!ranked)
+    hipLaunchKernelGGL((mc_kernel<KC, false, T>), grid, dim3(kBlock), 0, s, m0, v0, m1, v1, ny, nx,
+                       k, iso, rt, kc, n_samples, sp.per_split, key0, key1, out, plane);
+  if (sp.splits > 1) {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(mc_finish_kernel, fill_grid, dim3(kBlock), 0, s, out, n_out,
+                       static_cast<float>(n_samples));
+  }
   return hipGetLastError();
 }
 

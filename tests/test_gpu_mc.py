@@ -241,3 +241,29 @@ def test_unknown_mode_is_rejected():
     ts = moments_dev(f)
     with pytest.raises(ValueError):
         P.mc_lcp(*ts, [0.0], n_samples=4, seed=1, mode="pixel")
+
+
+@pytest.mark.parametrize("mode", ["vector", "vertex"])
+@pytest.mark.parametrize("shape,s,k", [((2, 2), 15, 1), ((2, 2), 17, 8), ((33, 33), 31, 2),
+                                       ((34, 66), 64, 9), ((34, 66), 129, 16),
+                                       ((65, 33), 1001, 1)])
+def test_samples_split_over_blocks_match_oracle(shape, s, k, mode):
+    """Small grids share a tile's samples between blocks (counts added as
+    integers, then divided): sample counts below, at and past the smallest
+    split, odd ones and ones whose last split is short, against the oracle's
+    float32-decision counts, with ragged tiles.  The output holds other values
+    beforehand, and a second call on it gives the same maps."""
+    ny, nx = shape
+    f = synth.gen_moments(ny, nx, seed=3 * ny + nx, sigma=(0.05, 0.5))
+    ts = moments_dev(f)
+    iso = np.random.default_rng(s).uniform(-0.15, 0.15, k).astype(np.float32)
+    out = torch.full((k, ny - 1, nx - 1), float("nan"), device="cuda")
+    first = P.mc_lcp(*ts, iso, n_samples=s, seed=s, out=out, mode=mode).clone()
+    again = P.mc_lcp(*ts, iso, n_samples=s, seed=s, out=out, mode=mode)
+    assert torch.equal(first, again)
+    r = O.mc_lcp(*stored64(ts), 1.0, 1.0, iso, s, s, precision="f32", mode=mode)
+    flips = np.abs(np.rint(host64(first) * s) - np.rint(r * s))
+    assert flips.sum() <= 5 + 1e-5 * flips.size * s, flips.sum()
+    # a whole count over the sample count, as one block would have stored it
+    counts = np.rint(host64(first) * s).astype(np.float32)
+    assert np.array_equal(first.cpu().numpy(), counts / np.float32(s))
