@@ -26,12 +26,7 @@ static std::atomic<int> g_band_rows_override{0};
 
 void set_band_rows_override(int rows) { g_band_rows_override.store(rows); }
 
-// Rows per band: each band re-reads two halo rows and re-evaluates one corner
-// row, and short bands give more waves to even out the tail of the launch.
-// On gfx950, 8191 x 8191 cells at K = 16: the paired tile (64 strips) ran
-// 1.26 ms with 64-row bands against 1.32 (48 rows), 1.37 (96) and 1.30 (128);
-// the split tile (65 strips, dense rows) 1.45 ms with 16-row bands against
-// 1.50 (8) and 1.55 (64).  0 in band_rows: this choice, made per layout.
+// band_rows 0: lcp_band_rows, per layout and size.
 LcpShape default_lcp_shape(int64_t ny, int64_t nx, int n_iso) {
   (void)nx;
   (void)n_iso;
@@ -40,12 +35,6 @@ LcpShape default_lcp_shape(int64_t ny, int64_t nx, int n_iso) {
   s.band_rows = g_band_rows_override.load();
   s.poison = (debug_flags() & PDIV_DEBUG_POISON_LDS) != 0;
   return s;
-}
-
-int band_rows_for(const LcpShape& s, int64_t ny, bool paired) {
-  if (s.band_rows > 0) return s.band_rows;
-  if (ny <= 4096) return 32;
-  return paired ? 64 : 16;
 }
 
 namespace {
@@ -188,12 +177,16 @@ __global__ __launch_bounds__(kBlock) void lcp_kernel_split(
 // Dynamic LDS that leaves room for only two 4-wave blocks of `kernel` per CU
 // (160 KiB of LDS: 3 x 54 KiB does not fit), i.e. two waves per SIMD instead
 // of the three its registers allow.  The fused kernel's stores into rows that
-// start inside a 128-byte line, and its launches at up to 4 isovalues, run
-// faster with fewer waves writing at once (8192^2 at 16 isovalues into dense
-// maps: 1.35 against 1.45 ms; at 8: 0.73 against 0.80 ms; line-aligned rows
-// at 4 isovalues: 0.403 against 0.418 ms; line-aligned at 16: unchanged).
+// start inside a 128-byte line, and its launches at up to 4 isovalues on large
+// maps, run faster with fewer waves writing at once (8192^2 at 16 isovalues
+// into dense maps: 1.30 against 1.37 ms; at 8: 0.71 against 0.76 ms;
+// line-aligned rows at 4 isovalues: 0.413 against 0.425 ms; line-aligned at
+// 16: unchanged).  Line-aligned maps of fewer cells fit the caches better and
+// want the waves (at 1 / 4 isovalues 2047x3001 29.5 / 45.6 us at two waves,
+// 25.5 / 43.3 without the limit; 5792^2 142 / 223 against 136 / 219).
 // Zero if the attributes cannot be read (the launch then runs at the usual
 // occupancy).
+constexpr int64_t kTwoWaveCells = int64_t(48) << 20;
 template <typename Kernel>
 size_t two_waves_per_simd_lds(Kernel kernel) {
   hipFuncAttributes a{};
@@ -210,13 +203,15 @@ hipError_t launch_kc(const void* p0, const void* p1, const void* p2, const void*
                      int nx, const StencilCoef& k, const IsoChunk& iso, float* out,
                      int64_t pitch, int64_t plane, LcpShape shape, hipStream_t s) {
   const int64_t n_cells = int64_t(ny - 1) * (nx - 1);
-  const bool lines = use_paired_tile(out, pitch, plane, KC, n_cells);
-  // the fused kernel takes the paired tile on other rows too (default policy)
-  const bool unaligned = FUSED && !lines && use_paired_unaligned(KC, n_cells);
-  const bool paired = lines || unaligned;
+  const bool lines = rows_on_lines(out, pitch, plane);
+  // the LDS check runs the staged tile at every size
+  const bool paired = use_paired_tile(FUSED, lines, KC, n_cells) ||
+                      (FUSED && std::is_same<T, float>::value && shape.poison);
+  const bool unaligned = paired && !lines;  // fused only: default store policy
   const int cells = cells_per_wave(paired);
-  const int band_rows = band_rows_for(shape, ny, paired);
   const int n_strips = (nx - 1 + cells - 1) / cells;
+  const int band_rows =
+      shape.band_rows > 0 ? shape.band_rows : lcp_band_rows(n_strips, ny - 1, paired);
   const int n_bands = (ny - 1 + band_rows - 1) / band_rows;
   const int64_t waves = static_cast<int64_t>(n_strips) * n_bands;
   if (!launch_fits((waves + kWavesPerBlock - 1) / kWavesPerBlock, kBlock))
@@ -255,7 +250,7 @@ hipError_t launch_kc(const void* p0, const void* p1, const void* p2, const void*
     size_t lds = 0;
     if constexpr (FUSED && KC <= 4) {
       static const size_t two = two_waves_per_simd_lds(lcp_kernel_paired<KC, FUSED, T>);
-      lds = two;
+      if (n_cells >= kTwoWaveCells) lds = two;
     }
     hipLaunchKernelGGL((lcp_kernel_paired<KC, FUSED, T>), dim3(blocks), dim3(kBlock), lds, s,
                        static_cast<const T*>(p0), static_cast<const T*>(p1),

@@ -29,16 +29,15 @@
 // by the neighbour (XCD-contiguous strips share an L2).  It runs the same
 // arithmetic with the LDS-staged rows, launched at two waves per SIMD (the
 // launcher reserves LDS: fewer waves writing at once complete more shared
-// lines in L2); at 8192^2 into dense maps it takes 0.46 / 0.73 / 1.35 ms at
-// 4 / 8 / 16 isovalues (0.50 / 0.80 / 1.455 ms at three waves per SIMD)
-// against 0.40 / 0.66 / 1.07 ms into line-aligned rows (with the streaming
-// policy 0.578 / 0.974 / 1.760 ms at three waves; the split tile 1.51 ms at
-// 16).
+// lines in L2); at 8192^2 into dense maps it takes 0.45 / 0.71 / 1.30 ms at
+// 4 / 8 / 16 isovalues (0.47 / 0.76 / 1.37 ms at three waves per SIMD)
+// against 0.41 / 0.65 / 1.11 ms into line-aligned rows (with the streaming
+// policy 0.578 / 0.974 / 1.760 ms at three waves; the split tile 0.49 / 0.77 /
+// 1.34 ms).
 //
 // Split (lcp_tile_split), for the other outputs (the two-step path on rows
-// that start inside a line, and small maps with few isovalues, where a
-// launch's fixed cost dominates and is lower for this tile: use_paired_tile
-// below): a wave owns 127 vertex columns, the 126 cells [x0, x0+126),
+// that start inside a line, and maps that the caches hold, where whole-line
+// stores gain nothing: use_paired_tile below): a wave owns 127 vertex columns, the 126 cells [x0, x0+126),
 // x0 = 126 strip.  Lane L holds columns A = x0+L and B = x0+63+L (lane 63's
 // A repeats lane 0's B), forms cells (A, A+1) and (B, B+1) with the right
 // pair from lane L+1, and lanes 0..62 write 63 consecutive cells per store.
@@ -692,25 +691,55 @@ __device__ __forceinline__ void lcp_tile_split(const T* __restrict__ p0, const T
   if (j < j1) step(a1, b1, j, pa, pb, qa, qb);  // a1/b1 hold row j + 1 == j1
 }
 
-// Layout choice: the paired tile when every output row starts on a 128-byte
-// line (base aligned, row pitch and plane stride multiples of 32 floats) and
-// either there are at least 8 isovalues or the map has at least 2^22 cells
-// (use_paired_tile); under the same size rule the fused kernel also takes it
-// for other rows (use_paired_unaligned), with the default store policy.
-// On large maps its whole-line stores outweigh the seam step at any
-// isovalue count (8192^2, rows interleaved, paired against split: 0.269 /
-// 0.293 ms at 1 isovalue, 0.318 / 0.360 ms at 2, 0.430 / 0.497 ms at 4;
-// 4096^2: 62 / 76 us at 1, 103 / 142 us at 4); on small maps with few
-// isovalues the launch is dominated by its fixed cost, which is lower for
-// the split tile (up to 1024^2: 16 against 24 us at 1 isovalue, 26 against
-// 35 us at 4).
-inline bool use_paired_tile(const float* out, int64_t pitch, int64_t plane, int kc,
-                            int64_t cells) {
-  return (reinterpret_cast<uintptr_t>(out) % 128 == 0) && (pitch % 32 == 0) &&
-         (plane % 32 == 0) && (kc >= 8 || cells >= (int64_t(1) << 22));
+// Whether every output row starts on a 128-byte line.
+inline bool rows_on_lines(const float* out, int64_t pitch, int64_t plane) {
+  return (reinterpret_cast<uintptr_t>(out) % 128 == 0) && (pitch % 32 == 0) && (plane % 32 == 0);
 }
-inline bool use_paired_unaligned(int kc, int64_t cells) {
-  return kc >= 8 || cells >= (int64_t(1) << 22);
+
+// Layout choice, from float32 maps of 300^2 to 8192^2 cells at the best band
+// height of each tile, three sets of buffers in turn (split against paired,
+// us).  The paired tile's whole-line stores pay once the maps outgrow the
+// caches; its seam step and, fused, its staged rows cost more than they
+// save below that.
+//   fused, rows on lines: at 1, 2, 4 isovalues 721x1440 6.8 / 9.5, 8.1 / 10.8,
+//     11.0 / 13.1, 1448^2 16.2 / 19.4 at 4, 2047x3001 28.0 / 25.5, 34.4 /
+//     30.9, 49.6 / 43.3: paired from 2^22 cells; at 8 and more 721x1440 15.5 /
+//     17.3 (16: 27.1 / 27.1), 1448^2 32.5 / 26.8 and 55.7 / 42.8: paired from
+//     1.25 M cells.
+//   fused, other rows (default store policy): 2047x3001 at 1, 4, 8, 16
+//     isovalues 27.8 / 28.7, 48.9 / 49.1, 78.2 / 76.3, 135.5 / 131.7;
+//     3000x3500 49.4 / 52.3, 82.7 / 85.4, 125.9 / 131.4, 233 / 227; 4096^2
+//     77.8 / 74.4, 130.9 / 122, 202 / 190, 357 / 334: paired from 12 M cells,
+//     at 12 and more isovalues from 6 M.
+//   two-step, rows on lines: 721x1440 4.4 / 5.1 at 1 isovalue, 9.5 / 8.4 at 4,
+//     24.3 / 23.0 at 16; 4096^2 43.9 / 44.3, 99.5 / 83.1, 339 / 268: paired
+//     except at 1 isovalue and on the smallest maps (300^2: equal).
+//   two-step, other rows: split only.
+inline bool use_paired_tile(bool fused, bool lines, int kc, int64_t cells) {
+  constexpr int64_t kM = 1000000;
+  if (!fused) return lines && kc >= 2 && cells >= kM / 4;
+  if (lines) return cells >= (kc >= 8 ? kM * 5 / 4 : int64_t(1) << 22);
+  return cells >= (kc >= 12 ? 6 * kM : 12 * kM);
+}
+
+// Cell rows per wave band.  A band re-evaluates one corner row and re-reads
+// two input rows, so tall bands do less work; but a wave walks its band row
+// by row, so a grid of few tall bands leaves SIMDs idle while a few waves
+// walk (500x500, 1 isovalue, fused: 15.9 us with 32-row bands, 9.3 / 6.0 /
+// 4.3 / 3.6 / 3.4 us with 16 / 8 / 4 / 2 / 1; 721x1440, 8 isovalues: 45 /
+// 26 / 20 / 16.7 / 15.7 / 17.6 us with 32 ... 1).  The tallest band that still
+// gives two rounds of the three waves per SIMD the tiles run at (6144 waves on
+// 1024 SIMDs); bands of 4 and 2 rows do with fewer waves, as their redundant
+// row costs more.  The split tile gains nothing from bands over 8 rows at any
+// size (8192^2, 16 isovalues, two-step: 1.30 ms with 8 rows, 1.41 / 1.44 / 1.50
+// with 16 / 32 / 64); the paired one takes up to 64 (8192^2 fused, 16
+// isovalues: 1.106 ms, 1.125 / 1.174 / 1.176 with 32 / 16 / 8; 5792^2: 656,
+// 601, 593, 608 us with 64 / 32 / 16 / 8).
+inline int lcp_band_rows(int64_t strips, int64_t rows, bool paired) {
+  auto waves = [&](int b) { return strips * ((rows + b - 1) / b); };
+  for (int b = paired ? 64 : 8; b >= 8; b /= 2)
+    if (waves(b) >= 6000) return b;
+  return waves(4) >= 3000 ? 4 : waves(2) >= 1500 ? 2 : 1;
 }
 
 // The tile of layout PAIRED.  STREAM: non-temporal stores (for rows that

@@ -496,6 +496,47 @@ def test_unaligned_paired_tile_large_map_and_poison():
     assert err_report(host64(dense[:, a:b, :]), want)["max_abs"] <= LCP_TOL
 
 
+# Sizes on both sides of where the tile layout changes (fused, rows on lines:
+# 1.25 M cells at 8 and more isovalues, 2^22 below; other rows: 12 M, 6 M from
+# 12 isovalues; two-step: 0.25 M from 2) and of the band heights: one strip to
+# many, bands of 1, 2, 4, 8 rows and more, a single row.
+@pytest.mark.parametrize("shape,ks", [((2, 2), (1, 16)), ((2, 5000), (1, 8)), ((700, 2), (2, 16)),
+                                      ((68, 68), (1, 8)), ((300, 257), (4,)), ((502, 500), (2, 16)),
+                                      ((721, 1440), (8,)), ((1121, 1130), (8,)),
+                                      ((2049, 2049), (1,)), ((2452, 2450), (16,)),
+                                      ((8, 1750001), (1,)), ((3501, 3470), (4,))])
+def test_tile_choice_and_band_heights(shape, ks):
+    """Every layout and band height the launcher picks gives bitwise the maps
+    of the two-step path at a fixed band height, into dense maps, maps one
+    float into their buffer and line-aligned rows, and the first rows are
+    within 1e-5 of the oracle."""
+    ny, nx = shape
+    rng = np.random.default_rng(ny + nx)
+    f = {"mean_u": rng.normal(0, 0.3, shape), "var_u": rng.uniform(0.01, 0.25, shape),
+         "mean_v": rng.normal(0, 0.3, shape), "var_v": rng.uniform(0.01, 0.25, shape)}
+    ts = moments_dev(f)
+    div = P.divergence_gaussian(*ts)
+    rows = min(ny, 40)  # vertex rows of the oracle's part; its cells but the last row
+    rm, rv = O.divergence_gaussian(*[m[:rows] for m in stored64(ts)], 1.0, 1.0)
+    for k in ks:
+        iso = np.linspace(-0.4, 0.4, k).astype(np.float32)
+        try:
+            P.set_lcp_band_rows(5)
+            ref = P.lcp(*div, iso)
+        finally:
+            P.set_lcp_band_rows(0)
+        flat = torch.full((ref.numel() + 8,), -7.0, device="cuda")
+        shifted = flat[1:1 + ref.numel()].view(ref.shape)
+        for got in (P.lcp(*div, iso), P.lcp(*div, iso, out=P.empty_lcp(k, ny, nx)),
+                    P.lcp_from_moments(*ts, iso), P.lcp_from_moments(*ts, iso, out=shifted),
+                    P.lcp_from_moments(*ts, iso, out=P.empty_lcp(k, ny, nx))):
+            assert torch.equal(got, ref), k
+        assert float(flat[0]) == -7.0 and bool((flat[1 + ref.numel():] == -7.0).all())
+        top = rows - 1 if rows == ny else rows - 2
+        want = O.lcp(rm, rv, iso)[:, :top]
+        assert err_report(host64(ref[:, :top]), want)["max_abs"] <= LCP_TOL
+
+
 def test_input_checks_reject_bad_values():
     """PDIV_DEBUG_CHECK_INPUTS: a negative variance or a non-finite mean is
     reported as PDIV_ERR_INVALID before any work; admissible inputs pass and
