@@ -30,7 +30,6 @@ struct alignas(16) BatchField {
   StencilCoef coef;
 };
 
-int iso_bucket(int n);
 // Kernel for a batch: fused (moments of dtype dt) or two-step (float planes),
 // paired or split tile layout.
 const void* batch_kernel_ptr(bool fused, pdiv_dtype dt, int kc, bool paired);

@@ -124,16 +124,18 @@ __global__ __launch_bounds__(kBlock) void divergence_kernel(const T* __restrict_
   }
 }
 
-template <int KC, bool FUSED, bool PAIRED, typename T, bool POISON = false,
+// ALL: every slot holds an isovalue (a count known to the compiler); else the
+// slots from n_store on store nothing.
+template <int KC, bool FUSED, bool PAIRED, bool ALL, typename T, bool POISON = false,
           bool STREAM = PAIRED>
 __device__ __forceinline__ void lcp_body(const T* __restrict__ p0,
                                                      const T* __restrict__ p1,
                                                      const T* __restrict__ p2,
                                                      const T* __restrict__ p3, int ny, int nx,
                                                      StencilCoef k, IsoChunk iso,
-                                                     float* __restrict__ out, int64_t plane,
-                                                     int64_t pitch, int band_rows, int n_strips,
-                                                     int n_bands) {
+                                                     int n_store, float* __restrict__ out,
+                                                     int64_t plane, int64_t pitch, int band_rows,
+                                                     int n_strips, int n_bands) {
   // Blocks are dealt round-robin to the 8 XCDs (block b runs on XCD b % 8),
   // each with its own L2.  Give each XCD a contiguous run of tiles, so that
   // neighbouring strips, whose output rows meet inside a cache line, write
@@ -146,8 +148,9 @@ __device__ __forceinline__ void lcp_body(const T* __restrict__ p0,
   const int band = wave / n_strips;
   if (band >= n_bands) return;
   const int j0 = band * band_rows;
-  lcp_tile<KC, FUSED, PAIRED, T, POISON, STREAM>(p0, p1, p2, p3, ny, nx, k, iso, KC, out, plane,
-                                                 pitch, strip, j0, min(j0 + band_rows, ny - 1));
+  lcp_tile<KC, FUSED, PAIRED, T, POISON, STREAM>(p0, p1, p2, p3, ny, nx, k, iso,
+                                                 ALL ? KC : n_store, out, plane, pitch, strip, j0,
+                                                 min(j0 + band_rows, ny - 1));
 }
 
 // Paired-layout kernel: asks the compiler for three waves per SIMD (at most
@@ -155,23 +158,25 @@ __device__ __forceinline__ void lcp_body(const T* __restrict__ p0,
 // one spill costs less than the third wave's absence or the per-row moves of
 // a single set (measured on gfx950 at 8192^2, K = 16: 1.144 ms against 1.151).
 // STREAM = false: the fused kernel on rows that start inside a line.
-template <int KC, bool FUSED, typename T, bool POISON = false, bool STREAM = true>
+template <int KC, bool FUSED, bool ALL, typename T, bool POISON = false, bool STREAM = true>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void lcp_kernel_paired(
     const T* __restrict__ p0, const T* __restrict__ p1, const T* __restrict__ p2,
-    const T* __restrict__ p3, int ny, int nx, StencilCoef k, IsoChunk iso, float* __restrict__ out,
-    int64_t plane, int64_t pitch, int band_rows, int n_strips, int n_bands) {
-  lcp_body<KC, FUSED, true, T, POISON, STREAM>(p0, p1, p2, p3, ny, nx, k, iso, out, plane, pitch,
-                                               band_rows, n_strips, n_bands);
+    const T* __restrict__ p3, int ny, int nx, StencilCoef k, IsoChunk iso, int n_store,
+    float* __restrict__ out, int64_t plane, int64_t pitch, int band_rows, int n_strips,
+    int n_bands) {
+  lcp_body<KC, FUSED, true, ALL, T, POISON, STREAM>(p0, p1, p2, p3, ny, nx, k, iso, n_store, out,
+                                                    plane, pitch, band_rows, n_strips, n_bands);
 }
 
 // Split-layout kernel (its tile has no LDS ring; two waves per SIMD).
-template <int KC, bool FUSED, typename T>
+template <int KC, bool FUSED, bool ALL, typename T>
 __global__ __launch_bounds__(kBlock) void lcp_kernel_split(
     const T* __restrict__ p0, const T* __restrict__ p1, const T* __restrict__ p2,
-    const T* __restrict__ p3, int ny, int nx, StencilCoef k, IsoChunk iso, float* __restrict__ out,
-    int64_t plane, int64_t pitch, int band_rows, int n_strips, int n_bands) {
-  lcp_body<KC, FUSED, false>(p0, p1, p2, p3, ny, nx, k, iso, out, plane, pitch, band_rows,
-                             n_strips, n_bands);
+    const T* __restrict__ p3, int ny, int nx, StencilCoef k, IsoChunk iso, int n_store,
+    float* __restrict__ out, int64_t plane, int64_t pitch, int band_rows, int n_strips,
+    int n_bands) {
+  lcp_body<KC, FUSED, false, ALL>(p0, p1, p2, p3, ny, nx, k, iso, n_store, out, plane, pitch,
+                                  band_rows, n_strips, n_bands);
 }
 
 // Dynamic LDS that leaves room for only two 4-wave blocks of `kernel` per CU
@@ -198,9 +203,9 @@ size_t two_waves_per_simd_lds(Kernel kernel) {
   return a.sharedSizeBytes < kPerBlock ? kPerBlock - a.sharedSizeBytes : 0;
 }
 
-template <int KC, bool FUSED, typename T>
+template <int KC, bool FUSED, bool ALL, typename T>
 hipError_t launch_kc(const void* p0, const void* p1, const void* p2, const void* p3, int ny,
-                     int nx, const StencilCoef& k, const IsoChunk& iso, float* out,
+                     int nx, const StencilCoef& k, const IsoChunk& iso, int n_store, float* out,
                      int64_t pitch, int64_t plane, LcpShape shape, hipStream_t s) {
   const int64_t n_cells = int64_t(ny - 1) * (nx - 1);
   const bool lines = rows_on_lines(out, pitch, plane);
@@ -221,47 +226,47 @@ hipError_t launch_kc(const void* p0, const void* p1, const void* p2, const void*
     // the checking variant exists for the fused float32 kernel only
     if (paired && shape.poison) {
       if (unaligned)
-        hipLaunchKernelGGL((lcp_kernel_paired<KC, FUSED, T, true, false>), dim3(blocks),
+        hipLaunchKernelGGL((lcp_kernel_paired<KC, FUSED, false, T, true, false>), dim3(blocks),
                            dim3(kBlock), 0, s, static_cast<const T*>(p0),
                            static_cast<const T*>(p1), static_cast<const T*>(p2),
-                           static_cast<const T*>(p3), ny, nx, k, iso, out, plane, pitch,
-                           band_rows, n_strips, n_bands);
+                           static_cast<const T*>(p3), ny, nx, k, iso, n_store, out, plane,
+                           pitch, band_rows, n_strips, n_bands);
       else
-        hipLaunchKernelGGL((lcp_kernel_paired<KC, FUSED, T, true>), dim3(blocks), dim3(kBlock),
+        hipLaunchKernelGGL((lcp_kernel_paired<KC, FUSED, false, T, true>), dim3(blocks), dim3(kBlock),
                            0, s, static_cast<const T*>(p0), static_cast<const T*>(p1),
                            static_cast<const T*>(p2), static_cast<const T*>(p3), ny, nx, k, iso,
-                           out, plane, pitch, band_rows, n_strips, n_bands);
+                           n_store, out, plane, pitch, band_rows, n_strips, n_bands);
       return hipGetLastError();
     }
   }
   if constexpr (FUSED) {
     if (unaligned) {
       static const size_t lds =
-          two_waves_per_simd_lds(lcp_kernel_paired<KC, FUSED, T, false, false>);
-      hipLaunchKernelGGL((lcp_kernel_paired<KC, FUSED, T, false, false>), dim3(blocks),
+          two_waves_per_simd_lds(lcp_kernel_paired<KC, FUSED, ALL, T, false, false>);
+      hipLaunchKernelGGL((lcp_kernel_paired<KC, FUSED, ALL, T, false, false>), dim3(blocks),
                          dim3(kBlock), lds, s, static_cast<const T*>(p0),
                          static_cast<const T*>(p1), static_cast<const T*>(p2),
-                         static_cast<const T*>(p3), ny, nx, k, iso, out, plane, pitch, band_rows,
-                         n_strips, n_bands);
+                         static_cast<const T*>(p3), ny, nx, k, iso, n_store, out, plane, pitch,
+                         band_rows, n_strips, n_bands);
       return hipGetLastError();
     }
   }
   if (paired) {
     size_t lds = 0;
     if constexpr (FUSED && KC <= 4) {
-      static const size_t two = two_waves_per_simd_lds(lcp_kernel_paired<KC, FUSED, T>);
+      static const size_t two = two_waves_per_simd_lds(lcp_kernel_paired<KC, FUSED, ALL, T>);
       if (n_cells >= kTwoWaveCells) lds = two;
     }
-    hipLaunchKernelGGL((lcp_kernel_paired<KC, FUSED, T>), dim3(blocks), dim3(kBlock), lds, s,
+    hipLaunchKernelGGL((lcp_kernel_paired<KC, FUSED, ALL, T>), dim3(blocks), dim3(kBlock), lds, s,
                        static_cast<const T*>(p0), static_cast<const T*>(p1),
-                       static_cast<const T*>(p2), static_cast<const T*>(p3), ny, nx, k, iso, out,
-                       plane, pitch, band_rows, n_strips, n_bands);
+                       static_cast<const T*>(p2), static_cast<const T*>(p3), ny, nx, k, iso, n_store,
+                       out, plane, pitch, band_rows, n_strips, n_bands);
   }
   else
-    hipLaunchKernelGGL((lcp_kernel_split<KC, FUSED, T>), dim3(blocks), dim3(kBlock), 0, s,
+    hipLaunchKernelGGL((lcp_kernel_split<KC, FUSED, ALL, T>), dim3(blocks), dim3(kBlock), 0, s,
                        static_cast<const T*>(p0), static_cast<const T*>(p1),
-                       static_cast<const T*>(p2), static_cast<const T*>(p3), ny, nx, k, iso, out,
-                       plane, pitch, band_rows, n_strips, n_bands);
+                       static_cast<const T*>(p2), static_cast<const T*>(p3), ny, nx, k, iso, n_store,
+                       out, plane, pitch, band_rows, n_strips, n_bands);
   return hipGetLastError();
 }
 
@@ -269,12 +274,24 @@ template <bool FUSED, typename T>
 hipError_t launch_any(const void* p0, const void* p1, const void* p2, const void* p3, int ny,
                       int nx, const StencilCoef& k, const IsoChunk& iso, int kc, float* out,
                       int64_t pitch, int64_t plane, LcpShape shape, hipStream_t s) {
-  switch (kc) {
-    case 1: return launch_kc<1, FUSED, T>(p0, p1, p2, p3, ny, nx, k, iso, out, pitch, plane, shape, s);
-    case 2: return launch_kc<2, FUSED, T>(p0, p1, p2, p3, ny, nx, k, iso, out, pitch, plane, shape, s);
-    case 4: return launch_kc<4, FUSED, T>(p0, p1, p2, p3, ny, nx, k, iso, out, pitch, plane, shape, s);
-    case 8: return launch_kc<8, FUSED, T>(p0, p1, p2, p3, ny, nx, k, iso, out, pitch, plane, shape, s);
-    case 16: return launch_kc<16, FUSED, T>(p0, p1, p2, p3, ny, nx, k, iso, out, pitch, plane, shape, s);
+  switch (iso_bucket(kc)) {
+#define PDIV_KC(K, ALL)                                                                       \
+  return launch_kc<K, FUSED, ALL, T>(p0, p1, p2, p3, ny, nx, k, iso, kc, out, pitch, plane, \
+                                     shape, s)
+    case 1: PDIV_KC(1, true);
+    case 2: PDIV_KC(2, true);
+    case 3: PDIV_KC(3, true);
+    case 4: PDIV_KC(4, true);
+    case 6: PDIV_KC(6, false);
+    case 8:
+      if (kc == 8) PDIV_KC(8, true);
+      PDIV_KC(8, false);
+    case 12: PDIV_KC(12, false);
+    case 16:
+      // all 16 slots: 1.066 ms at 8192^2 fused, 1.093 with the run-time count
+      if (kc == 16) PDIV_KC(16, true);
+      PDIV_KC(16, false);
+#undef PDIV_KC
   }
   return hipErrorInvalidValue;
 }

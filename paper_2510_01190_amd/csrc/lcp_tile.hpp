@@ -728,17 +728,21 @@ inline bool use_paired_tile(bool fused, bool lines, int kc, int64_t cells) {
 // walk (500x500, 1 isovalue, fused: 15.9 us with 32-row bands, 9.3 / 6.0 /
 // 4.3 / 3.6 / 3.4 us with 16 / 8 / 4 / 2 / 1; 721x1440, 8 isovalues: 45 /
 // 26 / 20 / 16.7 / 15.7 / 17.6 us with 32 ... 1).  The tallest band that still
-// gives two rounds of the three waves per SIMD the tiles run at (6144 waves on
-// 1024 SIMDs); bands of 4 and 2 rows do with fewer waves, as their redundant
-// row costs more.  The split tile gains nothing from bands over 8 rows at any
+// gives about two rounds of the two or three waves per SIMD the tiles run at
+// (1024 SIMDs; just over one round, 5792^2 with 64 rows, is the worst);
+// bands of 4 and 2 rows do with fewer waves, as their redundant row costs
+// more.  The split tile gains nothing from bands over 8 rows at any
 // size (8192^2, 16 isovalues, two-step: 1.30 ms with 8 rows, 1.41 / 1.44 / 1.50
 // with 16 / 32 / 64); the paired one takes up to 64 (8192^2 fused, 16
 // isovalues: 1.106 ms, 1.125 / 1.174 / 1.176 with 32 / 16 / 8; 5792^2: 656,
-// 601, 593, 608 us with 64 / 32 / 16 / 8).
+// 601, 593, 608 us with 64 / 32 / 16 / 8; 4096^2 into dense maps 343, 334, 337,
+// 348 us).
 inline int lcp_band_rows(int64_t strips, int64_t rows, bool paired) {
   auto waves = [&](int b) { return strips * ((rows + b - 1) / b); };
-  for (int b = paired ? 64 : 8; b >= 8; b /= 2)
-    if (waves(b) >= 6000) return b;
+  if (paired && waves(64) >= 8000) return 64;
+  if (paired && waves(32) >= 4000) return 32;
+  if (paired && waves(16) >= 6000) return 16;
+  if (waves(8) >= 6000) return 8;
   return waves(4) >= 3000 ? 4 : waves(2) >= 1500 ? 2 : 1;
 }
 

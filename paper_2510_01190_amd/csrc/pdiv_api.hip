@@ -171,10 +171,11 @@ pdiv_status lcp_chunks(bool fused, const void* p0, const void* p1, const void* p
   const StencilCoef k = make_coef(dx, dy);
   const int64_t plane = lo.plane;
   const LcpShape shape = default_lcp_shape(ny, nx, n_iso);
-  // chunks of 16, 8, 4, 2, 1 isovalues (the kernel is instantiated for these)
+  // chunks of up to 16 isovalues, each one launch that reads the field once
+  // (the unused slots of its bucket, iso_bucket, repeat the last isovalue and
+  // store nothing)
   for (int32_t k0 = 0; k0 < n_iso;) {
-    const int left = n_iso - k0;
-    const int kc = left >= 16 ? 16 : left >= 8 ? 8 : left >= 4 ? 4 : left >= 2 ? 2 : 1;
+    const int kc = std::min(n_iso - k0, kIsoChunk);
     IsoChunk c;
     for (int q = 0; q < kIsoChunk; ++q) c.c[q] = iso_host[k0 + (q < kc ? q : kc - 1)];
     hipError_t e = launch_lcp(fused, p0, p1, p2, p3, dt, ny, nx, k, c, kc, lcp + k0 * plane,

@@ -74,8 +74,11 @@ const void* kernel_for(int kc) {
   switch (kc) {
     case 1: return reinterpret_cast<const void*>(&batch_kernel<1, FUSED, PAIRED, T>);
     case 2: return reinterpret_cast<const void*>(&batch_kernel<2, FUSED, PAIRED, T>);
+    case 3: return reinterpret_cast<const void*>(&batch_kernel<3, FUSED, PAIRED, T>);
     case 4: return reinterpret_cast<const void*>(&batch_kernel<4, FUSED, PAIRED, T>);
+    case 6: return reinterpret_cast<const void*>(&batch_kernel<6, FUSED, PAIRED, T>);
     case 8: return reinterpret_cast<const void*>(&batch_kernel<8, FUSED, PAIRED, T>);
+    case 12: return reinterpret_cast<const void*>(&batch_kernel<12, FUSED, PAIRED, T>);
     case 16: return reinterpret_cast<const void*>(&batch_kernel<16, FUSED, PAIRED, T>);
   }
   return nullptr;
@@ -93,8 +96,6 @@ const void* kernel_for_dtype(bool fused, pdiv_dtype dt, int kc) {
 }
 
 }  // namespace
-
-int iso_bucket(int n) { return n <= 1 ? 1 : n <= 2 ? 2 : n <= 4 ? 4 : n <= 8 ? 8 : 16; }
 
 const void* batch_kernel_ptr(bool fused, pdiv_dtype dt, int kc, bool paired) {
   return paired ? kernel_for_dtype<true>(fused, dt, kc) : kernel_for_dtype<false>(fused, dt, kc);

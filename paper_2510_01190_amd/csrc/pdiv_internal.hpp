@@ -76,6 +76,17 @@ hipError_t launch_divergence(const void* mu, const void* vu, const void* mv, con
                              pdiv_dtype dt, int64_t ny, int64_t nx, const StencilCoef& k,
                              float* dmean, float* dvar, hipStream_t s);
 
+// Isovalue slots of the closed-form kernel that serves n isovalues (n <= 16):
+// the kernels exist for 1, 2, 3, 4, 6, 8, 12 and 16.  A launch of the next
+// larger one evaluates up to a third more tails than it stores, but reads the
+// field once, where chunks of powers of two read it up to four times (15 = 8 +
+// 4 + 2 + 1).  At 2047x3001, fused into dense
+// maps, against those chunks: 45 / 71 us at 3 isovalues, 61 / 87 at 5, 76 /
+// 123 at 7, 107 / 154 at 11, 144 / 211 at 15.
+constexpr int iso_bucket(int n) {
+  return n <= 4 ? (n < 1 ? 1 : n) : n <= 6 ? 6 : n <= 8 ? 8 : n <= 12 ? 12 : 16;
+}
+
 // LCP for isovalues [k0, k0+kc) (kc <= 16): from divergence Gaussians
 // (fused = false, planes dmean/dvar as float) or from moments (fused = true).
 // Output rows are `pitch` floats apart, planes `plane` floats.

@@ -537,6 +537,30 @@ def test_tile_choice_and_band_heights(shape, ks):
         assert err_report(host64(ref[:, :top]), want)["max_abs"] <= LCP_TOL
 
 
+@pytest.mark.parametrize("shape", [(2, 2), (67, 131), (1500, 1201)])
+def test_every_isovalue_count_in_one_launch(shape):
+    """Counts between the kernel's slot counts (1, 2, 3, 4, 6, 8, 12, 16) leave
+    slots that store nothing: every count's maps are bitwise the ones computed
+    one isovalue at a time, fused and two-step, dense, line-aligned and
+    interleaved, and nothing is written beyond the last map."""
+    ny, nx = shape
+    rng = np.random.default_rng(nx)
+    ts = moments_dev({"mean_u": rng.normal(0, 0.3, shape), "var_u": rng.uniform(0.01, 0.25, shape),
+                      "mean_v": rng.normal(0, 0.3, shape), "var_v": rng.uniform(0.01, 0.25, shape)})
+    div = P.divergence_gaussian(*ts)
+    iso = rng.uniform(-0.5, 0.5, 18).astype(np.float32)
+    ref = torch.cat([P.lcp(*div, [c]) for c in iso])
+    want = O.lcp(*O.divergence_gaussian(*stored64(ts), 1.0, 1.0), iso[:3])
+    assert err_report(host64(ref[:3]), want)["max_abs"] <= LCP_TOL
+    for k in range(2, 19):
+        flat = torch.full(((k + 2) * (ny - 1) * (nx - 1),), -7.0, device="cuda")
+        dense = flat[:k * (ny - 1) * (nx - 1)].view(k, ny - 1, nx - 1)
+        for out in (dense, P.empty_lcp(k, ny, nx), P.empty_lcp(k, ny, nx, interleave_rows=True)):
+            assert torch.equal(P.lcp_from_moments(*ts, iso[:k], out=out), ref[:k]), k
+            assert torch.equal(P.lcp(*div, iso[:k], out=out), ref[:k]), k
+        assert bool((flat[dense.numel():] == -7.0).all()), k
+
+
 def test_input_checks_reject_bad_values():
     """PDIV_DEBUG_CHECK_INPUTS: a negative variance or a non-finite mean is
     reported as PDIV_ERR_INVALID before any work; admissible inputs pass and
