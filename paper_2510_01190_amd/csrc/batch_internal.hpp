@@ -38,8 +38,9 @@ bool all_rows_on_lines(const std::vector<BatchField>& f);
 // Sets n_strips and tile_begin for band_rows-row bands of the layout's strips;
 // returns the tile count.
 int64_t fill_tiles(std::vector<BatchField>& f, int band_rows, bool paired);
-// Blocks of the kernel resident on the whole device at once.
-int resident_blocks(const void* kernel);
+// The launch shape by rule: band rows for a layout, and the grid.
+int batch_band_rows(const std::vector<BatchField>& f, bool paired);
+int batch_grid(int64_t n_tiles);
 hipError_t launch_batch(const void* kernel, const BatchField* dev_fields, int n_fields,
                         int64_t n_tiles, int band_rows, int grid, hipStream_t s);
 

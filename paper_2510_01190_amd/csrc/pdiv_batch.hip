@@ -6,11 +6,10 @@
 //
 // Every field is cut into the column-walking tiles of lcp_tile.hpp (126-cell
 // strips x band_rows-row bands).  Tile counts are prefix-summed over the
-// fields; a grid sized to the device's resident capacity walks the global tile
-// index with a stride of the total wave count (static, deterministic, no
-// counters to reset, so the launch can be captured and replayed as a graph).
-// A wave finds its field by binary search over the prefix table with scalar
-// loads.  Results are bitwise those of the single-field kernels: the same tile
+// fields; a grid of up to a wave per tile walks the global tile index with a
+// stride of the total wave count (static, deterministic, no counters to reset,
+// so the launch can be captured and replayed as a graph).  A wave finds its
+// field by a 64-way search over the prefix table.  Results are bitwise those of the single-field kernels: the same tile
 // code computes every cell.
 #include <hip/hip_runtime.h>
 
@@ -36,6 +35,28 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / kWave;
 
+// Field of tile t: the last f with fields[f].tile_begin <= t.  The 64 lanes
+// probe 64 evenly spaced entries at once, so the search is one load deep for
+// up to 64 fields and two for up to 4096 (a binary search by scalar loads was
+// 6 and 12 dependent loads).  All lanes of the wave are active; t and the
+// result are wave-uniform.
+__device__ __forceinline__ int field_of_tile(const BatchField* __restrict__ fields, int n_fields,
+                                             int64_t t) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, n = n_fields;  // the field is in [lo, lo + n)
+  while (n > 1) {
+    const int step = (n + 63) / 64;
+    const int f = lo + lane * step;
+    const bool at = f < lo + n && fields[f].tile_begin <= t;
+    // entries ascend, so the lanes that hold one at or before t are the first
+    const int last = __popcll(__ballot(at)) - 1;
+    const int next = lo + last * step;
+    n = min(step, lo + n - next);
+    lo = next;
+  }
+  return lo;
+}
+
 template <int KC, bool FUSED, bool PAIRED, typename T>
 __global__ __launch_bounds__(kBlock) void batch_kernel(const BatchField* __restrict__ fields,
                                                        int n_fields, int64_t n_tiles,
@@ -48,13 +69,7 @@ __global__ __launch_bounds__(kBlock) void batch_kernel(const BatchField* __restr
   const int64_t wave = __builtin_amdgcn_readfirstlane(blk * kWavesPerBlock + (threadIdx.x >> 6));
   const int64_t n_waves = int64_t(gridDim.x) * kWavesPerBlock;
   for (int64_t t = wave; t < n_tiles; t += n_waves) {
-    // field of tile t: the last f with fields[f].tile_begin <= t
-    int lo = 0, hi = n_fields - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (fields[mid].tile_begin <= t) lo = mid; else hi = mid - 1;
-    }
-    const BatchField& F = fields[lo];
+    const BatchField& F = fields[field_of_tile(fields, n_fields, t)];
     const int64_t local = t - F.tile_begin;
     const int strip = static_cast<int>(local % F.n_strips);
     const int band = static_cast<int>(local / F.n_strips);
@@ -108,6 +123,45 @@ bool all_rows_on_lines(const std::vector<BatchField>& f) {
   return true;
 }
 
+// Line-aligned fused batches: the paired tile from 2 M cells at 8 and more
+// isovalues, from 12 M below (48 fields of 64..2048 a side, 16.6 M cells, split
+// against paired at their best shapes: 93 / 97 us at 1 isovalue, 151 / 147 at
+// 4, 230 / 212 at 8; 64 of 64..1000, 6 M cells, 62.6 / 62.4 at 4, 98 / 89 at
+// 8; 12 fields, 1.9 M cells, 28 / 32 at 4).
+bool batch_paired(const std::vector<BatchField>& f, int kc) {
+  int64_t cells = 0;
+  for (auto& x : f) cells += int64_t(x.ny - 1) * (x.nx - 1);
+  return kc >= 8 ? cells >= 2000000 : kc >= 2 && cells >= 12000000;
+}
+
+// Band height by the number of tiles it leaves, as lcp_band_rows for one
+// field; the paired tile's staged rows want at least 16 where there are tiles
+// enough (48 fields, 4 isovalues: 159 / 147 / 151 / 156 us with 8 / 16 / 32 /
+// 64 rows; the split tile 165 / 151 / 162 / 155 us with 4 / 8 / 16 / 32; 12
+// fields: 30 / 28 / 28 / 32 / 40 us with 2 / 4 / 8 / 16 / 32).
+int batch_band_rows(const std::vector<BatchField>& f, bool paired) {
+  const int cells = cells_per_wave(paired);
+  auto tiles = [&](int b) {
+    int64_t t = 0;
+    for (auto& x : f)
+      t += int64_t((x.nx - 1 + cells - 1) / cells) * ((x.ny - 1 + b - 1) / b);
+    return t;
+  };
+  if (paired && tiles(32) >= 16000) return 32;
+  if (paired && tiles(16) >= 4000) return 16;
+  return tiles(8) >= 6000 ? 8 : tiles(4) >= 3000 ? 4 : tiles(2) >= 1500 ? 2 : 1;
+}
+
+// A wave per tile, as far as the grid goes: the hardware hands out blocks as
+// others finish, which evens out tiles of uneven cost; a grid of the resident
+// blocks striding over the tiles ran 180 against 162 us (48 fields, 4
+// isovalues, split tile, 16-row bands), 126 against 98 us (64 fields, 8
+// isovalues).  Larger tables are walked with a stride.
+int batch_grid(int64_t n_tiles) {
+  return int(std::max<int64_t>(1, std::min<int64_t>((n_tiles + kWavesPerBlock - 1) /
+                                                        kWavesPerBlock, int64_t(1) << 22)));
+}
+
 int64_t fill_tiles(std::vector<BatchField>& f, int band_rows, bool paired) {
   const int cells = cells_per_wave(paired);
   int64_t t = 0;
@@ -120,7 +174,8 @@ int64_t fill_tiles(std::vector<BatchField>& f, int band_rows, bool paired) {
   return t;
 }
 
-int resident_blocks(const void* kernel) {
+// Blocks of the kernel resident on the whole device at once.
+static int resident_blocks(const void* kernel) {
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 1024;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -252,6 +307,14 @@ void shape(pdiv_batch b, bool paired, int band_rows) {
   b->n_tiles = fill_tiles(b->fields, band_rows, paired);
 }
 
+// Grid of a tuned batch: gm / 2 times the resident capacity, at most a wave
+// per tile (kGridAll: just that).
+constexpr int kGridAll = 1 << 20;
+int tuned_grid(pdiv_batch b, int gm) {
+  const int64_t g = int64_t(resident_blocks(b->kernel)) * gm / 2;
+  return int(std::max<int64_t>(1, std::min<int64_t>(g, batch_grid(b->n_tiles))));
+}
+
 // Times the candidate shapes on the batch itself (the launches write the
 // batch's own outputs) and keeps the fastest: band rows x grid size, and both
 // tile layouts when every output row starts on a line.
@@ -263,7 +326,7 @@ pdiv_status autotune(pdiv_batch b, hipStream_t s) {
     auto it = g_tune.find(key);
     if (it != g_tune.end() && (b->lines || !it->second.paired)) {
       shape(b, it->second.paired != 0, it->second.band_rows);
-      b->grid = std::max(1, resident_blocks(b->kernel) * it->second.grid_mult / 2);
+      b->grid = tuned_grid(b, it->second.grid_mult);
       return upload(b);
     }
   }
@@ -276,10 +339,9 @@ pdiv_status autotune(pdiv_batch b, hipStream_t s) {
   for (int paired = 0; paired <= (b->lines ? 1 : 0) && st == PDIV_OK; ++paired) {
     for (int br : {8, 16, 32, 64}) {
       shape(b, paired != 0, br);
-      const int base = resident_blocks(b->kernel);
       if ((st = upload(b)) != PDIV_OK) break;
-      for (int gm : {1, 2, 4}) {  // grid = gm/2 x resident capacity
-        const int grid = std::max(1, base * gm / 2);
+      for (int gm : {1, 2, 4, kGridAll}) {
+        const int grid = tuned_grid(b, gm);
         hipError_t e = launch_batch(b->kernel, b->dev, int(b->fields.size()), b->n_tiles, br,
                                     grid, s);  // warm
         e = e != hipSuccess ? e : hipEventRecord(e0, s);
@@ -305,7 +367,7 @@ pdiv_status autotune(pdiv_batch b, hipStream_t s) {
   (void)hipEventDestroy(e1);
   if (st != PDIV_OK) return st;
   shape(b, win.paired != 0, win.band_rows);
-  b->grid = std::max(1, resident_blocks(b->kernel) * win.grid_mult / 2);
+  b->grid = tuned_grid(b, win.grid_mult);
   {
     std::lock_guard<std::mutex> g(g_tune_mu);
     g_tune[key] = win;
@@ -368,8 +430,9 @@ pdiv_status pdiv_batch_create(const pdiv_field* fields_host, int32_t n_fields, p
   if (flags & PDIV_BATCH_AUTOTUNE) {
     st = autotune(b, s);
   } else {
-    shape(b, b->lines && kc >= 8, 16);
-    b->grid = resident_blocks(b->kernel);
+    const bool paired = b->lines && batch_paired(b->fields, kc);
+    shape(b, paired, batch_band_rows(b->fields, paired));
+    b->grid = batch_grid(b->n_tiles);
     st = upload(b);
   }
   if (st == PDIV_OK && hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess)

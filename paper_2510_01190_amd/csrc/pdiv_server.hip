@@ -39,7 +39,6 @@ using namespace pdiv;
 namespace {
 
 constexpr int kMaxBatch = serve::kMaxBatch;
-constexpr int kBandRows = 16;    // tile height of server launches
 constexpr int kMaxStreams = 8;
 // Pinned staging buffers come in power-of-two size classes from 1 MiB up and
 // are reused; the pool grows until it holds kDefaultPinnedCap bytes (or, after
@@ -275,13 +274,12 @@ struct pdiv_server_s : serve::Executor {
       kc = std::max(kc, iso_bucket(r->n_iso));
     }
     const bool paired = kc >= 8 && all_rows_on_lines(fv);
-    const int64_t n_tiles = fill_tiles(fv, kBandRows, paired);
+    const int band_rows = batch_band_rows(fv, paired);
+    const int64_t n_tiles = fill_tiles(fv, band_rows, paired);
     std::memcpy(S.host_fields, fv.data(), sizeof(BatchField) * fv.size());
     hipStream_t s = streams[size_t(next_stream)];
     next_stream = (next_stream + 1) % n_streams;
     const void* kernel = batch_kernel_ptr(false, PDIV_F32, kc, paired);
-    const int grid =
-        int(std::max<int64_t>(1, std::min<int64_t>(resident_blocks(kernel), (n_tiles + 3) / 4)));
     if (fault_at > 0 && ++slider_starts == fault_at)
       return 0;  // forced from the host: nothing is enqueued
     hipError_t e = hipMemcpyAsync(S.dev_fields, S.host_fields, sizeof(BatchField) * fv.size(),
@@ -292,7 +290,8 @@ struct pdiv_server_s : serve::Executor {
                                          hipMemcpyHostToDevice, s);
     e = e != hipSuccess
             ? e
-            : launch_batch(kernel, S.dev_fields, int(fv.size()), n_tiles, kBandRows, grid, s);
+            : launch_batch(kernel, S.dev_fields, int(fv.size()), n_tiles, band_rows,
+                           batch_grid(n_tiles), s);
     return record(e, s, nullptr);
   }
 

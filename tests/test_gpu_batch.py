@@ -149,3 +149,30 @@ def test_autotuned_batch_with_line_aligned_outputs(tmp_path, monkeypatch):
     b2 = P.Batch(fields, graph=False, autotune=True)
     assert b2.info() == info
     b2.close()
+
+
+@pytest.mark.parametrize("n,hi,k", [(1, 40, 1), (2, 300, 7), (63, 30, 3), (64, 30, 2), (65, 30, 2),
+                                    (129, 150, 12), (4097, 6, 1), (40, 900, 9), (24, 1400, 2)])
+def test_field_search_and_batch_shapes(n, hi, k):
+    """Field counts around the 64-way search's steps (one probe up to 64
+    fields, two up to 4096, three beyond) and batches whose tile counts and
+    cells take each band height and, at 9 isovalues and 3 M cells and at 2 and
+    12 M, the paired tile: every field bitwise its own launch."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    rng = np.random.default_rng(n)
+    sizes = [(int(a), int(b)) for a, b in rng.integers(2, hi + 1, (n, 2))]
+    iso = rng.uniform(-0.5, 0.5, k).astype(np.float32)
+    dev_iso = torch.from_numpy(iso).cuda()
+    fields = []
+    for ny, nx in sizes:
+        m = [torch.randn(ny, nx, generator=g, device="cuda") * 0.3 if q % 2 == 0 else
+             torch.rand(ny, nx, generator=g, device="cuda") * 0.2 + 0.01 for q in range(4)]
+        fields.append(dict(mean_u=m[0], var_u=m[1], mean_v=m[2], var_v=m[3], isovalues=dev_iso))
+    b = P.Batch(fields, graph=False)
+    b.launch()
+    torch.cuda.synchronize()
+    for f, got in zip(fields, b.fields):
+        want = P.lcp_from_moments(f["mean_u"], f["var_u"], f["mean_v"], f["var_v"], iso)
+        assert torch.equal(got["lcp"], want), got["lcp"].shape
+    b.close()
