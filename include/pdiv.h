@@ -217,6 +217,17 @@ pdiv_status pdiv_isocontour(const float* field, int64_t ny, int64_t nx, float is
                             int64_t* row_offsets, float* segments, int64_t max_segments,
                             pdiv_stream stream);
 
+/* The segments alone, for a caller that sized the buffer from a first call
+ * with max_segments = 0: fields is that call's field (n_fields = 1), or
+ * pdiv_spaghetti's div_workspace (n_fields = n_members), n_fields planes
+ * [ny][nx]; row_offsets what the call left there (n_fields*(ny-1) + 1
+ * entries).  Writes what the same call with this buffer would write, without
+ * computing the divergences and counts again.  Segments past max_segments are
+ * not written; max_segments = 0 writes nothing. */
+pdiv_status pdiv_contour_segments(const float* fields, int64_t n_fields, int64_t ny, int64_t nx,
+                                  float isovalue, const int64_t* row_offsets, float* segments,
+                                  int64_t max_segments, pdiv_stream stream);
+
 /* Spaghetti plot in one call: the divergence of every member by Eq. 1 (each
  * member a deterministic field; bitwise the mean of pdiv_divergence_gaussian
  * with zero variances) into div_workspace, then every member's isocontour

@@ -72,6 +72,7 @@ _SIGS = {
     "pdiv_speed_gradient_moments": [_p, _p, _c.c_int, _i64, _i64, _i64, _i64, _f64, _f64, _i32,
                                     _p, _p, _p, _p, _c.c_int, _p],
     "pdiv_isocontour": [_p, _i64, _i64, _c.c_float, _p, _p, _i64, _p],
+    "pdiv_contour_segments": [_p, _i64, _i64, _i64, _c.c_float, _p, _p, _i64, _p],
     "pdiv_spaghetti": [_p, _p, _c.c_int, _i64, _i64, _i64, _i64, _f64, _f64, _c.c_float, _p, _p,
                        _p, _i64, _p],
     "pdiv_spaghetti_noalloc": [_p, _p, _c.c_int, _i64, _i64, _i64, _i64, _f64, _f64,
@@ -336,8 +337,8 @@ def isocontour(field, isovalue):
     n = int(offs[ny - 1].item())
     segs = torch.empty((n, 4), dtype=torch.float32, device=field.device)
     if n:
-        _check(lib().pdiv_isocontour(pf, ny, nx, c, _p(offs.data_ptr()), _p(segs.data_ptr()), n,
-                                     _stream()))
+        _check(lib().pdiv_contour_segments(pf, 1, ny, nx, c, _p(offs.data_ptr()),
+                                           _p(segs.data_ptr()), n, _stream()))
     return segs
 
 
@@ -352,12 +353,12 @@ def spaghetti(u_members, v_members, isovalue, dx: float = 1.0, dy: float = 1.0):
     work = torch.empty((m, ny, nx), dtype=torch.float32, device=u_members.device)
     offs = torch.empty(m * (ny - 1) + 1, dtype=torch.int64, device=u_members.device)
     c = float(np.float32(isovalue))
-    args = (pu, pv, _dtype_code(u_members), m, ny, nx, 0, dx, dy, c, _p(work.data_ptr()),
-            _p(offs.data_ptr()))
-    _check(lib().pdiv_spaghetti(*args, None, 0, _stream()))
+    _check(lib().pdiv_spaghetti(pu, pv, _dtype_code(u_members), m, ny, nx, 0, dx, dy, c,
+                                _p(work.data_ptr()), _p(offs.data_ptr()), None, 0, _stream()))
     n = int(offs[-1].item())
     segs = torch.empty((max(n, 1), 4), dtype=torch.float32, device=u_members.device)
-    _check(lib().pdiv_spaghetti(*args, _p(segs.data_ptr()), n, _stream()))
+    _check(lib().pdiv_contour_segments(_p(work.data_ptr()), m, ny, nx, c, _p(offs.data_ptr()),
+                                       _p(segs.data_ptr()), n, _stream()))
     bounds = offs[::ny - 1].cpu().tolist()
     return [segs[bounds[q]:bounds[q + 1]] for q in range(m)]
 

@@ -6,11 +6,11 @@
 // point at t = (c - p) / (q - p); the two saddle cases are split by the cell
 // centre ((v00 + v10) + (v11 + v01)) / 4.  Segments are listed cell by cell
 // in row-major order, so the output is deterministic:
-//   count  one wave per cell row: segments of the row;
+//   count  one or four waves per cell row: segments of the row;
 //   scan   one block: exclusive scan of the row counts, total at the end;
-//   write  one wave per cell row: a batch's segments are listed in LDS in
-//          output order (ballot + prefix count), then computed and stored
-//          64 at a time from the row's offset on.
+//   write  one or four waves per cell row: a batch's segments are listed in
+//          LDS in output order (ballot + prefix count), then computed and
+//          stored 64 at a time from the row's offset on.
 #include <hip/hip_runtime.h>
 
 #include "pdiv_device.hpp"
@@ -142,17 +142,29 @@ struct RowPair {
   }
 };
 
-// Row of this wave.  Blocks are dealt round-robin to the 8 XCDs (block b
+// Row of this wave: one row per wave, or (W = kWavesPerBlock) one row per
+// block, whose waves take batches of the row in turn.  Blocks are dealt round-robin to the 8 XCDs (block b
 // runs on XCD b mod 8), each with its own L2; renumbering the blocks so
 // that each XCD takes a contiguous run of rows lets the two rows that
 // share a vertex row read it through one L2.  A bijection on the blocks.
+template <int W>
 __device__ __forceinline__ int wave_row() {
+  static_assert(W == 1 || W == kWavesPerBlock, "a wave or a block per row");
   const int nb = gridDim.x, xcd = blockIdx.x % 8, q8 = nb / 8, r8 = nb % 8;
   const int blk = xcd * q8 + min(xcd, r8) + blockIdx.x / 8;
   // uniform across the wave, which the compiler must know: the row's buffer
   // descriptors then stay in scalar registers (a descriptor computed from a
   // lane-varying value makes every buffer access a loop over its values)
-  return __builtin_amdgcn_readfirstlane(blk * kWavesPerBlock + (threadIdx.x >> 6));
+  if constexpr (W == 1)
+    return __builtin_amdgcn_readfirstlane(blk * kWavesPerBlock + (threadIdx.x >> 6));
+  else
+    return blk;
+}
+
+// This wave's place among the W waves of its row.
+template <int W>
+__device__ __forceinline__ int wave_part() {
+  return W == 1 ? 0 : __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
 }
 
 __device__ __forceinline__ int case_index(const Corners& k, float c) {
@@ -162,17 +174,20 @@ __device__ __forceinline__ int case_index(const Corners& k, float c) {
 
 // Rows r = 0 .. n_fields (ny - 1) - 1 of n_fields fields stored field_stride
 // floats apart: cell row j = r mod (ny - 1) of field r / (ny - 1).
+template <int W>
 __global__ __launch_bounds__(kBlock) void contour_count_kernel(const float* __restrict__ f0, int ny,
                                                                int nx, int64_t field_stride,
                                                                int rows, float c,
                                                                int64_t* __restrict__ counts) {
-  const int r = wave_row();
-  if (r >= rows) return;
+  __shared__ int parts[kWavesPerBlock];
+  const int r = wave_row<W>();
+  if (r >= rows) return;  // W > 1: the whole block
+  const int part = wave_part<W>();
   const int j = r % (ny - 1);
   const RowPair rp(f0 + int64_t(r / (ny - 1)) * field_stride, nx, j);
   const int lane = threadIdx.x & 63;
   int n = 0;
-  for (int i0 = 0; i0 < nx - 1; i0 += 64 * kUnroll) {
+  for (int i0 = 64 * kUnroll * part; i0 < nx - 1; i0 += 64 * kUnroll * W) {
     Corners k[kUnroll];
     rp.batch(i0, lane, nx, k);
 #pragma unroll
@@ -183,19 +198,33 @@ __global__ __launch_bounds__(kBlock) void contour_count_kernel(const float* __re
   }
 #pragma unroll
   for (int s = 32; s > 0; s >>= 1) n += __shfl_xor(n, s, 64);
-  if (lane == 0) counts[r] = n;
+  if constexpr (W == 1) {
+    if (lane == 0) counts[r] = n;
+  } else {
+    if (lane == 0) parts[part] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int total = 0;
+#pragma unroll
+      for (int p = 0; p < W; ++p) total += parts[p];
+      counts[r] = total;
+    }
+  }
 }
 
 // Exclusive scan of counts[0 .. n) in place, total to counts[n]; one block.
-// Per pass thread t sums its kScanItems consecutive counts, the block scans
-// the thread sums (Hillis-Steele in LDS), and each thread writes its items'
-// offsets from its own prefix.
+// Per pass thread t sums its kScanItems consecutive counts, each wave scans
+// its lanes' sums by shuffles, the waves' totals meet in LDS (one barrier;
+// two sets, so the next pass may write while this one reads), and each thread
+// writes its items' offsets from its own prefix.
 __global__ __launch_bounds__(kScanBlock) void contour_scan_kernel(int64_t* __restrict__ counts,
                                                                   int n) {
-  __shared__ int64_t buf[kScanBlock];
-  const int t = threadIdx.x;
+  constexpr int kWaves = kScanBlock / 64;
+  __shared__ int64_t wave_sum[2][kWaves];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   int64_t carry = 0;
-  for (int64_t base = 0; base < n; base += int64_t(kScanBlock) * kScanItems) {
+  int set = 0;
+  for (int64_t base = 0; base < n; base += int64_t(kScanBlock) * kScanItems, set ^= 1) {
     const int64_t first = base + int64_t(t) * kScanItems;
     int64_t x[kScanItems];
     int64_t sum = 0;
@@ -204,27 +233,33 @@ __global__ __launch_bounds__(kScanBlock) void contour_scan_kernel(int64_t* __res
       x[q] = first + q < n ? counts[first + q] : 0;
       sum += x[q];
     }
-    buf[t] = sum;
-    __syncthreads();
-    for (int d = 1; d < kScanBlock; d <<= 1) {
-      const int64_t y = t >= d ? buf[t - d] : 0;
-      __syncthreads();
-      buf[t] += y;
-      __syncthreads();
+    int64_t incl = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int64_t y = __shfl_up(incl, d, 64);
+      incl += lane >= d ? y : 0;
     }
-    int64_t run = carry + buf[t] - sum;
+    if (lane == 63) wave_sum[set][wave] = incl;
+    __syncthreads();
+    int64_t run = carry + incl - sum;
+#pragma unroll
+    for (int p = 0; p < kWaves; ++p) {
+      const int64_t ws = wave_sum[set][p];
+      run += p < wave ? ws : 0;
+      carry += ws;
+    }
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) {
       if (first + q < n) counts[first + q] = run;
       run += x[q];
     }
-    carry += buf[kScanBlock - 1];
-    __syncthreads();
   }
   if (t == 0) counts[n] = carry;
 }
 
-// Write pass, one wave per cell row, 8 chunks of 64 cells per batch.  The
+// Write pass, one or four waves per cell row, 8 chunks of 64 cells per batch.
+// Four waves take four neighbouring batches at a time and learn from LDS how
+// many segments the ones before them hold.  The
 // batch's cells are classified lane by lane; the segments they hold are
 // listed in LDS in output order (cell, then its first and second segment),
 // each entry the cell's column within the batch and the segment's two edges;
@@ -234,21 +269,28 @@ __global__ __launch_bounds__(kScanBlock) void contour_scan_kernel(int64_t* __res
 // cells of which a few hold one, and the stores are contiguous.
 constexpr int kList = 64 * kUnroll * 2;  // segments of a batch, at most
 
+template <int W>
 __global__ __launch_bounds__(kBlock) void contour_write_kernel(
     const float* __restrict__ f0, int ny, int nx, int64_t field_stride, int rows, float c,
     const int64_t* __restrict__ offsets, float4* __restrict__ segs, int64_t max_segs) {
   __shared__ uint32_t list_block[kWavesPerBlock][kList + 1];  // + a slot for discards
-  const int r = wave_row();
-  if (r >= rows) return;
+  __shared__ uint32_t parts[2][kWavesPerBlock];
+  const int r = wave_row<W>();
+  if (r >= rows) return;  // W > 1: the whole block
   uint32_t* const list = list_block[threadIdx.x >> 6];
+  const int part = wave_part<W>();
   const int j = r % (ny - 1);
   const RowPair rp(f0 + int64_t(r / (ny - 1)) * field_stride, nx, j);
   const int lane = threadIdx.x & 63;
   const uint64_t below_me = __lanemask_lt();
   constexpr uint32_t kDrop = 0x7ffffff0u;
   int64_t k = offsets[r];
-  // every lane walks the same number of batches, so the ballots see the wave
-  for (int i00 = 0; i00 < nx - 1; i00 += 64 * kUnroll) {
+  if (k < 0) return;  // not an offset: nothing may be stored before segs
+  int set = 0;
+  // every wave of the row walks the same number of batches (one past the
+  // row's end lists nothing), so the ballots and barriers see all of them
+  for (int base = 0; base < nx - 1; base += 64 * kUnroll * W, set ^= 1) {
+    const int i00 = base + 64 * kUnroll * part;
     Corners vs[kUnroll];
     rp.batch(i00, lane, nx, vs);
     uint32_t nb = 0;  // segments of the batch listed so far (wave-uniform)
@@ -266,6 +308,21 @@ __global__ __launch_bounds__(kBlock) void contour_write_kernel(
       list[n >= 1 ? slot : kList] = e;
       list[n >= 2 ? slot + 1 : kList] = e | 1u;
       nb += uint32_t(__popcll(one) + __popcll(two));
+    }
+    uint32_t total = nb;  // segments of the W batches
+    if constexpr (W > 1) {
+      if (lane == 0) parts[set][part] = nb;
+      __syncthreads();
+      uint32_t before = 0;
+      total = 0;
+#pragma unroll
+      for (int p = 0; p < W; ++p) {
+        const uint32_t np = __builtin_amdgcn_readfirstlane(parts[set][p]);
+        before += p < part ? np : 0;
+        total += np;
+      }
+      k += before;
+      total -= before;
     }
     // the list is written and read by this wave only, in order
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -293,7 +350,7 @@ __global__ __launch_bounds__(kBlock) void contour_write_kernel(
       __builtin_amdgcn_raw_buffer_store_b128(val, out, int(ok ? uint32_t(lane) * 16u : kDrop), 0,
                                              0);
     }
-    k += int64_t(nb);
+    k += int64_t(total);
     // the next batch rewrites the list only after these reads
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -332,21 +389,62 @@ __global__ __launch_bounds__(kBlock) void members_divergence_kernel(
 
 }  // namespace
 
+namespace {
+
+// Four waves per row where a wave per row would be few waves with long walks:
+// rows of more than one batch, and at most 2^16 of them.  Count, scan and
+// write against a wave per row: 500x6000 33.5 -> 18.2 us, 721x1440 14.8 ->
+// 12.7, 2048^2 21.3 -> 19.1, 4096^2 52.9 -> 50.4, 8192^2 162.6 -> 161.0 (count
+// and scan alone 59, which the first call of a sized buffer now stops at).
+bool block_per_row(int64_t rows, int64_t nx) {
+  return nx > 64 * kUnroll && rows <= (int64_t(1) << 16);
+}
+
+hipError_t check_rows(int64_t rows) {
+  return rows > 0x7fffffff || !launch_fits((rows + kWavesPerBlock - 1) / kWavesPerBlock, kBlock)
+             ? hipErrorInvalidConfiguration
+             : hipSuccess;
+}
+
+}  // namespace
+
+hipError_t launch_contour_segments(const float* fields, int64_t n_fields, int64_t field_stride,
+                                   int64_t ny, int64_t nx, float c, const int64_t* row_offsets,
+                                   float* segments, int64_t max_segments, hipStream_t s) {
+  const int64_t rows = n_fields * (ny - 1);
+  const hipError_t e = check_rows(rows);
+  if (e != hipSuccess || max_segments == 0) return e;
+  float4* const segs = reinterpret_cast<float4*>(segments);
+  if (block_per_row(rows, nx))
+    hipLaunchKernelGGL(contour_write_kernel<kWavesPerBlock>, dim3(unsigned(rows)), dim3(kBlock), 0,
+                       s, fields, int(ny), int(nx), field_stride, int(rows), c, row_offsets, segs,
+                       max_segments);
+  else
+    hipLaunchKernelGGL(contour_write_kernel<1>,
+                       dim3(unsigned((rows + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock),
+                       0, s, fields, int(ny), int(nx), field_stride, int(rows), c, row_offsets,
+                       segs, max_segments);
+  return hipGetLastError();
+}
+
 hipError_t launch_isocontours(const float* fields, int64_t n_fields, int64_t field_stride,
                               int64_t ny, int64_t nx, float c, int64_t* row_offsets,
                               float* segments, int64_t max_segments, hipStream_t s) {
-  const int64_t rows64 = n_fields * (ny - 1);
-  if (rows64 > 0x7fffffff || !launch_fits((rows64 + kWavesPerBlock - 1) / kWavesPerBlock, kBlock))
-    return hipErrorInvalidConfiguration;
-  const int rows = int(rows64);
-  const unsigned blocks = unsigned((rows + kWavesPerBlock - 1) / kWavesPerBlock);
-  hipLaunchKernelGGL(contour_count_kernel, dim3(blocks), dim3(kBlock), 0, s, fields, int(ny),
-                     int(nx), field_stride, rows, c, row_offsets);
-  hipLaunchKernelGGL(contour_scan_kernel, dim3(1), dim3(kScanBlock), 0, s, row_offsets, rows);
-  hipLaunchKernelGGL(contour_write_kernel, dim3(blocks), dim3(kBlock), 0, s, fields, int(ny),
-                     int(nx), field_stride, rows, c, row_offsets,
-                     reinterpret_cast<float4*>(segments), max_segments);
-  return hipGetLastError();
+  const int64_t rows = n_fields * (ny - 1);
+  const hipError_t e = check_rows(rows);
+  if (e != hipSuccess) return e;
+  if (block_per_row(rows, nx))
+    hipLaunchKernelGGL(contour_count_kernel<kWavesPerBlock>, dim3(unsigned(rows)), dim3(kBlock), 0,
+                       s, fields, int(ny), int(nx), field_stride, int(rows), c, row_offsets);
+  else
+    hipLaunchKernelGGL(contour_count_kernel<1>,
+                       dim3(unsigned((rows + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock),
+                       0, s, fields, int(ny), int(nx), field_stride, int(rows), c, row_offsets);
+  hipLaunchKernelGGL(contour_scan_kernel, dim3(1), dim3(kScanBlock), 0, s, row_offsets, int(rows));
+  const hipError_t le = hipGetLastError();
+  return le != hipSuccess ? le
+                          : launch_contour_segments(fields, n_fields, field_stride, ny, nx, c,
+                                                    row_offsets, segments, max_segments, s);
 }
 
 hipError_t launch_isocontour(const float* field, int64_t ny, int64_t nx, float c,

@@ -186,6 +186,15 @@ pdiv_status lcp_chunks(bool fused, const void* p0, const void* p1, const void* p
   return PDIV_OK;
 }
 
+pdiv_status check_segments(const float* segments, int64_t max_segments) {
+  if (max_segments < 0) return invalid("max_segments must be >= 0 (got %lld)",
+                                       (long long)max_segments);
+  if (max_segments > 0 && segments == nullptr) return invalid("segments is NULL");
+  if (max_segments > 0 && reinterpret_cast<uintptr_t>(segments) % 16 != 0)
+    return invalid("segments must be 16-byte aligned");
+  return PDIV_OK;
+}
+
 pdiv_status check_spaghetti(const void* u_members, const void* v_members, pdiv_dtype in_dtype,
                             int64_t n_members, int64_t ny, int64_t nx, int64_t* member_stride,
                             double dx, double dy, const int64_t* row_offsets,
@@ -207,12 +216,7 @@ pdiv_status check_spaghetti(const void* u_members, const void* v_members, pdiv_d
   if (*member_stride == 0) *member_stride = n;
   if (*member_stride < n)
     return invalid("member_stride %lld < ny*nx %lld", (long long)*member_stride, (long long)n);
-  if (max_segments < 0) return invalid("max_segments must be >= 0 (got %lld)",
-                                       (long long)max_segments);
-  if (max_segments > 0 && segments == nullptr) return invalid("segments is NULL");
-  if (max_segments > 0 && reinterpret_cast<uintptr_t>(segments) % 16 != 0)
-    return invalid("segments must be 16-byte aligned");
-  return PDIV_OK;
+  return check_segments(segments, max_segments);
 }
 
 // Every member's Eq. 1 divergence into div (n_members planes of ny*nx
@@ -525,14 +529,29 @@ pdiv_status pdiv_isocontour(const float* field, int64_t ny, int64_t nx, float is
   PDIV_NONNULL(field);
   PDIV_NONNULL(row_offsets);
   PDIV_TRY(check_grid(ny, nx));
-  if (max_segments < 0) return invalid("max_segments must be >= 0 (got %lld)",
-                                       (long long)max_segments);
-  if (max_segments > 0 && segments == nullptr) return invalid("segments is NULL");
-  if (max_segments > 0 && reinterpret_cast<uintptr_t>(segments) % 16 != 0)
-    return invalid("segments must be 16-byte aligned");
+  PDIV_TRY(check_segments(segments, max_segments));
   return device_status(launch_isocontour(field, ny, nx, isovalue, row_offsets, segments,
                                          max_segments, static_cast<hipStream_t>(stream)),
                        "isocontour launch");
+}
+
+pdiv_status pdiv_contour_segments(const float* fields, int64_t n_fields, int64_t ny, int64_t nx,
+                                  float isovalue, const int64_t* row_offsets, float* segments,
+                                  int64_t max_segments, pdiv_stream stream) {
+  g_last_error.clear();
+  log_call("pdiv_contour_segments fields=%lld ny=%lld nx=%lld max_segments=%lld",
+           (long long)n_fields, (long long)ny, (long long)nx, (long long)max_segments);
+  PDIV_NONNULL(fields);
+  PDIV_NONNULL(row_offsets);
+  PDIV_TRY(check_grid(ny, nx));
+  if (n_fields < 1 || n_fields > int64_t(0x7fffffff) / (ny - 1))
+    return invalid("n_fields must be >= 1 with n_fields*(ny-1) < 2^31 (got %lld)",
+                   (long long)n_fields);
+  PDIV_TRY(check_segments(segments, max_segments));
+  return device_status(launch_contour_segments(fields, n_fields, ny * nx, ny, nx, isovalue,
+                                               row_offsets, segments, max_segments,
+                                               static_cast<hipStream_t>(stream)),
+                       "contour segments launch");
 }
 
 pdiv_status pdiv_spaghetti(const void* u_members, const void* v_members, pdiv_dtype in_dtype,

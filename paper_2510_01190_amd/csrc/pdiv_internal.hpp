@@ -130,6 +130,10 @@ hipError_t launch_isocontour(const float* field, int64_t ny, int64_t nx, float c
 hipError_t launch_isocontours(const float* fields, int64_t n_fields, int64_t field_stride,
                               int64_t ny, int64_t nx, float c, int64_t* row_offsets,
                               float* segments, int64_t max_segments, hipStream_t s);
+// The segments alone, row_offsets as launch_isocontours left them.
+hipError_t launch_contour_segments(const float* fields, int64_t n_fields, int64_t field_stride,
+                                   int64_t ny, int64_t nx, float c, const int64_t* row_offsets,
+                                   float* segments, int64_t max_segments, hipStream_t s);
 // Eq. 1 of each of m members (deterministic fields) into div [m][ny][nx].
 hipError_t launch_members_divergence(const void* u, const void* v, pdiv_dtype dt, int64_t m,
                                      int64_t ny, int64_t nx, int64_t stride,

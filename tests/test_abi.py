@@ -298,3 +298,17 @@ def test_log_mode_writes_one_line_per_call():
                            timeout=120)
         assert r.stdout.strip() == str(INVALID)
         assert ("[pdiv] pdiv_lcp ny=1 nx=8 n_iso=1" in r.stderr) == expect, r.stderr
+
+
+def test_contour_segments_rejects_bad_arguments():
+    L = P.lib()
+    c = ctypes.c_float(0.0)
+    call = L.pdiv_contour_segments
+    _expect_invalid(call(NUL, 1, 8, 8, c, FAKE, FAKE, 4, NUL), "fields")
+    _expect_invalid(call(FAKE, 0, 8, 8, c, FAKE, FAKE, 4, NUL), "n_fields")
+    _expect_invalid(call(FAKE, 1 << 29, 8, 8, c, FAKE, FAKE, 4, NUL), "n_fields")
+    _expect_invalid(call(FAKE, 1, 1, 8, c, FAKE, FAKE, 4, NUL), "at least 2x2")
+    _expect_invalid(call(FAKE, 1, 8, 8, c, NUL, FAKE, 4, NUL), "row_offsets")
+    _expect_invalid(call(FAKE, 1, 8, 8, c, FAKE, NUL, 4, NUL), "segments is NULL")
+    _expect_invalid(call(FAKE, 1, 8, 8, c, FAKE, FAKE, -1, NUL), "max_segments")
+    _expect_invalid(call(FAKE, 1, 8, 8, c, FAKE, ctypes.c_void_p(0x1004), 4, NUL), "aligned")

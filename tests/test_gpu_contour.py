@@ -118,3 +118,48 @@ def test_spaghetti_16bit_members_and_spacing(dt):
     for m in range(4):
         d, _ = P.divergence_gaussian(u[m].contiguous(), zero, v[m].contiguous(), zero, 0.5, 2.0)
         assert torch.equal(sp[m], P.isocontour(d, -0.01))
+
+
+@pytest.mark.parametrize("shape", [(3, 513), (5, 514), (4, 1025), (3, 2048), (4, 2049), (3, 2050),
+                                   (2, 4098), (700, 600)])
+def test_rows_shared_by_four_waves_match_oracle(shape):
+    """Rows of more than one batch of 512 cells are walked by four waves: row
+    lengths around one batch, around the block's four and past them."""
+    rng = np.random.default_rng(shape[1])
+    f = np.round(rng.normal(0, 1, shape), 1).astype(np.float32)
+    _compare(f, 0.3)
+
+
+def test_more_rows_than_blocks_take_and_scan_passes():
+    """Past 2^16 rows a wave walks a row again; the scan takes several passes.
+    Each half of the field, below that, gives the same counts and points."""
+    ny, nx = 65600, 515
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    f = torch.randn(ny, nx, generator=g, device="cuda")
+    f = (f + 2.0 * torch.linspace(-1, 1, ny, device="cuda")[:, None]).contiguous()
+    whole = P.isocontour(f, 0.1)
+    cut = 30011
+    parts = [P.isocontour(f[:cut + 1].contiguous(), 0.1), P.isocontour(f[cut:].contiguous(), 0.1)]
+    assert whole.shape[0] == parts[0].shape[0] + parts[1].shape[0]
+    assert torch.equal(whole[:parts[0].shape[0]], parts[0])
+    rest = whole[parts[0].shape[0]:]
+    assert torch.equal(rest[:, 0::2], parts[1][:, 0::2])
+    assert float((rest[:, 1::2] - cut - parts[1][:, 1::2]).abs().max()) <= 2.0 ** -7  # half an ulp at 2^16
+
+
+def test_contour_segments_alone():
+    """The segment pass on a counting call's offsets: the same segments, none
+    past max_segments, nothing for max_segments 0."""
+    f = torch.from_numpy(np.random.default_rng(2).normal(0, 1, (3, 50, 700)).astype(np.float32)).cuda()
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+    L = P.lib()
+    whole = P.isocontour(f[1], 0.2)
+    offs = torch.empty(50, dtype=torch.int64, device="cuda")
+    assert L.pdiv_isocontour(ptr(f[1]), 50, 700, ctypes.c_float(0.2), ptr(offs), None, 0, stream) == 0
+    for cap in (0, whole.shape[0] // 3, whole.shape[0]):
+        segs = torch.full_like(whole, -7.0)
+        assert L.pdiv_contour_segments(ptr(f[1]), 1, 50, 700, ctypes.c_float(0.2), ptr(offs),
+                                       ptr(segs), cap, stream) == 0
+        assert torch.equal(segs[:cap], whole[:cap]) and bool((segs[cap:] == -7.0).all())
