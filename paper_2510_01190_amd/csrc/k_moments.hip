@@ -3,7 +3,9 @@
 //
 // Layout: member m of a component is a plane of n_points values starting at
 // element m*stride.  The fit is pointwise, so the grid is treated as a flat
-// array: thread t owns VEC consecutive points and walks the members with a
+// array: thread t owns VEC consecutive points, has UNROLL members' loads in
+// flight (VEC 4: two; four ran 69.4 against 67.8 us at 721x1440x50, 6.4 TB/s)
+// and walks the members with a
 // float32 Welford update (mean += d/n, M2 += d (x - mean)), which needs no
 // second pass and keeps its accuracy when |mean| >> sigma.
 #include "pdiv_device.hpp"
@@ -62,7 +64,40 @@ __global__ __launch_bounds__(256) void moments_kernel(const Tin* __restrict__ u,
   for (int q = 0; q < VEC; ++q) mean_u[q] = m2_u[q] = mean_v[q] = m2_v[q] = 0.0f;
 
   int m = 0;
-  if (full) {
+  if constexpr (VEC == 1) {
+    // UNROLL members' loads are in flight at once; the last round repeats the
+    // last member's load and does not fold it in again, so the remainder is
+    // one round too, not one per member
+    float xu[UNROLL], xv[UNROLL];
+    auto load = [&](int r, int member) {
+      const int64_t row = static_cast<int64_t>(member) * stride;
+      xu[r] = ld(u + row, p0);
+      xv[r] = ld(v + row, p0);
+    };
+    auto fold = [&](int r) {
+      const float inv = 1.0f / static_cast<float>(m + r + 1);
+      float d = xu[r] - mean_u[0];
+      mean_u[0] = fmaf(d, inv, mean_u[0]);
+      m2_u[0] = fmaf(d, xu[r] - mean_u[0], m2_u[0]);
+      float e = xv[r] - mean_v[0];
+      mean_v[0] = fmaf(e, inv, mean_v[0]);
+      m2_v[0] = fmaf(e, xv[r] - mean_v[0], m2_v[0]);
+    };
+    for (; m + UNROLL <= m_members; m += UNROLL) {
+#pragma unroll
+      for (int r = 0; r < UNROLL; ++r) load(r, m + r);
+#pragma unroll
+      for (int r = 0; r < UNROLL; ++r) fold(r);
+    }
+    if (m < m_members) {
+#pragma unroll
+      for (int r = 0; r < UNROLL; ++r) load(r, min(m + r, m_members - 1));
+#pragma unroll
+      for (int r = 0; r < UNROLL; ++r)
+        if (m + r < m_members) fold(r);
+      m = m_members;
+    }
+  } else if (full) {
     for (; m + UNROLL <= m_members; m += UNROLL) {
       float xu[UNROLL][VEC], xv[UNROLL][VEC];
 #pragma unroll
@@ -117,14 +152,24 @@ hipError_t launch_typed(const void* u, const void* v, int64_t m, int64_t n, int6
                         int ddof, void* mu, void* vu, void* mv, void* vv, hipStream_t s) {
   const float inv_dof = static_cast<float>(1.0 / static_cast<double>(m - ddof));
   const size_t align = sizeof(Tin) * 4;
-  const bool vec4 = (stride % 4 == 0) && (reinterpret_cast<uintptr_t>(u) % align == 0) &&
+  // Four points a thread (16-byte loads of float32) for long streams over
+  // grids that still fill the chip; a point a thread, eight members in flight,
+  // everywhere else: its four times as many waves hide the loads of small
+  // grids and short ensembles.  One point against four, us: 68x68x15 3.3 / 5.8,
+  // 256x256x30 6.0 / 12.3, 500x500x20 9.5 / 11.8, 500x500x50 20.3 / 25.3,
+  // 300x2000x17 16.6 / 19.6, 2000x2000x10 72.6 / 73.9 (bfloat16 44 / 49), but
+  // 721x1440x50 84 / 68 (bfloat16 47.5 / 41.3), 2000x2000x25 171 / 163.
+  // (A grid past one launch of single points takes four, too.)
+  const bool long_stream = n >= (int64_t(1) << 19) && m >= 24;
+  const bool vec4 = (long_stream || !launch_fits((n + 255) / 256, 256)) && (stride % 4 == 0) &&
+                    (reinterpret_cast<uintptr_t>(u) % align == 0) &&
                     (reinterpret_cast<uintptr_t>(v) % align == 0);
   constexpr int kBlock = 256;
   if (vec4) {
     const int64_t threads = (n + 3) / 4;
     if (!launch_fits((threads + kBlock - 1) / kBlock, kBlock)) return hipErrorInvalidConfiguration;
     dim3 grid(static_cast<unsigned>((threads + kBlock - 1) / kBlock));
-    hipLaunchKernelGGL((moments_kernel<Tin, Tout, 4, 4>), grid, dim3(kBlock), 0, s,
+    hipLaunchKernelGGL((moments_kernel<Tin, Tout, 4, 2>), grid, dim3(kBlock), 0, s,
                        static_cast<const Tin*>(u), static_cast<const Tin*>(v),
                        static_cast<int>(m), n, stride, inv_dof, static_cast<Tout*>(mu),
                        static_cast<Tout*>(vu), static_cast<Tout*>(mv), static_cast<Tout*>(vv));

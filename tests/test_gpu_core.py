@@ -333,6 +333,37 @@ def test_moments_member_stride_and_ragged_tail():
         assert np.max(np.abs(host64(g) - r)) <= 1e-6 * max(1.0, np.abs(r).max())
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("m,n,stride", [(1, 130, 130), (7, 99, 128), (8, 1000, 1000), (9, 257, 257),
+                                        (23, 524288, 524288), (24, 524291, 524292),
+                                        (25, 524289, 524292), (25, 524289, 524289)])
+def test_moments_members_in_flight(m, n, stride, dt):
+    """Member counts below, at and past one round of loads, and the rule's edge
+    (from 2^19 points and 24 members four points a thread, with a ragged end,
+    where the members are aligned), over members further apart than the grid;
+    what lies between members is not read into the fit."""
+    from gpu_util import TORCH_DT
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + m)
+    bufs = [torch.full((m, stride), float("nan"), dtype=TORCH_DT[dt], device="cuda") for _ in "uv"]
+    for b in bufs:
+        b[:, :n] = (torch.randn(m, n, generator=g, device="cuda") + 3.0).to(TORCH_DT[dt])
+    outs = [torch.full((n + 1,), -7.0, device="cuda") for _ in range(4)]
+    import ctypes
+    st = P.lib().pdiv_moments(*[ctypes.c_void_p(b.data_ptr()) for b in bufs],
+                              {"f32": 0, "bf16": 2}[dt], m, 1, n, stride, 0,
+                              *[ctypes.c_void_p(o.data_ptr()) for o in outs], 0,
+                              ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == 0
+    for i, b in enumerate(bufs):
+        x = host64(b[:, :n])
+        mean, var = host64(outs[2 * i]), host64(outs[2 * i + 1])
+        assert mean[n] == -7.0 and var[n] == -7.0
+        ta, tr = _moment_tols(x, m)
+        assert np.max(np.abs(mean[:n] - x.mean(0))) <= ta
+        assert np.all(np.abs(var[:n] - x.var(0)) <= (tr + 2 * U32) * x.var(0) + 1e-30)
+
+
 def test_pipeline_fit_divergence_lcp():
     """Ensemble -> moments -> fused LCP against the oracle fed with the members."""
     m, ny, nx = 20, 100, 140
