@@ -19,7 +19,10 @@
 // 4-row tile walking all members 0.120 ms; four waves per 4-row tile
 // 0.105 ms; per 8-row tile (two halo rows per eight output rows, not per
 // four) 0.099 ms; per 16-row tile 0.107 ms (254 registers); eight waves per
-// 8-row tile 0.101 ms.
+// 8-row tile 0.101 ms.  The next member's rows are loaded while the current
+// one is folded in (each wave's run is a chain of dependent member loads):
+// 500x500x20 16.5 -> 15.4 us, 721x1440x50 110.7 -> 105 us (three sets of
+// members in turn, so none stays in the caches).
 #include <hip/hip_runtime.h>
 
 #include "pdiv_device.hpp"
@@ -30,9 +33,13 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / 64;
-constexpr int kBand = 8;
 constexpr int kStrip = 62;
-static_assert(kBand % kWavesPerBlock == 0, "the merge gives each wave whole output rows");
+// Output rows per tile: 8 (two halo rows per eight), but 4 where tiles of 8
+// would be fewer than eight blocks per CU.  8 against 4, us: 68x68x15 8.7 /
+// 5.9, 256x256x30 12.0 / 10.0, 500x500x20 15.4 / 13.7, 500x500x50 33.0 / 29.6,
+// 300x2000x17 23.3 / 22.0; 721x1440x50 105 / 109, 2000x2000x10 107 / 110.
+constexpr int kBand = 8;
+constexpr int64_t kShortBandBlocks = 2048;
 
 // first member of wave w's run
 __device__ __forceinline__ int member_run_start(int w, int m_members) {
@@ -50,13 +57,14 @@ __device__ __forceinline__ void merge_fit(float& mean, float& m2, int n_a, float
   m2 = (m2 + m2_b) + d * d * (static_cast<float>(n_a) * f_b);
 }
 
-template <typename Tin, typename Tout>
+template <int BAND, typename Tin, typename Tout>
 __global__ __launch_bounds__(kBlock) void speed_gradient_moments_kernel(
     const Tin* __restrict__ u, const Tin* __restrict__ v, int m_members, int ny, int nx,
     int64_t stride, StencilCoef k, float inv_dof, Tout* __restrict__ mgx,
     Tout* __restrict__ vgx, Tout* __restrict__ mgy, Tout* __restrict__ vgy, int n_strips) {
+  static_assert(BAND % kWavesPerBlock == 0, "the merge gives each wave whole output rows");
   // partial fits: [wave][row of the band][mean_x, m2_x, mean_y, m2_y][lane]
-  __shared__ float part[kWavesPerBlock][kBand][4][64];
+  __shared__ float part[kWavesPerBlock][BAND][4][64];
   // Blocks are dealt round-robin to the 8 XCDs, each with its own L2; give
   // each XCD a contiguous run of tiles, so that the halo rows two bands
   // share are fetched into one L2.  The map is a bijection on [0, gridDim.x).
@@ -70,31 +78,34 @@ __global__ __launch_bounds__(kBlock) void speed_gradient_moments_kernel(
   const int xc = x < 0 ? 0 : (x > nx - 1 ? nx - 1 : x);
   const bool bx = (x == 0) | (x == nx - 1);
   const float cxm = bx ? k.cxm_bd : k.cxm_in;
-  const int y0 = band * kBand;
-  float mean_x[kBand], m2_x[kBand], mean_y[kBand], m2_y[kBand];
+  const int y0 = band * BAND;
+  float mean_x[BAND], m2_x[BAND], mean_y[BAND], m2_y[BAND];
 #pragma unroll
-  for (int r = 0; r < kBand; ++r) mean_x[r] = m2_x[r] = mean_y[r] = m2_y[r] = 0.0f;
-  // speeds of the band's rows (and the two halo rows) for one member
-  auto speeds = [&](int m, float (&s)[kBand + 2]) {
+  for (int r = 0; r < BAND; ++r) mean_x[r] = m2_x[r] = mean_y[r] = m2_y[r] = 0.0f;
+  // U and V of the band's rows (and the two halo rows) for one member: row
+  // bases are wave-uniform, the lane's offset within a row is the same for all
+  const uint32_t xo = uint32_t(xc);
+  auto load = [&](int m, float (&a)[BAND + 2], float (&b)[BAND + 2]) {
     const Tin* const um = u + int64_t(m) * stride;
     const Tin* const vm = v + int64_t(m) * stride;
-    float a[kBand + 2], b[kBand + 2];
 #pragma unroll
-    for (int r = 0; r < kBand + 2; ++r) {
+    for (int r = 0; r < BAND + 2; ++r) {
       int yy = y0 - 1 + r;
       yy = yy < 0 ? 0 : (yy > ny - 1 ? ny - 1 : yy);
-      const int64_t o = int64_t(yy) * nx + xc;
-      a[r] = to_f32(um[o]);
-      b[r] = to_f32(vm[o]);
+      a[r] = to_f32(*at(um + int64_t(yy) * nx, xo));
+      b[r] = to_f32(*at(vm + int64_t(yy) * nx, xo));
     }
+  };
+  auto speeds = [&](const float (&a)[BAND + 2], const float (&b)[BAND + 2],
+                    float (&s)[BAND + 2]) {
 #pragma unroll
-    for (int r = 0; r < kBand + 2; ++r) s[r] = sqrtf(fmaf(a[r], a[r], b[r] * b[r]));
+    for (int r = 0; r < BAND + 2; ++r) s[r] = sqrtf(fmaf(a[r], a[r], b[r] * b[r]));
   };
   // the i-th member of the run folded into the running fit (Welford)
-  auto update = [&](int i, const float (&s)[kBand + 2]) {
+  auto update = [&](int i, const float (&s)[BAND + 2]) {
     const float inv = 1.0f / static_cast<float>(i + 1);
 #pragma unroll
-    for (int r = 0; r < kBand; ++r) {
+    for (int r = 0; r < BAND; ++r) {
       const int y = y0 + r;
       const float own = s[r + 1];
       // both neighbours read with every lane active: a DPP read inside a
@@ -118,13 +129,23 @@ __global__ __launch_bounds__(kBlock) void speed_gradient_moments_kernel(
   };
   const int m_lo = member_run_start(w, m_members);
   const int m_hi = member_run_start(w + 1, m_members);
-  for (int m = m_lo; m < m_hi; ++m) {
-    float s[kBand + 2];
-    speeds(m, s);
-    update(m - m_lo, s);
+  // the next member's rows are loaded while the current one is folded in
+  if (m_lo < m_hi) {
+    float a0[BAND + 2], b0[BAND + 2], a1[BAND + 2], b1[BAND + 2], s[BAND + 2];
+    load(m_lo, a0, b0);
+    for (int m = m_lo; m < m_hi; m += 2) {
+      load(min(m + 1, m_hi - 1), a1, b1);
+      speeds(a0, b0, s);
+      update(m - m_lo, s);
+      if (m + 1 < m_hi) {
+        load(min(m + 2, m_hi - 1), a0, b0);
+        speeds(a1, b1, s);
+        update(m + 1 - m_lo, s);
+      }
+    }
   }
 #pragma unroll
-  for (int r = 0; r < kBand; ++r) {
+  for (int r = 0; r < BAND; ++r) {
     part[w][r][0][lane] = mean_x[r];
     part[w][r][1][lane] = m2_x[r];
     part[w][r][2][lane] = mean_y[r];
@@ -135,7 +156,7 @@ __global__ __launch_bounds__(kBlock) void speed_gradient_moments_kernel(
   // wave w now owns output rows y0 + w, y0 + w + 4, ...: the runs' fits
   // merged in run order
 #pragma unroll
-  for (int r = w; r < kBand; r += kWavesPerBlock) {
+  for (int r = w; r < BAND; r += kWavesPerBlock) {
     const int y = y0 + r;
     if (y >= ny) break;
     float mx = 0.0f, qx = 0.0f, my = 0.0f, qy = 0.0f;
@@ -160,14 +181,21 @@ hipError_t launch_sg(const void* u, const void* v, int64_t m, int64_t ny, int64_
                      int64_t stride, const StencilCoef& k, int ddof, void* mgx, void* vgx,
                      void* mgy, void* vgy, hipStream_t s) {
   const float inv_dof = static_cast<float>(1.0 / static_cast<double>(m - ddof));
-  const int n_strips = int((nx + kStrip - 1) / kStrip);
+  const int64_t n_strips = (nx + kStrip - 1) / kStrip;
   const int64_t blocks = speed_gradient_blocks(ny, nx);  // one per tile
   if (!launch_fits(blocks, kBlock)) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((speed_gradient_moments_kernel<Tin, Tout>), dim3(unsigned(blocks)),
-                     dim3(kBlock), 0, s, static_cast<const Tin*>(u), static_cast<const Tin*>(v),
-                     int(m), int(ny), int(nx), stride, k, inv_dof, static_cast<Tout*>(mgx),
-                     static_cast<Tout*>(vgx), static_cast<Tout*>(mgy), static_cast<Tout*>(vgy),
-                     n_strips);
+#define PDIV_SG(BAND)                                                                           \
+  hipLaunchKernelGGL((speed_gradient_moments_kernel<BAND, Tin, Tout>),                          \
+                     dim3(unsigned(n_strips * ((ny + BAND - 1) / BAND))), dim3(kBlock), 0, s,   \
+                     static_cast<const Tin*>(u), static_cast<const Tin*>(v), int(m), int(ny),   \
+                     int(nx), stride, k, inv_dof, static_cast<Tout*>(mgx),                      \
+                     static_cast<Tout*>(vgx), static_cast<Tout*>(mgy), static_cast<Tout*>(vgy), \
+                     int(n_strips))
+  if (blocks < kShortBandBlocks)
+    PDIV_SG(4);
+  else
+    PDIV_SG(kBand);
+#undef PDIV_SG
   return hipGetLastError();
 }
 

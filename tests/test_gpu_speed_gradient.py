@@ -109,3 +109,19 @@ def test_ensemble_full_size_and_the_path_on_it():
     ref_e2e = O.lcp(*O.divergence_gaussian(*ref, 1.0, 1.0), iso)
     print(f"[721x1440x50] end to end max |LCP - oracle(float64 fit)| = "
           f"{float(np.max(np.abs(e2e - ref_e2e))):.3e}")
+
+
+@pytest.mark.parametrize("m,shape", [(1, (6, 63)), (2, (4, 62)), (5, (5, 125)), (9, (13, 64)),
+                                     (3, (1100, 950))])
+def test_member_runs_and_band_heights(m, shape):
+    """Runs of no, one and several members per wave (each wave loads a member
+    ahead), grids around the strips and bands of four rows, and one of enough
+    tiles for bands of eight."""
+    ny, nx = shape
+    rng = np.random.default_rng(m + nx)
+    U = rng.normal(0.4, 1, (m, ny, nx)).astype(np.float32)
+    V = rng.normal(-0.2, 1, (m, ny, nx)).astype(np.float32)
+    got = P.speed_gradient_moments(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda(), 1.0, 1.0,
+                                   0)
+    U, V = U.astype(np.float64), V.astype(np.float64)
+    _check([host64(g) for g in got], O.speed_gradient_moments(U, V, 1.0, 1.0, 0), U, V, m, 0)
