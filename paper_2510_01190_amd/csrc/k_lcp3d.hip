@@ -43,18 +43,6 @@ constexpr int kWavesPerBlock = kBlock / 64;
 // longer chunks mean fewer waves.  At 512^3 float32: 8, 12, 16, 32, 64
 // slices take 0.877, 0.852, 0.901, 0.962, 0.976 ms.
 constexpr int kZChunk = 12;
-// Vertex rows per band: 32, except 16 for the two-step kernel on rows that
-// do not start on lines, where the shorter walks (twice the waves, the first
-// row of each band peeled) measured faster (512^3 dense maps: 0.396 / 0.911 /
-// 3.152 ms at 1 / 4 / 16 isovalues against 0.408 / 0.958 / 3.377 ms with
-// 32); line-aligned rows are unchanged by it and the fused kernel on dense
-// rows gains nothing (0.985 / 1.482 / 3.955 against 0.980 / 1.496 / 3.879).
-template <bool FUSED, bool LINES>
-constexpr int band_rows3() {
-  return (LINES || FUSED) ? 32 : 16;
-}
-constexpr int kMinBandRows3 = 16;
-
 // Eq. 2-3 with the z term at one vertex; the neighbours are already clamped
 // at the boundary and the coefficients chosen (1/(2h) inside, 1/h on a
 // boundary plane).  Contraction is off so the rounding is fixed.
@@ -165,9 +153,10 @@ struct Planes6 {
 
 // One vertex row's inputs for a lane's column at the L+1 levels it holds,
 // loaded a row ahead of their use.  Two-step: the divergence mean and
-// variance per level.  Fused: U's x neighbours (mean, variance) and V's next
-// row per level, and W at the levels one below to one above the held ones
-// (level t + 1 of the array is held level t; adjacent held levels share W).
+// variance per level.  Fused: U (mean, variance; its x neighbours come from
+// the adjacent lanes) and V's next row per level, and W at the levels one
+// below to one above the held ones (level t + 1 of the array is held level t;
+// adjacent held levels share W).
 template <int L, bool FUSED>
 struct Row3;
 template <int L>
@@ -176,7 +165,7 @@ struct Row3<L, false> {
 };
 template <int L>
 struct Row3<L, true> {
-  float ul[L + 1], ur[L + 1], sl[L + 1], sr[L + 1];
+  float u[L + 1], s[L + 1];
   float vm[L + 1], vv[L + 1];
   float wm[L + 3], wv[L + 3];
 };
@@ -200,8 +189,11 @@ __device__ __forceinline__ void row_corners(const Row3<L, FUSED>& r, VWin<L>& w,
   for (int l = 0; l <= L; ++l) {
     DivGauss g;
     if constexpr (FUSED) {
-      g = div_gauss3(r.ul[l], r.ur[l], r.sl[l], r.sr[l], w.m[l][0], r.vm[l], w.v[l][0], r.vv[l],
-                     r.wm[l], r.wm[l + 2], r.wv[l], r.wv[l + 2], cxm, cxv, cym, cyv,
+      // the lanes beside a boundary column hold that column again (clamped),
+      // so the boundary's one-sided differences need no selection
+      g = div_gauss3(dpp_from_left(r.u[l]), dpp_from_right(r.u[l]), dpp_from_left(r.s[l]),
+                     dpp_from_right(r.s[l]), w.m[l][0], r.vm[l], w.v[l][0], r.vv[l], r.wm[l],
+                     r.wm[l + 2], r.wv[l], r.wv[l + 2], cxm, cxv, cym, cyv,
                      bz[l] ? k.czm_bd : k.czm_in, bz[l] ? k.czv_bd : k.czv_in);
       w.m[l][0] = w.m[l][1];
       w.v[l][0] = w.v[l][1];
@@ -246,7 +238,7 @@ struct Rows3 {
 // One row's inputs at L+1 held levels.  lo[t]: byte offset of level t
 // relative to level lb (W's level t - 1 for the fused W array, whose level
 // t + 1 is held level t); wave-uniform for the wave's own column (scalar
-// offsets), per lane for the seam (added to the column offset).
+// offsets), per lane for the two-step seam (added to the column offset).
 template <int L, bool UNIFORM, typename T>
 __device__ __forceinline__ void load_levels(Row3<L, false>& r, const Rows3<false, T>& rd,
                                             const uint32_t* lo, const Col& c) {
@@ -259,22 +251,18 @@ __device__ __forceinline__ void load_levels(Row3<L, false>& r, const Rows3<false
 template <int L, bool UNIFORM, typename T>
 __device__ __forceinline__ void load_levels(Row3<L, true>& r, const Rows3<true, T>& rd,
                                             const uint32_t* lw, const Col& c) {
-  auto get = [&](const RowReader<T>& x, uint32_t col, uint32_t lev) {
-    return UNIFORM ? x.get(col, lev) : x.get(col + lev);
-  };
+  static_assert(UNIFORM, "the fused walk has no seam");
 #pragma unroll
   for (int t = 0; t < L + 3; ++t) {
-    r.wm[t] = get(rd.wm, c.x, lw[t]);
-    r.wv[t] = get(rd.wv, c.x, lw[t]);
+    r.wm[t] = rd.wm.get(c.x, lw[t]);
+    r.wv[t] = rd.wv.get(c.x, lw[t]);
   }
 #pragma unroll
   for (int l = 0; l <= L; ++l) {
-    r.ul[l] = get(rd.u, c.xl, lw[l + 1]);
-    r.ur[l] = get(rd.u, c.xr, lw[l + 1]);
-    r.sl[l] = get(rd.s, c.xl, lw[l + 1]);
-    r.sr[l] = get(rd.s, c.xr, lw[l + 1]);
-    r.vm[l] = get(rd.vm, c.x, lw[l + 1]);
-    r.vv[l] = get(rd.vv, c.x, lw[l + 1]);
+    r.u[l] = rd.u.get(c.x, lw[l + 1]);
+    r.s[l] = rd.s.get(c.x, lw[l + 1]);
+    r.vm[l] = rd.vm.get(c.x, lw[l + 1]);
+    r.vv[l] = rd.vv.get(c.x, lw[l + 1]);
   }
 }
 
@@ -291,21 +279,30 @@ __device__ __forceinline__ void load_levels(Row3<L, true>& r, const Rows3<true, 
 // are loaded one row ahead, so their latency overlaps the previous row's
 // arithmetic.
 //
-// Two strip layouts, the same arithmetic (so the same bits):
+// Strip layouts, the same arithmetic (so the same bits):
 //   LINES = false: lane L holds vertex column x0+L, x0 = 63 strip; the wave
 //     forms the 63 cells [x0, x0+63) (lane 63 has no cell), for any row pitch.
-//   LINES = true, for outputs whose rows start on 128-byte lines: x0 = 64
-//     strip and lane 63 forms cell x0+63 too, so each store instruction
-//     writes 256 contiguous bytes, two whole lines.  Its right column x0+64
-//     belongs to no lane: a seam step has lanes 2i and 2i+1 (i = q LZ + l)
-//     evaluate columns x0+63 and x0+64 at levels l and l+1 for isovalue q,
-//     lane 2i forms that cell with the cell formula of every other lane, and
-//     lane 63 takes it over with one readlane/writelane per (q, l).  Needs
-//     2 KC LZ <= 64.
-// FUSED: each row's corners come from Eq. 2-3 with the z term evaluated on
-// the spot from the six moment volumes (the divergence never reaches HBM),
-// with the operands and order of divergence3d_kernel, so the maps are
-// bitwise the two-step result.
+//   LINES = true (two-step), for outputs whose rows start on 128-byte lines:
+//     x0 = 64 strip and lane 63 forms cell x0+63 too, so each store
+//     instruction writes 256 contiguous bytes, two whole lines.  Its right
+//     column x0+64 belongs to no lane: a seam step has lanes 2i and 2i+1 (i =
+//     q LZ + l) evaluate columns x0+63 and x0+64 at levels l and l+1 for
+//     isovalue q, lane 2i forms that cell with the cell formula of every other
+//     lane, and lane 63 takes it over with one readlane/writelane per (q, l).
+//     Needs 2 KC LZ <= 64.
+//   FUSED: each row's corners come from Eq. 2-3 with the z term evaluated on
+//     the spot from the six moment volumes (the divergence never reaches HBM),
+//     with the operands and order of divergence3d_kernel, so the maps are
+//     bitwise the two-step result.  Lane L holds column x0-1+L, x0 = 61 strip:
+//     lanes 0 and 63 are the x halo of U, whose neighbours the lanes exchange
+//     by DPP, and lanes 1..61 form the 61 cells [x0, x0+61), for any row
+//     pitch.  Bound by latency and registers: loading U once instead of its
+//     two neighbours, and no seam (which held two columns' moments at two
+//     levels of their own), took 4 isovalues from 240 registers on line-
+//     aligned rows, 173 on others, to 161, three waves per SIMD instead of
+//     two.  256x512x384 float32 at 1 / 4 / 8 isovalues on line-aligned rows
+//     393 / 584 / 899 -> 357 / 555 / 846 us, bfloat16 319 / 547 / 920 -> 245 /
+//     463 / 780; 512^3 float32 1026 / 1505 / 2302 -> 966 / 1500 / 2190.
 // With 8 corners the float32 combination can land an ulp outside [0, 1]
 // where the probability is 0 or 1; the exact value is inside, so clamping
 // only removes error.  The IEEE 754-2019 maximum and minimum (v_maximum3_f32,
@@ -315,14 +312,21 @@ __device__ __forceinline__ float clamp01(float v) {
   return __builtin_elementwise_minimum(__builtin_elementwise_maximum(v, 0.0f), 1.0f);
 }
 
+template <bool FUSED, bool LINES>
+constexpr int strip_cells3() {
+  return FUSED ? 61 : LINES ? 64 : 63;
+}
+
 template <int KC, int LZ, bool FUSED, bool LINES, typename T>
 __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int ny, int nx,
                                                        StencilCoef3 k, IsoChunk iso,
                                                        float* __restrict__ out, int64_t pitch,
                                                        int64_t plane, int n_groups, int n_strips,
-                                                       int n_bands) {
+                                                       int n_bands, int band_rows) {
+  static_assert(!(LINES && FUSED), "the seam step is the two-step kernel's");
   static_assert(!LINES || 2 * KC * LZ <= 64, "the seam step needs two lanes per (q, l)");
-  constexpr int kW = LINES ? 64 : 63;  // cells per strip
+  constexpr int kW = strip_cells3<FUSED, LINES>();
+  constexpr int kHalo = FUSED ? 1 : 0;  // lanes left of the strip's first cell
   const int nb = gridDim.x, xcd = blockIdx.x % 8, q8 = nb / 8, r8 = nb % 8;
   const int blk = xcd * q8 + min(xcd, r8) + blockIdx.x / 8;
   const int wave = __builtin_amdgcn_readfirstlane(blk * kWavesPerBlock + (threadIdx.x >> 6));
@@ -334,14 +338,16 @@ __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int 
   if (band >= n_bands) return;
   const int k0 = grp * LZ;
   const int nl = min(LZ, nz - 1 - k0);
-  const int j0 = band * band_rows3<FUSED, LINES>();
-  const int j1 = min(j0 + band_rows3<FUSED, LINES>(), ny - 1);
+  const int j0 = band * band_rows;
+  const int j1 = min(j0 + band_rows, ny - 1);
   const int x0 = strip * kW;
   const uint32_t store_bytes = uint32_t(min(kW, nx - 1 - x0)) * 4u;
-  const uint32_t soff = uint32_t(lane) * 4u;
+  // a halo lane's offset lies beyond any row, which drops its store
+  const uint32_t soff = lane >= kHalo ? uint32_t(lane - kHalo) * 4u : 0x7ffffff0u;
   const int64_t layer = int64_t(ny - 1) * pitch;
   const int64_t vplane = int64_t(ny) * nx;
-  const Col col = make_col(uint32_t(min(x0 + lane, nx - 1)), nx, sizeof(T));
+  const Col col =
+      make_col(uint32_t(min(max(x0 + lane - kHalo, 0), nx - 1)), nx, sizeof(T));
   const float cxm = col.bx ? k.xy.cxm_bd : k.xy.cxm_in;
   const float cxv = col.bx ? k.xy.cxv_bd : k.xy.cxv_in;
   bool bz[LZ + 1];
@@ -359,31 +365,20 @@ __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int 
 #pragma unroll
   for (int q = 1; q < KC; ++q) c_seam = (sq == q) ? iso.c[q] : c_seam;
   const Col cs = make_col(uint32_t(min(x0 + 63 + (lane & 1), nx - 1)), nx, sizeof(T));
-  const float sxm = cs.bx ? k.xy.cxm_bd : k.xy.cxm_in;
-  const float sxv = cs.bx ? k.xy.cxv_bd : k.xy.cxv_in;
-  bool sbz[2];
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int kk = min(k0 + sl + t, nz - 1);
-    sbz[t] = (kk == 0) | (kk == nz - 1);
-  }
   // Level offsets (bytes) from the readers' base level lb.  Fused: W's
   // levels clamp(k0-1+t), t < LZ+3 (held level l is t = l+1); two-step: the
   // held levels.  The seam's per lane, from its first level k0+sl.
   const int lb = FUSED ? max(k0 - 1, 0) : k0;
   const uint32_t pb = uint32_t(vplane) * uint32_t(sizeof(T));
   constexpr int kLv = FUSED ? LZ + 3 : LZ + 1;
-  uint32_t lo[kLv], slo[FUSED ? 4 : 2];
+  uint32_t lo[kLv], slo[2];
 #pragma unroll
   for (int t = 0; t < kLv; ++t)
     lo[t] = uint32_t((FUSED ? min(max(k0 - 1 + t, 0), nz - 1) : min(k0 + t, nz - 1)) - lb) * pb;
 #pragma unroll
-  for (int t = 0; t < (FUSED ? 4 : 2); ++t)
-    slo[t] = uint32_t((FUSED ? min(max(k0 + sl - 1 + t, 0), nz - 1) : min(k0 + sl + t, nz - 1)) -
-                      lb) * pb;
+  for (int t = 0; t < 2; ++t) slo[t] = uint32_t(min(k0 + sl + t, nz - 1) - lb) * pb;
 
   VWin<LZ> win;
-  VWin<1> swin;
   if constexpr (FUSED) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -395,17 +390,10 @@ __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int 
         win.m[l][h] = vm.get(col.x, lo[l + 1]);
         win.v[l][h] = vv.get(col.x, lo[l + 1]);
       }
-      if constexpr (LINES) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          swin.m[t][h] = vm.get(cs.x + slo[t + 1]);
-          swin.v[t][h] = vv.get(cs.x + slo[t + 1]);
-        }
-      }
     }
   }
   Row3<LZ, FUSED> raw;
-  Row3<1, FUSED> sraw;
+  Row3<1, false> sraw;
   auto load = [&](int j) {
     const Rows3<FUSED, T> rd(src, lb, j, nz, ny, nx, vplane);
     load_levels<LZ, true, T>(raw, rd, lo, col);
@@ -427,12 +415,15 @@ __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int 
     const bool by = (j == 0) | (j == ny - 1);
     return by ? k.xy.cyv_bd : k.xy.cyv_in;
   };
+  auto seam_corners = [&](Corner (&sc)[2]) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) sc[t] = make_corner(DivGauss{sraw.m[t], sraw.v[t]});
+  };
   {  // the band's first vertex row: corners only (j1 > j0 always)
     Corner c[LZ + 1];
     row_corners<LZ, FUSED>(raw, win, bz, cxm, cxv, cym_of(j0), cyv_of(j0), k, c);
     Corner sc[2];
-    if constexpr (LINES)
-      row_corners<1, FUSED>(sraw, swin, sbz, sxm, sxv, cym_of(j0), cyv_of(j0), k, sc);
+    if constexpr (LINES) seam_corners(sc);
     load(j0 + 1);
 #pragma unroll
     for (int q = 0; q < KC; ++q)
@@ -454,8 +445,7 @@ __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int 
     Corner c[LZ + 1];
     row_corners<LZ, FUSED>(raw, win, bz, cxm, cxv, cym_of(j), cyv_of(j), k, c);
     Corner sc[2];
-    if constexpr (LINES)
-      row_corners<1, FUSED>(sraw, swin, sbz, sxm, sxv, cym_of(j), cyv_of(j), k, sc);
+    if constexpr (LINES) seam_corners(sc);
     if (j < j1) load(j + 1);
     // seam: lane 2i holds cell x0+63 of layer l at isovalue q
     float seam = 0.0f;
@@ -511,30 +501,53 @@ __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int 
   }
 }
 
+// Vertex rows per band.  A band's first row is evaluated for both bands and
+// its V window loaded again, but a wave walks its rows one after another, so
+// small volumes want short bands (100x130x150, fused, 4 isovalues, us with 1 /
+// 2 / 4 / 8 / 16 / 32 rows: 33 / 28 / 30 / 38 / 46 / 87; two-step 25 / 20 / 22 /
+// 28 / 35 / 67; 48^3 7 / 9 / 14 / 23 / 43 / 81; 180x200x220 123 / 107 / 98 / 100
+// / 113 / 140; 256x512x384 578 / 558 / 564 / 586 with 4 ... 32; 512^3 1573 / 1487
+// / 1500 / 1563).
+int band_rows3(int64_t columns, int64_t rows) {
+  auto waves = [&](int b) { return columns * ((rows + b - 1) / b); };
+  if (waves(16) >= 12000) return 16;
+  if (waves(8) >= 8000) return 8;
+  return waves(4) >= 3000 ? 4 : waves(2) >= 1500 ? 2 : 1;
+}
+
 template <int KC, int LZ, bool FUSED, bool LINES, typename T>
 hipError_t launch_lcp3d_kc(const Planes6& src, int nz, int ny, int nx, const StencilCoef3& k,
                            const IsoChunk& iso, float* out, int64_t pitch, int64_t plane,
                            hipStream_t s) {
-  constexpr int kW = LINES ? 64 : 63;
+  constexpr int kW = strip_cells3<FUSED, LINES>();
   const int n_groups = (nz - 1 + LZ - 1) / LZ;
   const int n_strips = (nx - 1 + kW - 1) / kW;
-  constexpr int kRows = band_rows3<FUSED, LINES>();
-  const int n_bands = (ny - 1 + kRows - 1) / kRows;
-  const int64_t waves = int64_t(n_groups) * n_strips * n_bands;
-  const int64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
+  int band_rows = band_rows3(int64_t(n_groups) * n_strips, ny - 1);
+  int n_bands = 0;
+  int64_t blocks = 0;
+  do {  // taller bands where a launch would not hold the blocks
+    n_bands = (ny - 1 + band_rows - 1) / band_rows;
+    const int64_t waves = int64_t(n_groups) * n_strips * n_bands;
+    blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
+    if (launch_fits(blocks, kBlock)) break;
+    band_rows *= 2;
+  } while (n_bands > 1);
   if (!launch_fits(blocks, kBlock)) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL((lcp3d_kernel<KC, LZ, FUSED, LINES, T>), dim3(unsigned(blocks)), dim3(kBlock),
                      0, s, src, nz, ny, nx, k, iso, out, pitch, plane, n_groups, n_strips,
-                     n_bands);
+                     n_bands, band_rows);
   return hipGetLastError();
 }
 
 }  // namespace
 
+// What the grid check counts: bands of 16 rows (launches take taller ones
+// where those would not fit).
+constexpr int kCheckedBandRows = 16;
 int64_t lcp3d_blocks(int64_t nz, int64_t ny, int64_t nx, int kc) {
   const int lz = kc <= 4 ? 4 : 2;  // the fewest layers any launch uses
   const int64_t waves = ((nz - 1 + lz - 1) / lz) * ((nx - 1 + 62) / 63) *
-                        ((ny - 1 + kMinBandRows3 - 1) / kMinBandRows3);
+                        ((ny - 1 + kCheckedBandRows - 1) / kCheckedBandRows);
   return (waves + kWavesPerBlock - 1) / kWavesPerBlock;
 }
 
@@ -598,17 +611,19 @@ hipError_t launch_lcp3d_kcs(const Planes6& src, int z, int y, int x, const Stenc
   }
 }
 
-// The line-aligned tile when every output row starts on a 128-byte line.
+// Two-step: the line-aligned tile when every output row starts on a 128-byte
+// line.
 template <bool FUSED, typename T>
 hipError_t launch_lcp3d_any(const Planes6& src, int64_t nz, int64_t ny, int64_t nx,
                             const StencilCoef3& k, const IsoChunk& iso, int kc, float* out_k0,
                             int64_t pitch, int64_t plane, hipStream_t s) {
   if (!lcp3d_slice_fits(ny, nx, sizeof(T))) return hipErrorInvalidValue;
   const int z = int(nz), y = int(ny), x = int(nx);
-  const bool lines = (reinterpret_cast<uintptr_t>(out_k0) % 128 == 0) && pitch % 32 == 0 &&
-                     plane % 32 == 0;
-  return lines ? launch_lcp3d_kcs<FUSED, true, T>(src, z, y, x, k, iso, kc, out_k0, pitch, plane, s)
-               : launch_lcp3d_kcs<FUSED, false, T>(src, z, y, x, k, iso, kc, out_k0, pitch, plane, s);
+  if constexpr (!FUSED) {
+    if (rows_on_lines(out_k0, pitch, plane))
+      return launch_lcp3d_kcs<FUSED, true, T>(src, z, y, x, k, iso, kc, out_k0, pitch, plane, s);
+  }
+  return launch_lcp3d_kcs<FUSED, false, T>(src, z, y, x, k, iso, kc, out_k0, pitch, plane, s);
 }
 
 }  // namespace

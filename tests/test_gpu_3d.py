@@ -245,3 +245,32 @@ def test_bench_size_sampled_slabs():
         worst = max(worst, float(np.max(np.abs(host64(out[:, k0:k0 + 2]) - r))))
     print(f"\n[512^3 K=4] max |LCP - oracle(stored volumes)| on sampled slabs = {worst:.3e}")
     assert worst <= LCP_TOL
+
+
+@pytest.mark.parametrize("shape,k", [((3, 4, 62), 1), ((3, 5, 63), 4), ((2, 3, 123), 8),
+                                     ((6, 9, 124), 16), ((9, 2, 61), 2), ((90, 70, 130), 4),
+                                     ((70, 260, 130), 1), ((300, 300, 200), 1)])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_fused_strips_of_61_cells_and_band_heights(shape, k, dt):
+    """The fused walk takes U's neighbours from the adjacent lanes, in strips of
+    61 cells: widths of one strip less and more than whole, and volumes whose
+    band heights are 1, 2, 4 and 8 rows, bitwise the two-step maps on dense,
+    odd and line-aligned rows, padding untouched; the two-step line-aligned and
+    dense maps agree, and the lowest cell layer is within 1e-5 of the oracle."""
+    rng = np.random.default_rng(sum(shape))
+    ts = []
+    for q in range(6):
+        a = rng.normal(0, 0.3, shape) if q % 2 == 0 else rng.uniform(0.02, 0.2, shape)
+        ts.append(dev(a, dt))
+    div = P.divergence_gaussian_3d(*ts, dx=0.5, dy=1.0, dz=2.0)
+    iso = np.linspace(-0.4, 0.4, k).astype(np.float32)
+    ref = P.lcp_3d(*div, iso)
+    for pitch in (None, shape[2] - 1, shape[2] + 4):
+        view, buf = _padded(k, shape, pitch=pitch, gap=32)
+        P.lcp_3d_from_moments(*ts, iso, dx=0.5, dy=1.0, dz=2.0, out=view)
+        assert torch.equal(view, ref) and _padding_untouched(view, buf), pitch
+        view, buf = _padded(k, shape, pitch=pitch, gap=32)
+        P.lcp_3d(*div, iso, out=view)
+        assert torch.equal(view, ref) and _padding_untouched(view, buf), pitch
+    want = O.lcp_3d(host64(div[0][:2]), host64(div[1][:2]), iso)
+    assert np.max(np.abs(host64(ref[:, :1]) - want)) <= LCP_TOL
