@@ -317,9 +317,13 @@ constexpr int strip_cells3() {
   return FUSED ? 61 : LINES ? 64 : 63;
 }
 
-template <int KC, int LZ, bool FUSED, bool LINES, typename T>
+// ALL: every slot holds an isovalue; else the slots from n_store on store
+// nothing (the run-time count costs scalar registers and selects: two-step at 8
+// isovalues 595 -> 710 us at 256x512x384, fused at 16 1550 -> 1746, so only
+// counts that save a whole launch run that way).
+template <int KC, int LZ, bool FUSED, bool LINES, bool ALL, typename T>
 __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int ny, int nx,
-                                                       StencilCoef3 k, IsoChunk iso,
+                                                       StencilCoef3 k, IsoChunk iso, int n_store,
                                                        float* __restrict__ out, int64_t pitch,
                                                        int64_t plane, int n_groups, int n_strips,
                                                        int n_bands, int band_rows) {
@@ -476,7 +480,9 @@ __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int 
         v = clamp01(v);
         if constexpr (LINES)
           v = to_lane63(v, __builtin_amdgcn_readlane(__float_as_int(seam), 2 * (q * LZ + l)));
-        RowWriter<LINES>(row_out + int64_t(q) * plane + int64_t(l) * layer, layer_bytes[l])
+        // maps past n_store (spare slots) get an empty record range
+        RowWriter<LINES>(row_out + int64_t(q) * plane + int64_t(l) * layer,
+                         ALL || q < n_store ? layer_bytes[l] : 0u)
             .put(v, soff);
       }
     }
@@ -515,9 +521,9 @@ int band_rows3(int64_t columns, int64_t rows) {
   return waves(4) >= 3000 ? 4 : waves(2) >= 1500 ? 2 : 1;
 }
 
-template <int KC, int LZ, bool FUSED, bool LINES, typename T>
+template <int KC, int LZ, bool FUSED, bool LINES, bool ALL, typename T>
 hipError_t launch_lcp3d_kc(const Planes6& src, int nz, int ny, int nx, const StencilCoef3& k,
-                           const IsoChunk& iso, float* out, int64_t pitch, int64_t plane,
+                           const IsoChunk& iso, int n_store, float* out, int64_t pitch, int64_t plane,
                            hipStream_t s) {
   constexpr int kW = strip_cells3<FUSED, LINES>();
   const int n_groups = (nz - 1 + LZ - 1) / LZ;
@@ -533,8 +539,8 @@ hipError_t launch_lcp3d_kc(const Planes6& src, int nz, int ny, int nx, const Ste
     band_rows *= 2;
   } while (n_bands > 1);
   if (!launch_fits(blocks, kBlock)) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((lcp3d_kernel<KC, LZ, FUSED, LINES, T>), dim3(unsigned(blocks)), dim3(kBlock),
-                     0, s, src, nz, ny, nx, k, iso, out, pitch, plane, n_groups, n_strips,
+  hipLaunchKernelGGL((lcp3d_kernel<KC, LZ, FUSED, LINES, ALL, T>), dim3(unsigned(blocks)), dim3(kBlock),
+                     0, s, src, nz, ny, nx, k, iso, n_store, out, pitch, plane, n_groups, n_strips,
                      n_bands, band_rows);
   return hipGetLastError();
 }
@@ -553,6 +559,18 @@ int64_t lcp3d_blocks(int64_t nz, int64_t ny, int64_t nx, int kc) {
 
 bool lcp3d_slice_fits(int64_t ny, int64_t nx, size_t elem_bytes) {
   return 7 * ny * nx * int64_t(elem_bytes) < (int64_t(1) << 31);
+}
+
+// Isovalues of the next launch when `left` remain.  Two-step: 8, 4, 3, 2, 1 (a
+// wave carries four cell layers at up to 8; at 16 it could carry only two, and
+// the tails of the extra shared z levels cost more than reading the divergence
+// volumes twice).  Fused (each launch reads six volumes): 16, 8 and any count
+// below.  256x512x384, us, against chunks of powers of two: two-step 3
+// isovalues 275 / 339, 7 577 / 654; fused 3 461 / 752, 5 683 / 858, 6 716 /
+// 957, 7 870 / 1288, 14 1584 / 1815.
+int lcp3d_chunk(int left, bool fused) {
+  if (fused) return left >= 16 ? 16 : left >= 8 ? 8 : left;
+  return left >= 8 ? 8 : left >= 4 ? 4 : left;
 }
 
 int64_t divergence3d_blocks(int64_t nz, int64_t ny, int64_t nx) {
@@ -591,24 +609,28 @@ template <bool FUSED, bool LINES, typename T>
 hipError_t launch_lcp3d_kcs(const Planes6& src, int z, int y, int x, const StencilCoef3& k,
                             const IsoChunk& iso, int kc, float* out, int64_t pitch, int64_t plane,
                             hipStream_t s) {
+#define PDIV_L3(K, LZ, ALL)                                                                   \
+  return launch_lcp3d_kc<K, LZ, FUSED, LINES, ALL, T>(src, z, y, x, k, iso, kc, out, pitch, \
+                                                      plane, s)
+  // two-step: 4 layers; fused: the moment rows' registers leave room for 2
+  // above 4 isovalues.  lcp3d_chunk gives only these counts.
   switch (kc) {
-    case 1: return launch_lcp3d_kc<1, 4, FUSED, LINES, T>(src, z, y, x, k, iso, out, pitch, plane, s);
-    case 2: return launch_lcp3d_kc<2, 4, FUSED, LINES, T>(src, z, y, x, k, iso, out, pitch, plane, s);
-    case 4: return launch_lcp3d_kc<4, 4, FUSED, LINES, T>(src, z, y, x, k, iso, out, pitch, plane, s);
-    // two-step: 4 layers at 8 isovalues (16 come as two launches); fused: the
-    // moment rows' registers leave room for 2 layers at 8 and 16
-    case 8:
-      if constexpr (FUSED)
-        return launch_lcp3d_kc<8, 2, FUSED, LINES, T>(src, z, y, x, k, iso, out, pitch, plane, s);
-      else
-        return launch_lcp3d_kc<8, 4, FUSED, LINES, T>(src, z, y, x, k, iso, out, pitch, plane, s);
-    case 16:
-      if constexpr (FUSED)
-        return launch_lcp3d_kc<16, 2, FUSED, LINES, T>(src, z, y, x, k, iso, out, pitch, plane, s);
-      else
-        return hipErrorInvalidValue;
-    default: return hipErrorInvalidValue;
+    case 1: PDIV_L3(1, 4, true);
+    case 2: PDIV_L3(2, 4, true);
+    case 3: PDIV_L3(3, 4, true);
+    case 4: PDIV_L3(4, 4, true);
+    case 8: PDIV_L3(8, FUSED ? 2 : 4, true);
   }
+  if constexpr (FUSED) {
+    switch (kc) {
+      case 5: PDIV_L3(6, 2, false);
+      case 6: PDIV_L3(6, 2, true);
+      case 7: PDIV_L3(8, 2, false);
+      case 16: PDIV_L3(16, 2, true);
+    }
+  }
+#undef PDIV_L3
+  return hipErrorInvalidValue;
 }
 
 // Two-step: the line-aligned tile when every output row starts on a 128-byte

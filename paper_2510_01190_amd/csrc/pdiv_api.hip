@@ -648,19 +648,14 @@ pdiv_status check_layout3(int64_t row_pitch, int64_t plane_stride, int64_t nz, i
   return PDIV_OK;
 }
 
-// Isovalue chunks for the 3D LCP launches: 8, 4, 2, 1 for the two-step form
-// (a wave carries four cell layers at up to 8 isovalues; at 16 it could
-// carry only two, and the tails of the extra shared z levels cost more than
-// reading the divergence volumes twice), 16, 8, 4, 2, 1 fused (the six
-// moment volumes are read once).  planes is null for the two-step form (dm,
+// The isovalues in chunks of lcp3d_chunk, one launch each.  planes is null for the two-step form (dm,
 // dv given), else the six moment volumes.
 pdiv_status lcp3d_chunks(const float* dm, const float* dv, const void* const* planes,
                          pdiv_dtype dt, int64_t nz, int64_t ny, int64_t nx,
                          const StencilCoef3& k, const float* iso_host, int32_t n_iso,
                          float* lcp, const OutLayout& lo, hipStream_t s) {
   for (int32_t k0 = 0; k0 < n_iso;) {
-    const int left = n_iso - k0;
-    const int kc = (left >= 16 && planes) ? 16 : left >= 8 ? 8 : left >= 4 ? 4 : left >= 2 ? 2 : 1;
+    const int kc = lcp3d_chunk(n_iso - k0, planes != nullptr);
     IsoChunk c;
     for (int q = 0; q < kIsoChunk; ++q) c.c[q] = iso_host[k0 + (q < kc ? q : kc - 1)];
     float* const out = lcp + k0 * lo.plane;

@@ -86,7 +86,6 @@ hipError_t launch_divergence(const void* mu, const void* vu, const void* mv, con
 constexpr int iso_bucket(int n) {
   return n <= 4 ? (n < 1 ? 1 : n) : n <= 6 ? 6 : n <= 8 ? 8 : n <= 12 ? 12 : 16;
 }
-
 // LCP for isovalues [k0, k0+kc) (kc <= 16): from divergence Gaussians
 // (fused = false, planes dmean/dvar as float) or from moments (fused = true).
 // Output rows are `pitch` floats apart, planes `plane` floats.
@@ -158,7 +157,10 @@ hipError_t launch_divergence3d(const void* mu, const void* vu, const void* mv, c
                                int64_t ny, int64_t nx, const StencilCoef3& k, float* dmean,
                                float* dvar, hipStream_t s);
 
-// 8-corner LCP for isovalues [k0, k0+kc) (kc in {1, 2, 4, 8, 16}) from 3D
+// Isovalues of the next 3D launch when `left` remain.
+int lcp3d_chunk(int left, bool fused);
+
+// 8-corner LCP for isovalues [k0, k0+kc) (kc from lcp3d_chunk) from 3D
 // divergence Gaussians; maps [kc][nz-1][ny-1][nx-1], rows `pitch` floats
 // apart, layers (ny-1) pitch, maps `plane` floats apart.
 hipError_t launch_lcp3d(const float* dm, const float* dv, int64_t nz, int64_t ny, int64_t nx,

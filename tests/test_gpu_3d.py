@@ -274,3 +274,25 @@ def test_fused_strips_of_61_cells_and_band_heights(shape, k, dt):
         assert torch.equal(view, ref) and _padding_untouched(view, buf), pitch
     want = O.lcp_3d(host64(div[0][:2]), host64(div[1][:2]), iso)
     assert np.max(np.abs(host64(ref[:, :1]) - want)) <= LCP_TOL
+
+
+@pytest.mark.parametrize("shape", [(2, 2, 2), (6, 9, 130)])
+def test_every_isovalue_count_3d(shape):
+    """Every count's maps, in whatever launches it takes, are bitwise the ones
+    computed one isovalue at a time, fused and two-step, dense and
+    line-aligned, and nothing is written past the last map."""
+    rng = np.random.default_rng(shape[2])
+    ts = [dev(rng.normal(0, 0.3, shape) if q % 2 == 0 else rng.uniform(0.02, 0.2, shape), "f32")
+          for q in range(6)]
+    div = P.divergence_gaussian_3d(*ts)
+    iso = rng.uniform(-0.5, 0.5, 25).astype(np.float32)
+    ref = torch.cat([P.lcp_3d(*div, [c]) for c in iso])
+    assert np.max(np.abs(host64(ref[:2]) - O.lcp_3d(*map(host64, div), iso[:2]))) <= LCP_TOL
+    for k in range(2, 26):
+        for pitch in (shape[2] - 1, None):
+            view, buf = _padded(k, shape, pitch=pitch, gap=64)
+            P.lcp_3d(*div, iso[:k], out=view)
+            assert torch.equal(view, ref[:k]) and _padding_untouched(view, buf), (k, pitch)
+            view, buf = _padded(k, shape, pitch=pitch, gap=64)
+            P.lcp_3d_from_moments(*ts, iso[:k], out=view)
+            assert torch.equal(view, ref[:k]) and _padding_untouched(view, buf), (k, pitch)
