@@ -13,6 +13,7 @@
 // request's maps come from the same tile code as pdiv_lcp on the same
 // divergence Gaussians, so a result is bitwise the same alone or in the mix.
 #include <hip/hip_runtime.h>
+#include <sys/prctl.h>
 
 #include <algorithm>
 #include <atomic>
@@ -320,6 +321,11 @@ struct pdiv_server_s : serve::Executor {
 
   void run() {
     (void)hipSetDevice(device);
+    // The kernel may end a sleep up to the thread's timer slack late, 50 us by
+    // default: a poll of 20 us came round after 72, and a request waits for
+    // two or three of them (a new 512x512 field and six sliders: 410 us, 323
+    // with a slack of 1 us).
+    (void)prctl(PR_SET_TIMERSLACK, 1000ul, 0ul, 0ul, 0ul);
     std::unique_lock<std::mutex> lk(mu);
     while (true) {
       core->step(*this);
