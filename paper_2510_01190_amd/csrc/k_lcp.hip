@@ -56,7 +56,8 @@ constexpr int kWavesPerBlock = kBlock / kWave;
 // 62-column strips put the row segments off cache-line boundaries).  Either
 // way the operands are those of a straight evaluation with clamped
 // neighbours.
-template <typename T>
+// NT: non-temporal stores.
+template <typename T, bool NT>
 __global__ __launch_bounds__(kBlock) void divergence_kernel(const T* __restrict__ mu,
                                                             const T* __restrict__ vu,
                                                             const T* __restrict__ mv,
@@ -114,8 +115,13 @@ __global__ __launch_bounds__(kBlock) void divergence_kernel(const T* __restrict_
     r.vv_r = vv_r;
     const DivGauss g = raw_div(r, c.bx, j, ny, k);
     if (store) {
-      __builtin_nontemporal_store(g.mean, dmean + row + x);
-      __builtin_nontemporal_store(g.var, dvar + row + x);
+      if constexpr (NT) {
+        __builtin_nontemporal_store(g.mean, dmean + row + x);
+        __builtin_nontemporal_store(g.var, dvar + row + x);
+      } else {
+        dmean[row + x] = g.mean;
+        dvar[row + x] = g.var;
+      }
     }
     vm_l = vm_c;
     vv_l = vv_c;
@@ -301,36 +307,40 @@ hipError_t launch_any(const void* p0, const void* p1, const void* p2, const void
 hipError_t launch_divergence(const void* mu, const void* vu, const void* mv, const void* vv,
                              pdiv_dtype dt, int64_t ny, int64_t nx, const StencilCoef& k,
                              float* dmean, float* dvar, hipStream_t s) {
-  // rows per wave: at 8192^2 float32 takes 0.314 / 0.311 / 0.309 / 0.317 ms
-  // with 8 / 16 / 12 / 24 rows, 16-bit storage 0.310 / 0.347 / 0.366 / 0.377 ms
-  const int rows = dt == PDIV_F32 ? 16 : 8;
+  // Rows per wave: two.  A V row is then loaded twice (four rows per two), but
+  // from the caches, and short walks keep more waves in flight: with 2 / 4 / 8 /
+  // 16 rows 8192^2 float32 takes 299 / 303 / 308 / 314 us, 16-bit storage 285 /
+  // 308 / 332 / 407, 4096^2 77 / 79 / 82 / 88 and 79 / 81 / 92 / 106, 1021x1531
+  // 10.1 / 10.7 / 11.5 / 11.6.  Doubled where the grid's y would pass 2^15.
+  int rows = 2;
+  while ((ny + rows * kWavesPerBlock - 1) / (rows * kWavesPerBlock) > (int64_t(1) << 15)) rows *= 2;
+  // Small results stay in the caches for the LCP that reads them next (both
+  // calls at 1021x1531, 3 isovalues: 20.1 us, 21.6 with non-temporal stores);
+  // large ones are streamed past them (4096^2: 165, 159).
+  const bool nt = ny * nx > 3 * (int64_t(1) << 20);
   // strips of 64 columns for 32-bit storage, of 62 for 16-bit (DPP halo)
   const int64_t strip = dt == PDIV_F32 ? kWave : kWave - 2;
   dim3 grid(static_cast<unsigned>((nx + strip - 1) / strip),
             static_cast<unsigned>((ny + rows * kWavesPerBlock - 1) / (rows * kWavesPerBlock)));
   const int iny = static_cast<int>(ny), inx = static_cast<int>(nx);
+#define PDIV_DIV(T, NT)                                                                         \
+  hipLaunchKernelGGL((divergence_kernel<T, NT>), grid, dim3(kBlock), 0, s,                      \
+                     static_cast<const T*>(mu), static_cast<const T*>(vu),                      \
+                     static_cast<const T*>(mv), static_cast<const T*>(vv), iny, inx, k, dmean,  \
+                     dvar, rows)
+#define PDIV_DIV2(T)     \
+  if (nt)                \
+    PDIV_DIV(T, true);   \
+  else                   \
+    PDIV_DIV(T, false)
   switch (dt) {
-    case PDIV_F32:
-      hipLaunchKernelGGL(divergence_kernel<float>, grid, dim3(kBlock), 0, s,
-                         static_cast<const float*>(mu), static_cast<const float*>(vu),
-                         static_cast<const float*>(mv), static_cast<const float*>(vv), iny, inx,
-                         k, dmean, dvar, rows);
-      break;
-    case PDIV_F16:
-      hipLaunchKernelGGL(divergence_kernel<__half>, grid, dim3(kBlock), 0, s,
-                         static_cast<const __half*>(mu), static_cast<const __half*>(vu),
-                         static_cast<const __half*>(mv), static_cast<const __half*>(vv), iny,
-                         inx, k, dmean, dvar, rows);
-      break;
-    case PDIV_BF16:
-      hipLaunchKernelGGL(divergence_kernel<bf16_t>, grid, dim3(kBlock), 0, s,
-                         static_cast<const bf16_t*>(mu), static_cast<const bf16_t*>(vu),
-                         static_cast<const bf16_t*>(mv), static_cast<const bf16_t*>(vv), iny,
-                         inx, k, dmean, dvar, rows);
-      break;
-    default:
-      return hipErrorInvalidValue;
+    case PDIV_F32: PDIV_DIV2(float); break;
+    case PDIV_F16: PDIV_DIV2(__half); break;
+    case PDIV_BF16: PDIV_DIV2(bf16_t); break;
+    default: return hipErrorInvalidValue;
   }
+#undef PDIV_DIV2
+#undef PDIV_DIV
   return hipGetLastError();
 }
 
