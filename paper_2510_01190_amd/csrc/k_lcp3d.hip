@@ -40,9 +40,18 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / 64;
 // z slices per divergence3d wave: each chunk re-reads W at its two ends, and
-// longer chunks mean fewer waves.  At 512^3 float32: 8, 12, 16, 32, 64
-// slices take 0.877, 0.852, 0.901, 0.962, 0.976 ms.
-constexpr int kZChunk = 12;
+// longer chunks mean fewer waves.  2 / 4 / 6 / 8 / 12 / 16 slices, us: float32
+// 100x130x150 14.4 / 12.7 / 13.0 / 13.9 / 14.4 / 13.9, 256x512x384 314 / 315 /
+// 321 / 318 / 328 / 323, 512^3 872 / 844 / 869 / 843 / 865 / 853; bfloat16
+// 180x200x220 50 / 45 / 47 / 48 / 48 / 51, 512^3 668 / 559 / 536 / 567 / 548 /
+// 620.
+int z_chunk3(pdiv_dtype dt, int64_t points) {
+  return dt != PDIV_F32 && points > (int64_t(1) << 23) ? 6 : 4;
+}
+// What the grid check counts (launches take more slices where those would not
+// fit).
+constexpr int kCheckedZChunk = 12;
+
 // Eq. 2-3 with the z term at one vertex; the neighbours are already clamped
 // at the boundary and the coefficients chosen (1/(2h) inside, 1/h on a
 // boundary plane).  Contraction is off so the rounding is fixed.
@@ -66,7 +75,7 @@ __device__ __forceinline__ DivGauss div_gauss3(float mu_xl, float mu_xr, float v
 }
 
 // Grid: blocks of 4 waves over (x block of 64 columns, 4 consecutive rows
-// y, a chunk of kZChunk slices z), x block fastest, in XCD-contiguous block
+// y, a chunk of z_chunk slices z), x block fastest, in XCD-contiguous block
 // order (blocks are dealt round-robin to the 8 XCDs; this gives each XCD a
 // contiguous run, so blocks that share neighbour rows share an L2).  A wave
 // walks z along its row: W's values at z-1, z, z+1 stay in a three-deep
@@ -74,21 +83,22 @@ __device__ __forceinline__ DivGauss div_gauss3(float mu_xl, float mu_xr, float v
 // V's rows y-1, y+1 are those of the block's other waves (found in cache).
 // Every vertex sees the same inputs and operations as a straight evaluation
 // of Eq. 2-3 with clamped neighbours.
-template <typename T>
+// NT: non-temporal stores.
+template <typename T, bool NT>
 __global__ __launch_bounds__(kBlock) void divergence3d_kernel(
     const T* __restrict__ mu, const T* __restrict__ vu, const T* __restrict__ mv,
     const T* __restrict__ vv, const T* __restrict__ mw, const T* __restrict__ vw, int nz, int ny,
     int nx, StencilCoef3 k, float* __restrict__ dmean, float* __restrict__ dvar, int n_xb,
-    int n_yq) {
+    int n_yq, int z_chunk) {
   const int nb = gridDim.x, xcd = blockIdx.x % 8, q8 = nb / 8, r8 = nb % 8;
   const int blk = xcd * q8 + min(xcd, r8) + blockIdx.x / 8;
   const int xb = blk % n_xb;
   const int rest = blk / n_xb;
   const int y = (rest % n_yq) * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int z0 = (rest / n_yq) * kZChunk;
+  const int z0 = (rest / n_yq) * z_chunk;
   const int x = xb * 64 + (threadIdx.x & 63);
   if (y >= ny || x >= nx) return;
-  const int z1 = min(z0 + kZChunk, nz);
+  const int z1 = min(z0 + z_chunk, nz);
   const Col c = make_col(uint32_t(x), nx, sizeof(T));
   const int yl = y > 0 ? y - 1 : 0, yr = y < ny - 1 ? y + 1 : ny - 1;
   const bool by = (y == 0) | (y == ny - 1);
@@ -125,8 +135,13 @@ __global__ __launch_bounds__(kBlock) void divergence3d_kernel(
                                   v_l.get(c.x), v_r.get(c.x), t_l.get(c.x), t_r.get(c.x), mzl,
                                   mzr, vzl, vzr, cxm, cxv, cym, cyv,
                                   bz ? k.czm_bd : k.czm_in, bz ? k.czv_bd : k.czv_in);
-    __builtin_nontemporal_store(g.mean, dmean + row + x);
-    __builtin_nontemporal_store(g.var, dvar + row + x);
+    if constexpr (NT) {
+      __builtin_nontemporal_store(g.mean, dmean + row + x);
+      __builtin_nontemporal_store(g.var, dvar + row + x);
+    } else {
+      dmean[row + x] = g.mean;
+      dvar[row + x] = g.var;
+    }
     wm_prev = wm_cur;
     wv_prev = wv_cur;
     wm_cur = wm_next;
@@ -573,9 +588,15 @@ int lcp3d_chunk(int left, bool fused) {
   return left >= 8 ? 8 : left >= 4 ? 4 : left;
 }
 
-int64_t divergence3d_blocks(int64_t nz, int64_t ny, int64_t nx) {
+namespace {
+int64_t divergence3d_blocks(int64_t nz, int64_t ny, int64_t nx, int z_chunk) {
   return ((nx + 63) / 64) * ((ny + kWavesPerBlock - 1) / kWavesPerBlock) *
-         ((nz + kZChunk - 1) / kZChunk);
+         ((nz + z_chunk - 1) / z_chunk);
+}
+}  // namespace
+
+int64_t divergence3d_blocks(int64_t nz, int64_t ny, int64_t nx) {
+  return divergence3d_blocks(nz, ny, nx, kCheckedZChunk);
 }
 
 hipError_t launch_divergence3d(const void* mu, const void* vu, const void* mv, const void* vv,
@@ -584,21 +605,38 @@ hipError_t launch_divergence3d(const void* mu, const void* vu, const void* mv, c
                                float* dvar, hipStream_t s) {
   const int n_xb = int((nx + 63) / 64);
   const int n_yq = int((ny + kWavesPerBlock - 1) / kWavesPerBlock);
-  const int64_t blocks = divergence3d_blocks(nz, ny, nx);
+  int z_chunk = z_chunk3(dt, nz * ny * nx);
+  int64_t blocks = divergence3d_blocks(nz, ny, nx, z_chunk);
+  if (!launch_fits(blocks, kBlock)) {
+    z_chunk = kCheckedZChunk;
+    blocks = divergence3d_blocks(nz, ny, nx, z_chunk);
+  }
+  // results of up to 8 M points stay in the caches for the LCP that reads
+  // them next (both calls at 180x200x220, 2 isovalues: 96.7 us, 101.4 with
+  // non-temporal stores), larger ones are streamed past them (256x512x384: 550,
+  // 533)
+  const bool nt = nz * ny * nx > (int64_t(1) << 23);
   if (!launch_fits(blocks, kBlock)) return hipErrorInvalidConfiguration;
   const dim3 grid{unsigned(blocks)}, block{unsigned(kBlock)};
   const int z = int(nz), y = int(ny), x = int(nx);
-#define PDIV_DIV3(T)                                                                         \
-  hipLaunchKernelGGL(divergence3d_kernel<T>, grid, block, 0, s, static_cast<const T*>(mu),   \
-                     static_cast<const T*>(vu), static_cast<const T*>(mv),                   \
-                     static_cast<const T*>(vv), static_cast<const T*>(mw),                   \
-                     static_cast<const T*>(vw), z, y, x, k, dmean, dvar, n_xb, n_yq)
+#define PDIV_DIV3_(T, NT)                                                                    \
+  hipLaunchKernelGGL((divergence3d_kernel<T, NT>), grid, block, 0, s,                        \
+                     static_cast<const T*>(mu), static_cast<const T*>(vu),                   \
+                     static_cast<const T*>(mv), static_cast<const T*>(vv),                   \
+                     static_cast<const T*>(mw), static_cast<const T*>(vw), z, y, x, k, dmean, \
+                     dvar, n_xb, n_yq, z_chunk)
+#define PDIV_DIV3(T)     \
+  if (nt)                \
+    PDIV_DIV3_(T, true); \
+  else                   \
+    PDIV_DIV3_(T, false)
   switch (dt) {
     case PDIV_F32: PDIV_DIV3(float); break;
     case PDIV_F16: PDIV_DIV3(__half); break;
     case PDIV_BF16: PDIV_DIV3(bf16_t); break;
     default: return hipErrorInvalidValue;
   }
+#undef PDIV_DIV3_
 #undef PDIV_DIV3
   return hipGetLastError();
 }
