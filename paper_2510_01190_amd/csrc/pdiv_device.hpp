@@ -288,6 +288,53 @@ __device__ __forceinline__ U4 philox4x32_10(U4 c, uint32_t k0, uint32_t k1) {
   return c;
 }
 
+// The same generator at counters (point, step, 0, 0), for many steps of one
+// point.  With the counter's last words zero, the first two rounds split into
+// words of the point alone (PhiloxPoint, computed once) and words of the step
+// alone (wave-uniform): 16 of 18 vector multiplications remain per step.
+struct PhiloxPoint {
+  uint32_t w1, x2, y2;
+};
+
+__device__ __forceinline__ PhiloxPoint philox_point(uint32_t point, uint32_t k0, uint32_t k1) {
+  constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u, W0 = 0x9E3779B9u;
+  const uint64_t p0 = static_cast<uint64_t>(M0) * point;
+  const uint64_t p1 = static_cast<uint64_t>(M1) * (static_cast<uint32_t>(p0 >> 32) ^ k1);
+  PhiloxPoint r;
+  r.w1 = static_cast<uint32_t>(p0);
+  r.x2 = static_cast<uint32_t>(p1 >> 32) ^ (k0 + W0);
+  r.y2 = static_cast<uint32_t>(p1);
+  return r;
+}
+
+__device__ __forceinline__ U4 philox4x32_10_step(const PhiloxPoint& pt, uint32_t step, uint32_t k0,
+                                                 uint32_t k1) {
+  constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;
+  constexpr uint32_t W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
+  const uint64_t s = static_cast<uint64_t>(M0) * (step ^ k0);
+  U4 c;
+  c.x = pt.x2;
+  c.y = pt.y2;
+  c.z = pt.w1 ^ (static_cast<uint32_t>(s >> 32) ^ (k1 + W1));
+  c.w = static_cast<uint32_t>(s);
+  k0 += 2u * W0;
+  k1 += 2u * W1;
+#pragma unroll
+  for (int r = 2; r < 10; ++r) {
+    const uint64_t a = static_cast<uint64_t>(M0) * c.x;
+    const uint64_t b = static_cast<uint64_t>(M1) * c.z;
+    U4 n;
+    n.x = xor3_uniform(static_cast<uint32_t>(b >> 32), c.y, k0);
+    n.y = static_cast<uint32_t>(b);
+    n.z = xor3_uniform(static_cast<uint32_t>(a >> 32), c.w, k1);
+    n.w = static_cast<uint32_t>(a);
+    c = n;
+    k0 += W0;
+    k1 += W1;
+  }
+  return c;
+}
+
 // Box-Muller (1958): u1 = (wa + 1) 2^-32 in (0, 1], u2 = wb 2^-32 in [0, 1);
 // r = sqrt(-2 ln u1); (r cos 2 pi u2, r sin 2 pi u2).  The hardware sine and
 // cosine take their argument in revolutions, so u2 is passed as is.  r is
