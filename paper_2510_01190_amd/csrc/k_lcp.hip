@@ -221,8 +221,9 @@ hipError_t launch_kc(const void* p0, const void* p1, const void* p2, const void*
   const bool unaligned = paired && !lines;  // fused only: default store policy
   const int cells = cells_per_wave(paired);
   const int n_strips = (nx - 1 + cells - 1) / cells;
-  const int band_rows =
-      shape.band_rows > 0 ? shape.band_rows : lcp_band_rows(n_strips, ny - 1, paired);
+  const int band_rows = shape.band_rows > 0
+                            ? shape.band_rows
+                            : lcp_band_rows(n_strips, ny - 1, paired, FUSED, KC);
   const int n_bands = (ny - 1 + band_rows - 1) / band_rows;
   const int64_t waves = static_cast<int64_t>(n_strips) * n_bands;
   if (!launch_fits((waves + kWavesPerBlock - 1) / kWavesPerBlock, kBlock))

@@ -44,6 +44,8 @@
 // No seam step.
 #pragma once
 
+#include <cstdint>
+
 #include "pdiv_device.hpp"
 #include "pdiv_internal.hpp"
 
@@ -726,24 +728,48 @@ inline bool use_paired_tile(bool fused, bool lines, int kc, int64_t cells) {
 // two input rows, so tall bands do less work; but a wave walks its band row
 // by row, so a grid of few tall bands leaves SIMDs idle while a few waves
 // walk (500x500, 1 isovalue, fused: 15.9 us with 32-row bands, 9.3 / 6.0 /
-// 4.3 / 3.6 / 3.4 us with 16 / 8 / 4 / 2 / 1; 721x1440, 8 isovalues: 45 /
-// 26 / 20 / 16.7 / 15.7 / 17.6 us with 32 ... 1).  The tallest band that still
-// gives about two rounds of the two or three waves per SIMD the tiles run at
-// (1024 SIMDs; just over one round, 5792^2 with 64 rows, is the worst);
-// bands of 4 and 2 rows do with fewer waves, as their redundant row costs
-// more.  The split tile gains nothing from bands over 8 rows at any
-// size (8192^2, 16 isovalues, two-step: 1.30 ms with 8 rows, 1.41 / 1.44 / 1.50
-// with 16 / 32 / 64); the paired one takes up to 64 (8192^2 fused, 16
-// isovalues: 1.106 ms, 1.125 / 1.174 / 1.176 with 32 / 16 / 8; 5792^2: 656,
+// 4.3 / 3.6 / 3.4 us with 16 / 8 / 4 / 2 / 1).
+//
+// Grids of less than eight 8-row bands per SIMD: the time goes with the rows
+// that the fullest of the 1024 SIMDs walks, a band's own redundant work at
+// half a row, n (b + 1/2) for n = ceil(waves / 1024).  1448x1448, 4 isovalues
+// into dense maps, 2 ... 10 rows: 18.1 17.3 18.1 16.7 15.7 17.0 18.0 15.5 16.2 us
+// (n = 9 6 5 4 3 3 3 2 2), 12 / 14 / 16: 17.8 / 19.8 / 21.5.  A SIMD's only wave
+// hides no latency (721x1440, 8 isovalues, 9 rows: 17.0 us, 15.2 with 3), and
+// with few isovalues two hide less than three (1000x1000, 2 isovalues, 4 rows:
+// 8.3 us, 7.8 with 2).  Against the tallest band that gives a number of waves
+// (6000, 3000 and 1500 for 8, 4 and 2 rows), over 208 sizes, counts and
+// layouts from 300x300 to 2047x3001 the times fall by 2.3% on average: 721x1440
+// 16.2 to 14.8 us at 8 isovalues and 29.6 to 25.8 at 16, 1448^2 17.1 to 15.6 at 4
+// and, on lines, 44.9 to 40.5 at 16, 2047x3001 on lines 47.7 to 44.4 at 4.  Taller
+// bands than 8 rows gain nothing where the stores are most of the work, the
+// two-step path and many isovalues on rows that start inside a line
+// (1500x4000, 16 isovalues into dense maps, 16 rows: 142.7 us, 137.5 with 8).
+//
+// Larger grids, whose SIMDs even out: the split tile gains nothing from more
+// than 8 rows at any size (8192^2, 16 isovalues, two-step: 1.30 ms with 8 rows,
+// 1.41 / 1.44 / 1.50 with 16 / 32 / 64); the paired one takes up to 64 (8192^2 fused,
+// 16 isovalues: 1.106 ms, 1.125 / 1.174 / 1.176 with 32 / 16 / 8; 5792^2: 656,
 // 601, 593, 608 us with 64 / 32 / 16 / 8; 4096^2 into dense maps 343, 334, 337,
 // 348 us).
-inline int lcp_band_rows(int64_t strips, int64_t rows, bool paired) {
+inline int lcp_band_rows(int64_t strips, int64_t rows, bool paired, bool fused, int kc) {
   auto waves = [&](int b) { return strips * ((rows + b - 1) / b); };
-  if (paired && waves(64) >= 8000) return 64;
-  if (paired && waves(32) >= 4000) return 32;
-  if (paired && waves(16) >= 6000) return 16;
-  if (waves(8) >= 6000) return 8;
-  return waves(4) >= 3000 ? 4 : waves(2) >= 1500 ? 2 : 1;
+  if (waves(8) >= 8000) {
+    if (paired && waves(64) >= 8000) return 64;
+    if (paired && waves(32) >= 4000) return 32;
+    if (paired && waves(16) >= 6000) return 16;
+    return 8;
+  }
+  constexpr int64_t kSimds = 1024;
+  const int tallest = fused && (paired || kc < 12) ? 16 : 8;
+  int64_t least = INT64_MAX;
+  int best = 1;
+  for (int b = 1; b <= tallest; ++b) {
+    const int64_t n = (waves(b) + kSimds - 1) / kSimds;
+    const int64_t cost = n * (2 * b + 1) * (n == 1 ? 40 : n == 2 && kc < 8 ? 23 : 20);
+    if (cost < least) least = cost, best = b;
+  }
+  return best;
 }
 
 // The tile of layout PAIRED.  STREAM: non-temporal stores (for rows that

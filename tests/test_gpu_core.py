@@ -568,6 +568,18 @@ def test_tile_choice_and_band_heights(shape, ks):
         assert err_report(host64(ref[:, :top]), want)["max_abs"] <= LCP_TOL
 
 
+@pytest.mark.parametrize("shape,ks", [((1025, 100), (1,)), ((1026, 100), (1,)), ((2050, 127), (8,)),
+                                      ((640, 2000), (4, 16)), ((1021, 1531), (2, 16)),
+                                      ((1448, 1448), (4, 16)), ((1200, 2400), (3, 12)),
+                                      ((2047, 3001), (4,)), ((2662, 3001), (1,)),
+                                      ((2675, 3001), (1,))])
+def test_band_heights_by_rounds_of_waves(shape, ks):
+    """Heights picked by the rows that the fullest SIMD walks: just under and
+    over one wave per SIMD, 3, 4, 5, 6, 7, 9, 12 and 16 rows, both sides of eight
+    8-row bands per SIMD."""
+    test_tile_choice_and_band_heights(shape, ks)
+
+
 @pytest.mark.parametrize("shape", [(2, 2), (67, 131), (1500, 1201)])
 def test_every_isovalue_count_in_one_launch(shape):
     """Counts between the kernel's slot counts (1, 2, 3, 4, 6, 8, 12, 16) leave
