@@ -316,8 +316,12 @@ __device__ __forceinline__ void load_levels(Row3<L, true>& r, const Rows3<true, 
 //     levels of their own), took 4 isovalues from 240 registers on line-
 //     aligned rows, 173 on others, to 161, three waves per SIMD instead of
 //     two.  256x512x384 float32 at 1 / 4 / 8 isovalues on line-aligned rows
-//     393 / 584 / 899 -> 357 / 555 / 846 us, bfloat16 319 / 547 / 920 -> 245 /
-//     463 / 780; 512^3 float32 1026 / 1505 / 2302 -> 966 / 1500 / 2190.
+//     393 / 584 / 899 -> 357 / 555 / 836 us, bfloat16 319 / 547 / 920 -> 245 /
+//     463 / 755; 512^3 float32 1026 / 1505 / 2302 -> 966 / 1500 / 2174.
+//     Where 61 cells make a ninth strip of what 63 made eight, 4 isovalues on
+//     dense rows lose 4% (300x400x500 638 -> 667); strips of 63, whose end lanes
+//     load their missing neighbours, win that back (623) but cost 173 registers
+//     and up to 6% everywhere else.
 // With 8 corners the float32 combination can land an ulp outside [0, 1]
 // where the probability is 0 or 1; the exact value is inside, so clamping
 // only removes error.  The IEEE 754-2019 maximum and minimum (v_maximum3_f32,
@@ -566,7 +570,7 @@ hipError_t launch_lcp3d_kc(const Planes6& src, int nz, int ny, int nx, const Ste
 // where those would not fit).
 constexpr int kCheckedBandRows = 16;
 int64_t lcp3d_blocks(int64_t nz, int64_t ny, int64_t nx, int kc) {
-  const int lz = kc <= 4 ? 4 : 2;  // the fewest layers any launch uses
+  const int lz = kc <= 4 ? 4 : 2;  // launches above 4 isovalues take 3 or 4
   const int64_t waves = ((nz - 1 + lz - 1) / lz) * ((nx - 1 + 62) / 63) *
                         ((ny - 1 + kCheckedBandRows - 1) / kCheckedBandRows);
   return (waves + kWavesPerBlock - 1) / kWavesPerBlock;
@@ -581,7 +585,7 @@ bool lcp3d_slice_fits(int64_t ny, int64_t nx, size_t elem_bytes) {
 // the tails of the extra shared z levels cost more than reading the divergence
 // volumes twice).  Fused (each launch reads six volumes): 16, 8 and any count
 // below.  256x512x384, us, against chunks of powers of two: two-step 3
-// isovalues 275 / 339, 7 577 / 654; fused 3 461 / 752, 5 683 / 858, 6 716 /
+// isovalues 275 / 339, 7 577 / 654; fused 3 461 / 752, 5 668 / 858, 6 700 /
 // 957, 7 870 / 1288, 14 1584 / 1815.
 int lcp3d_chunk(int left, bool fused) {
   if (fused) return left >= 16 ? 16 : left >= 8 ? 8 : left;
@@ -650,21 +654,26 @@ hipError_t launch_lcp3d_kcs(const Planes6& src, int z, int y, int x, const Stenc
 #define PDIV_L3(K, LZ, ALL)                                                                   \
   return launch_lcp3d_kc<K, LZ, FUSED, LINES, ALL, T>(src, z, y, x, k, iso, kc, out, pitch, \
                                                       plane, s)
-  // two-step: 4 layers; fused: the moment rows' registers leave room for 2
-  // above 4 isovalues.  lcp3d_chunk gives only these counts.
+  // two-step: 4 layers; fused: the moment rows' registers leave room for 3
+  // above 4 isovalues (3 against 2 layers re-evaluate 4 levels' tails for 3
+  // cells, not 3 for 2, at the same waves per SIMD: 148 ... 167 registers to 8
+  // isovalues, 229 at 16; float32 on line-aligned rows, 16 isovalues, 512^3
+  // 3855 -> 3711 us, 256x512x384 1516 -> 1452, 300x400x500 1887 -> 1690; 8
+  // isovalues 2186 -> 2174, 863 -> 836, 993 -> 972; bfloat16 at 8 1995 -> 1886,
+  // 783 -> 755, 920 -> 871).  lcp3d_chunk gives only these counts.
   switch (kc) {
     case 1: PDIV_L3(1, 4, true);
     case 2: PDIV_L3(2, 4, true);
     case 3: PDIV_L3(3, 4, true);
     case 4: PDIV_L3(4, 4, true);
-    case 8: PDIV_L3(8, FUSED ? 2 : 4, true);
+    case 8: PDIV_L3(8, FUSED ? 3 : 4, true);
   }
   if constexpr (FUSED) {
     switch (kc) {
-      case 5: PDIV_L3(6, 2, false);
-      case 6: PDIV_L3(6, 2, true);
-      case 7: PDIV_L3(8, 2, false);
-      case 16: PDIV_L3(16, 2, true);
+      case 5: PDIV_L3(6, 3, false);
+      case 6: PDIV_L3(6, 3, true);
+      case 7: PDIV_L3(8, 3, false);
+      case 16: PDIV_L3(16, 3, true);
     }
   }
 #undef PDIV_L3

@@ -296,3 +296,21 @@ def test_every_isovalue_count_3d(shape):
             view, buf = _padded(k, shape, pitch=pitch, gap=64)
             P.lcp_3d_from_moments(*ts, iso[:k], out=view)
             assert torch.equal(view, ref[:k]) and _padding_untouched(view, buf), (k, pitch)
+
+
+@pytest.mark.parametrize("nz", [3, 4, 5, 7, 8])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_three_layer_groups_3d(nz, dt):
+    """Fused launches above 4 isovalues walk three cell layers per wave: the
+    last group of one, two and three layers, one group and several, bitwise
+    the two-step maps, nothing written past the last layer."""
+    shape = (nz, 20, 65)
+    rng = np.random.default_rng(nz)
+    ts = [dev(rng.normal(0, 0.3, shape) if q % 2 == 0 else rng.uniform(0.02, 0.2, shape), dt)
+          for q in range(6)]
+    div = P.divergence_gaussian_3d(*ts)
+    for k in (5, 6, 7, 8, 16):
+        iso = np.linspace(-0.4, 0.4, k).astype(np.float32)
+        view, buf = _padded(k, shape, gap=32)
+        P.lcp_3d_from_moments(*ts, iso, out=view)
+        assert torch.equal(view, P.lcp_3d(*div, iso)) and _padding_untouched(view, buf), k
