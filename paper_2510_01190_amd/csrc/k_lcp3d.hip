@@ -7,7 +7,7 @@
 //   divergence3d_kernel  Eq. 2-3 with the z term, one vertex per lane; HBM
 //                        bound: 6 planes read, 2 written.
 //   lcp3d_kernel         8-corner LCP from the divergence Gaussians.  A wave
-//                        holds a strip of 64 vertex columns (63 cells) and LZ
+//                        holds a strip of 64 vertex columns (61 to 64 cells) and LZ
 //                        consecutive cell layers k0..k0+LZ-1 and walks a band
 //                        of rows along y.  At each row it evaluates the
 //                        corner tails once for the LZ+1 z-levels it holds,
@@ -532,9 +532,12 @@ __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int 
 // 2 / 4 / 8 / 16 / 32 rows: 33 / 28 / 30 / 38 / 46 / 87; two-step 25 / 20 / 22 /
 // 28 / 35 / 67; 48^3 7 / 9 / 14 / 23 / 43 / 81; 180x200x220 123 / 107 / 98 / 100
 // / 113 / 140; 256x512x384 578 / 558 / 564 / 586 with 4 ... 32; 512^3 1573 / 1487
-// / 1500 / 1563).
-int band_rows3(int64_t columns, int64_t rows) {
+// / 1500 / 1563).  The line-aligned tile at 8 isovalues, most work per row, takes
+// 32 rows on large volumes (512^3, 16 isovalues in two launches 2734 us with 16,
+// 2687 with 32; 256x512x384, 8: 522, 534).
+int band_rows3(int64_t columns, int64_t rows, bool lines, int kc) {
   auto waves = [&](int b) { return columns * ((rows + b - 1) / b); };
+  if (lines && kc == 8 && waves(32) >= 12000) return 32;
   if (waves(16) >= 12000) return 16;
   if (waves(8) >= 8000) return 8;
   return waves(4) >= 3000 ? 4 : waves(2) >= 1500 ? 2 : 1;
@@ -547,7 +550,7 @@ hipError_t launch_lcp3d_kc(const Planes6& src, int nz, int ny, int nx, const Ste
   constexpr int kW = strip_cells3<FUSED, LINES>();
   const int n_groups = (nz - 1 + LZ - 1) / LZ;
   const int n_strips = (nx - 1 + kW - 1) / kW;
-  int band_rows = band_rows3(int64_t(n_groups) * n_strips, ny - 1);
+  int band_rows = band_rows3(int64_t(n_groups) * n_strips, ny - 1, LINES, KC);
   int n_bands = 0;
   int64_t blocks = 0;
   do {  // taller bands where a launch would not hold the blocks
