@@ -323,7 +323,7 @@ pdiv_status pdiv_lcp_3d_from_moments(const void* mean_u, const void* var_u, cons
 
 /* ------------------------------------------------------------------------
  * Batched launch: many independent fields of uneven size, each with its own
- * isovalues, in ONE persistent kernel (fused Eq. 2-3 + closed-form LCP).
+ * isovalues, in ONE kernel launch (fused Eq. 2-3 + closed-form LCP).
  * The paper's GPU run is dominated by launch overhead on a small field
  * (Section 4, Red Sea); a batch amortises one launch over all fields.
  * ------------------------------------------------------------------------ */

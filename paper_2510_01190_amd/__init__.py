@@ -474,7 +474,7 @@ def mc_sample_field(mean_u, var_u, mean_v, var_v, sample: int, seed: int):
 
 
 class Batch:
-    """Many fields of uneven size in one persistent launch (optionally graph-replayed).
+    """Many fields of uneven size in one launch (optionally graph-replayed).
 
     fields: sequence of dicts with mean_u, var_u, mean_v, var_v (device planes of one
     dtype), isovalues (device float32 tensor, 1..16 values), dx, dy, and optionally

@@ -1,5 +1,5 @@
 // Shared by the batched launch and the server: the per-field descriptor the
-// persistent kernel reads, and the host helpers that build and launch it.
+// batch kernel reads, and the host helpers that build and launch it.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -11,7 +11,7 @@
 
 namespace pdiv {
 
-// One field of a batch, as the persistent kernel reads it (scalar loads).
+// One field of a batch, as the batch kernel reads it (scalar loads).
 // Fused batches point p0..p3 at the moment planes (mean U, var U, mean V,
 // var V); two-step batches point p0, p1 at the divergence mean and variance.
 struct alignas(16) BatchField {

@@ -1,6 +1,6 @@
 // Column-walking tiles of the closed-form LCP (Eq. 2-3 and the level-crossing
 // probability of Section 3.1), shared by the single-field kernel and the
-// batched persistent kernel so that both give bitwise the same maps.  A wave
+// batch kernel so that both give bitwise the same maps.  A wave
 // walks a strip of cells down a band of cell rows, one vertex row at a time:
 // for each isovalue it evaluates each corner's tail once per row, pairs it
 // with the previous row's (vertical pairs, kept in registers) and forms the

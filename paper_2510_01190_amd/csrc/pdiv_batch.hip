@@ -1,4 +1,4 @@
-// Batched persistent launch: many independent fields of uneven size, each with
+// Batched launch: many independent fields of uneven size, each with
 // its own isovalues, in one kernel launch.  The paper's GPU timing is
 // dominated by launch overhead on a small field (Section 4, Red Sea); a batch
 // pays one launch for all of them and keeps every CU busy across field
