@@ -38,6 +38,7 @@
 #include <algorithm>
 
 #include "mc_rank.hpp"
+#include "mc_split.hpp"
 #include "pdiv_device.hpp"
 #include "pdiv_internal.hpp"
 
@@ -175,7 +176,7 @@ __global__ __launch_bounds__(kBlock) void mc_kernel(const T* __restrict__ mu,
 
   // this block's run of sample pairs
   const int first = int(blockIdx.z) * per_split;
-  const int last = min(first + per_split, (n_samples + 1) >> 1);
+  const int last = min(first + per_split, mc_pairs(n_samples));
   for (int pr = first; pr < last; ++pr) {
     // 1. draw both samples of the pair at every point of tile + halo
 #pragma unroll
@@ -379,7 +380,7 @@ __global__ __launch_bounds__(kBlock) void mc_vertex_kernel(const T* __restrict__
 
   // this block's run of sample groups
   const int first = int(blockIdx.z) * per_split;
-  const int last = min(first + per_split, (n_samples + 3) >> 2);
+  const int last = min(first + per_split, mc_groups(n_samples));
   for (int gr = first; gr < last; ++gr) {
 #pragma unroll
     for (int m = 0; m < VPT; ++m) {
@@ -506,44 +507,12 @@ __global__ __launch_bounds__(kBlock) void mc_sample_kernel(const T* __restrict__
   vs[p] = draw(ld(mv, p), __fsqrt_rn(ld(vv, p)), z.y);
 }
 
-// How the samples of a launch are split over blocks.  A block walks its
-// tile's sample steps (pairs, or groups of four) one after another, so a grid
-// of few tiles leaves most of the chip idle, and one of just over a multiple
-// of the resident blocks runs a nearly empty last round.  `splits` blocks per
-// tile share the steps; kSlots blocks run at once (4 per CU on 256 CUs) and a
-// block costs kSetup steps to start and finish, so a launch takes about
-// ceil(tiles * splits / kSlots) * (per_split + kSetup) steps.  Splitting adds
-// two small launches and the counters' atomics, so it has to promise a tenth.
-// Measured, one block per tile against split: 128x128, 1 isovalue, 2000
-// samples (16 tiles) 2215 against 71 us; 721x1440, 8 isovalues, 1000 samples
-// (1035 tiles, 11 past a full round) 2513 against 2103 us.
-struct McSplit {
-  int splits, per_split;
-};
-
-McSplit mc_split(int64_t tiles, int steps) {
-  constexpr int64_t kSlots = 1024, kSetup = 4, kMaxSplits = 256;
-  McSplit best{1, steps};
-  const double whole = double((tiles + kSlots - 1) / kSlots) * double(steps + kSetup);
-  double least = 0.9 * whole - 4.0;
-  for (int64_t z = 2; z <= kMaxSplits && z * kSetup <= steps; ++z) {
-    const int per = int((steps + z - 1) / z);
-    const int64_t used = (steps + per - 1) / per;  // splits that have work
-    const double cost = double((tiles * used + kSlots - 1) / kSlots) * double(per + kSetup);
-    if (cost < least) {
-      least = cost;
-      best = {int(used), per};
-    }
-  }
-  return best;
-}
-
 template <int KC, typename T>
 hipError_t launch_kc(const void* mu, const void* vu, const void* mv, const void* vv, int ny,
                      int nx, const StencilCoef& k, const IsoChunk& iso, int kc, int n_samples,
                      uint64_t seed, bool vertex, float* out, hipStream_t s) {
   const int64_t plane = static_cast<int64_t>(ny - 1) * (nx - 1);
-  const int steps = vertex ? (n_samples + 3) / 4 : (n_samples + 1) / 2;
+  const int steps = vertex ? mc_groups(n_samples) : mc_pairs(n_samples);
   const McSplit sp = mc_split(mc_tiles_x(nx) * mc_tiles_y(ny), steps);
   const dim3 grid(static_cast<unsigned>(mc_tiles_x(nx)), static_cast<unsigned>(mc_tiles_y(ny)),
                   static_cast<unsigned>(sp.splits));

@@ -1,0 +1,47 @@
+// Host check of the Monte Carlo launch's sample arithmetic
+// (csrc/mc_split.hpp, the header the library compiles), up to the largest
+// sample count a call accepts (2^31 - 1): every sample has its step, no step
+// is empty, and a split's runs cover the steps once, in int arithmetic that
+// stays in range (the kernel forms a run's end as first + per_split).
+// Built with g++ under ASan/UBSan.
+#include <cstdio>
+#include <initializer_list>
+
+#include "../../paper_2510_01190_amd/csrc/mc_split.hpp"
+
+namespace {
+
+int failures = 0;
+
+void check(bool ok, const char* what, long long a, long long b) {
+  if (!ok) {
+    if (failures < 20) std::printf("FAIL %s (%lld, %lld)\n", what, a, b);
+    ++failures;
+  }
+}
+
+void check_samples(int n) {
+  for (int per : {2, 4}) {
+    const int64_t steps = per == 2 ? pdiv::mc_pairs(n) : pdiv::mc_groups(n);
+    check(steps * per >= n && (steps - 1) * per < n, "steps", n, per);
+    for (int64_t tiles : {1LL, 2LL, 16LL, 169LL, 1023LL, 1035LL, 5000LL, 1LL << 26}) {
+      const pdiv::McSplit s = pdiv::mc_split(tiles, int(steps));
+      check(s.splits >= 1 && s.splits <= 256 && s.per_split >= 1, "split range", tiles, n);
+      check(int64_t(s.splits) * s.per_split >= steps, "steps covered", tiles, n);
+      check(int64_t(s.splits - 1) * s.per_split < steps, "no empty run", tiles, n);
+      const int last_first = (s.splits - 1) * s.per_split;  // as the last block forms it
+      const int end = last_first + s.per_split;
+      check(end >= last_first, "run end", tiles, n);
+    }
+  }
+}
+
+}  // namespace
+
+int main() {
+  for (int n = 1; n <= 3000; ++n) check_samples(n);
+  for (int n : {65535, 65536, 1000003, 1 << 30, (1 << 30) + 1}) check_samples(n);
+  for (int d = 0; d < 9; ++d) check_samples(0x7fffffff - d);
+  if (failures == 0) std::printf("ALL PASS\n");
+  return failures != 0;
+}

@@ -57,3 +57,27 @@ def test_monte_carlo_rank_table(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300, env=env)
     assert r.returncode == 0, (r.stdout[-3000:], r.stderr[-3000:])
     assert "ALL PASS" in r.stdout
+
+
+def _run_host_check(name, tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    exe = str(tmp_path / name)
+    src = os.path.join(HERE, "host_checks", name + ".cpp")
+    cmd = [gxx, "-std=c++17", "-O1", "-g", "-Wall", "-Wextra", "-Werror",
+           "-fsanitize=address,undefined", "-fno-sanitize-recover=all", src, "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-3000:]
+    env = dict(os.environ)
+    env.pop("LD_PRELOAD", None)
+    env["ASAN_OPTIONS"] = "detect_leaks=1:abort_on_error=1"
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300, env=env)
+    assert r.returncode == 0, (r.stdout[-3000:], r.stderr[-3000:])
+    assert "ALL PASS" in r.stdout
+
+
+def test_monte_carlo_sample_steps_and_splits(tmp_path):
+    """The Monte Carlo launch's step counts and splits (csrc/mc_split.hpp) up
+    to the largest sample count a call accepts."""
+    _run_host_check("mc_split_test", tmp_path)
