@@ -4,10 +4,11 @@
 // Layout: member m of a component is a plane of n_points values starting at
 // element m*stride.  The fit is pointwise, so the grid is treated as a flat
 // array: thread t owns VEC consecutive points, has UNROLL members' loads in
-// flight (VEC 4: two; four ran 69.4 against 67.8 us at 721x1440x50, 6.4 TB/s)
-// and walks the members with a
-// float32 Welford update (mean += d/n, M2 += d (x - mean)), which needs no
-// second pass and keeps its accuracy when |mean| >> sigma.
+// flight (fit_form in launch_rules.hpp; 721x1440x50 streams at 6.4 TB/s) and
+// walks the members with a float32 Welford update (mean += d/n, M2 += d (x -
+// mean)), which needs no second pass and keeps its accuracy when |mean| >>
+// sigma.
+#include "launch_rules.hpp"
 #include "pdiv_device.hpp"
 #include "pdiv_internal.hpp"
 
@@ -65,9 +66,10 @@ __global__ __launch_bounds__(256) void moments_kernel(const Tin* __restrict__ u,
 
   int m = 0;
   if constexpr (VEC == 1) {
-    // UNROLL members' loads are in flight at once; the last round repeats the
-    // last member's load and does not fold it in again, so the remainder is
-    // one round too, not one per member
+    // UNROLL members' loads are in flight at once; the remainder is one round
+    // too, of 2, 4 or UNROLL loads, those past the last member repeating its
+    // load and not folded in (a full round whatever the remainder ran 2.8
+    // against 2.4 us at 501x499x2, 3.0 / 2.8 at 101x77x25)
     float xu[UNROLL], xv[UNROLL];
     auto load = [&](int r, int member) {
       const int64_t row = static_cast<int64_t>(member) * stride;
@@ -89,14 +91,21 @@ __global__ __launch_bounds__(256) void moments_kernel(const Tin* __restrict__ u,
 #pragma unroll
       for (int r = 0; r < UNROLL; ++r) fold(r);
     }
-    if (m < m_members) {
+    auto tail = [&](auto count) {
 #pragma unroll
-      for (int r = 0; r < UNROLL; ++r) load(r, min(m + r, m_members - 1));
+      for (int r = 0; r < count.value; ++r) load(r, min(m + r, m_members - 1));
 #pragma unroll
-      for (int r = 0; r < UNROLL; ++r)
+      for (int r = 0; r < count.value; ++r)
         if (m + r < m_members) fold(r);
-      m = m_members;
-    }
+    };
+    const int rest = m_members - m;
+    if (rest > 4)
+      tail(std::integral_constant<int, UNROLL>{});
+    else if (rest > 2)
+      tail(std::integral_constant<int, 4>{});
+    else if (rest > 0)
+      tail(std::integral_constant<int, 2>{});
+    m = m_members;
   } else if (full) {
     for (; m + UNROLL <= m_members; m += UNROLL) {
       float xu[UNROLL][VEC], xv[UNROLL][VEC];
@@ -152,35 +161,28 @@ hipError_t launch_typed(const void* u, const void* v, int64_t m, int64_t n, int6
                         int ddof, void* mu, void* vu, void* mv, void* vv, hipStream_t s) {
   const float inv_dof = static_cast<float>(1.0 / static_cast<double>(m - ddof));
   const size_t align = sizeof(Tin) * 4;
-  // Four points a thread (16-byte loads of float32) for long streams over
-  // grids that still fill the chip; a point a thread, eight members in flight,
-  // everywhere else: its four times as many waves hide the loads of small
-  // grids and short ensembles.  One point against four, us: 68x68x15 3.3 / 5.8,
-  // 256x256x30 6.0 / 12.3, 500x500x20 9.5 / 11.8, 500x500x50 20.3 / 25.3,
-  // 300x2000x17 16.6 / 19.6, 2000x2000x10 72.6 / 73.9 (bfloat16 44 / 49), but
-  // 721x1440x50 84 / 68 (bfloat16 47.5 / 41.3), 2000x2000x25 171 / 163.
-  // (A grid past one launch of single points takes four, too.)
-  const bool long_stream = n >= (int64_t(1) << 19) && m >= 24;
-  const bool vec4 = (long_stream || !launch_fits((n + 255) / 256, 256)) && (stride % 4 == 0) &&
-                    (reinterpret_cast<uintptr_t>(u) % align == 0) &&
-                    (reinterpret_cast<uintptr_t>(v) % align == 0);
+  // The form by the rule, as far as the members' alignment allows loads of
+  // four (a grid past one launch of single points takes four, too).
+  FitForm form = fit_form(int(sizeof(Tin)), int(sizeof(Tout)), n, m);
   constexpr int kBlock = 256;
-  if (vec4) {
-    const int64_t threads = (n + 3) / 4;
-    if (!launch_fits((threads + kBlock - 1) / kBlock, kBlock)) return hipErrorInvalidConfiguration;
-    dim3 grid(static_cast<unsigned>((threads + kBlock - 1) / kBlock));
-    hipLaunchKernelGGL((moments_kernel<Tin, Tout, 4, 2>), grid, dim3(kBlock), 0, s,
-                       static_cast<const Tin*>(u), static_cast<const Tin*>(v),
-                       static_cast<int>(m), n, stride, inv_dof, static_cast<Tout*>(mu),
-                       static_cast<Tout*>(vu), static_cast<Tout*>(mv), static_cast<Tout*>(vv));
-  } else {
-    if (!launch_fits((n + kBlock - 1) / kBlock, kBlock)) return hipErrorInvalidConfiguration;
-    dim3 grid(static_cast<unsigned>((n + kBlock - 1) / kBlock));
-    hipLaunchKernelGGL((moments_kernel<Tin, Tout, 1, 8>), grid, dim3(kBlock), 0, s,
-                       static_cast<const Tin*>(u), static_cast<const Tin*>(v),
-                       static_cast<int>(m), n, stride, inv_dof, static_cast<Tout*>(mu),
-                       static_cast<Tout*>(vu), static_cast<Tout*>(mv), static_cast<Tout*>(vv));
+  if (!launch_fits((n + kBlock - 1) / kBlock, kBlock)) form = FitForm::kFour2;
+  if (stride % 4 != 0 || reinterpret_cast<uintptr_t>(u) % align != 0 ||
+      reinterpret_cast<uintptr_t>(v) % align != 0)
+    form = FitForm::kOne8;
+  const int64_t threads = form == FitForm::kOne8 ? n : (n + 3) / 4;
+  if (!launch_fits((threads + kBlock - 1) / kBlock, kBlock)) return hipErrorInvalidConfiguration;
+  const dim3 grid(static_cast<unsigned>((threads + kBlock - 1) / kBlock));
+#define PDIV_FIT(VEC, UNROLL)                                                                   \
+  hipLaunchKernelGGL((moments_kernel<Tin, Tout, VEC, UNROLL>), grid, dim3(kBlock), 0, s,        \
+                     static_cast<const Tin*>(u), static_cast<const Tin*>(v),                    \
+                     static_cast<int>(m), n, stride, inv_dof, static_cast<Tout*>(mu),           \
+                     static_cast<Tout*>(vu), static_cast<Tout*>(mv), static_cast<Tout*>(vv))
+  switch (form) {
+    case FitForm::kOne8: PDIV_FIT(1, 8); break;
+    case FitForm::kFour2: PDIV_FIT(4, 2); break;
+    case FitForm::kFour4: PDIV_FIT(4, 4); break;
   }
+#undef PDIV_FIT
   return hipGetLastError();
 }
 

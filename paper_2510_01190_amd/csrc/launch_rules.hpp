@@ -1,0 +1,52 @@
+// Rules that choose a kernel's form or launch shape by sizes and types: plain
+// C++, so that a host test holds each rule against the times it was drawn
+// from.  Times are of gfx950, three sets of buffers in turn, kernels alone.
+#pragma once
+
+#include <cstdint>
+
+namespace pdiv {
+
+// The ensemble fit's form: points a thread and members in flight.
+//   kOne8   a point, eight members: four times as many waves hide the loads
+//           of small grids and short ensembles;
+//   kFour2  four points (16-byte loads of float32), two members;
+//   kFour4  four points, four members: a wave hides more by itself, at half
+//           the waves, and members past a multiple of four are walked one at a
+//           time.
+// The forms of four take over where the members outgrow the caches: two
+// components of n points and m members from about 88 MiB.  kOne8 / kFour2 /
+// kFour4, us: float32 250k points x50 19.8 / 21.3 / 23.2, 340k x32 16.0 / 16.9 /
+// 18.2, 500k x22 16.8 / 16.3 / 18.6, x28 23.8 / 19.8 / 20.6, 1000x1000 x12 22.7 /
+// 22.8 / 22.6, x22 38.1 / 34.3 / 34.2, 1448x1448 x10 39.1 / 38.4 / 40.2, x18 65.6 /
+// 60.5 / 60.2; 16-bit 760k x25 17.6 / 19.6 / 18.8, x35 25.7 / 23.8 / 24.3, 1200x1000
+// x18 23.6 / 24.6 / 24.1, x28 34.3 / 31.7 / 32.4.  Between kFour2 and kFour4 the grid
+// decides: float32 1.2 M points x20 40.4 / 39.3, 2.8 M x15 69.1 / 78.1; 16-bit 1.45 M
+// x24 35.7 / 33.6, 2000x2000 x18 68.0 / 72.2.
+enum class FitForm { kOne8, kFour2, kFour4 };
+
+constexpr FitForm fit_form(int in_bytes, int out_bytes, int64_t n, int64_t m) {
+  constexpr int64_t kMi = int64_t(1) << 20;
+  const int64_t stream = 2 * in_bytes * m * n;
+  if (in_bytes == 4) {
+    // (16-bit results, of which a wave of single points stores 128 bytes a
+    // plane: 2.8 M points x10 47.5 us, 44 in fours)
+    const int least = out_bytes == 2 && n >= 7 * kMi / 5 ? 10 : 12;
+    if (n < 3 * kMi / 10 || m < least || stream < 88 * kMi) return FitForm::kOne8;
+    return n >= kMi && n < 9 * kMi / 4 ? FitForm::kFour4 : FitForm::kFour2;
+  }
+  // 16-bit to 16-bit: short streams and the stores decide earlier (400k points
+  // x20 9.0 us in fours, 10.2 by single points; 2.8 M x13 33, 38)
+  if (out_bytes == 2 && ((n >= 3 * kMi / 8 && n < 4 * kMi / 5 && m >= 12) ||
+                         (n >= 19 * kMi / 10 && m >= 10)))
+    return FitForm::kFour4;
+  // 16-bit to float32 on less than half a million points (500k x20 10.7 / 12.7 /
+  // 10.1, x40 18.3 / 19.4 / 15.8)
+  if (n < kMi / 2)
+    return n >= 3 * kMi / 8 && ((m % 4 == 0 && m >= 20) || m >= 40) ? FitForm::kFour4
+                                                                    : FitForm::kOne8;
+  if (m < 17 || stream < 88 * kMi) return FitForm::kOne8;
+  return n >= 19 * kMi / 20 && n < 3 * kMi ? FitForm::kFour4 : FitForm::kFour2;
+}
+
+}  // namespace pdiv

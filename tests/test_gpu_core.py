@@ -364,6 +364,42 @@ def test_moments_members_in_flight(m, n, stride, dt):
         assert np.all(np.abs(var[:n] - x.var(0)) <= (tr + 2 * U32) * x.var(0) + 1e-30)
 
 
+@pytest.mark.parametrize("n,m,dt,out", [(1000003, 22, "f32", "f32"), (1048576, 23, "f32", "f32"),
+                                        (2359296, 13, "f32", "bf16"), (440000, 41, "f16", "f32"),
+                                        (500000, 29, "bf16", "bf16"), (1100000, 25, "bf16", "f32"),
+                                        (2000000, 11, "f16", "f16"), (3200000, 18, "bf16", "f32"),
+                                        (5001, 3, "f32", "f32"), (5001, 13, "f16", "f32"),
+                                        (5001, 10, "f32", "bf16")])
+def test_fit_forms_agree(n, m, dt, out):
+    """Every form of the fit (a point or four a thread, two, four or eight
+    members in flight, remainders of 1 to 7 members) folds a point's members in
+    the same order: members that start off a four-element boundary, which take
+    single points, give bitwise the maps of aligned ones, whose form goes by
+    their size (the fit itself is held against the oracle above)."""
+    import ctypes
+    from gpu_util import TORCH_DT
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + m)
+    stride = (n + 7) // 4 * 4
+    code = {"f32": 0, "f16": 1, "bf16": 2}
+    fits = []
+    for shift in (0, 1):
+        g.manual_seed(n + m)
+        bufs = [torch.empty(m * stride + 4, dtype=TORCH_DT[dt], device="cuda") for _ in "uv"]
+        for b in bufs:
+            x = (torch.randn(m, n, generator=g, device="cuda") + 3.0).to(TORCH_DT[dt])
+            b[shift:shift + m * stride].view(m, stride)[:, :n] = x
+        outs = [torch.empty(n, device="cuda", dtype=TORCH_DT[out]) for _ in range(4)]
+        st = P.lib().pdiv_moments(
+            *[ctypes.c_void_p(b.data_ptr() + shift * b.element_size()) for b in bufs], code[dt], m,
+            1, n, stride, 1, *[ctypes.c_void_p(o.data_ptr()) for o in outs], code[out],
+            ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert st == 0
+        fits.append(outs)
+    for a, b in zip(*fits):
+        assert torch.equal(a, b)
+
+
 def test_pipeline_fit_divergence_lcp():
     """Ensemble -> moments -> fused LCP against the oracle fed with the members."""
     m, ny, nx = 20, 100, 140

@@ -81,3 +81,9 @@ def test_monte_carlo_sample_steps_and_splits(tmp_path):
     """The Monte Carlo launch's step counts and splits (csrc/mc_split.hpp) up
     to the largest sample count a call accepts."""
     _run_host_check("mc_split_test", tmp_path)
+
+
+def test_launch_rules_hold_against_measured_times(tmp_path):
+    """The rules that choose forms and launch shapes by size and type
+    (csrc/launch_rules.hpp) at the points they were measured at."""
+    _run_host_check("launch_rules_test", tmp_path)
