@@ -19,10 +19,14 @@
 // 4-row tile walking all members 0.120 ms; four waves per 4-row tile
 // 0.105 ms; per 8-row tile (two halo rows per eight output rows, not per
 // four) 0.099 ms; per 16-row tile 0.107 ms (254 registers); eight waves per
-// 8-row tile 0.101 ms.  The next member's rows are loaded while the current
-// one is folded in (each wave's run is a chain of dependent member loads):
-// 500x500x20 16.5 -> 15.4 us, 721x1440x50 110.7 -> 105 us (three sets of
-// members in turn, so none stays in the caches).
+// 8-row tile 0.101 ms.  In 4-row tiles the next member's rows
+// are loaded while the current one is folded in (each wave's run is a chain of
+// dependent member loads; 500x500x20 16.5 -> 13.7 us with the shorter band).
+// In 8-row tiles, whose 20 loads a member are in flight together anyway, that
+// gains nothing and the run's last member, loaded again, costs: float32 /
+// bfloat16 721x1440x24 55.7 / 43.2 us ahead, 54.3 / 42.3 without, 2000x2000x5 60.4 /
+// 56.3, 60.1 / 54.2, 721x1440x50 106.2 / 79.0, 105.1 / 80.3 (three sets of members
+// in turn, so none stays in the caches).
 #include <hip/hip_runtime.h>
 
 #include "pdiv_device.hpp"
@@ -129,8 +133,16 @@ __global__ __launch_bounds__(kBlock) void speed_gradient_moments_kernel(
   };
   const int m_lo = member_run_start(w, m_members);
   const int m_hi = member_run_start(w + 1, m_members);
-  // the next member's rows are loaded while the current one is folded in
-  if (m_lo < m_hi) {
+  if constexpr (BAND >= 8) {
+    for (int m = m_lo; m < m_hi; ++m) {
+      float a[BAND + 2], b[BAND + 2], s[BAND + 2];
+      load(m, a, b);
+      speeds(a, b, s);
+      update(m - m_lo, s);
+    }
+  } else if (m_lo < m_hi) {
+    // the next member's rows are loaded while the current one is folded in
+    // (past the run's end its last member again)
     float a0[BAND + 2], b0[BAND + 2], a1[BAND + 2], b1[BAND + 2], s[BAND + 2];
     load(m_lo, a0, b0);
     for (int m = m_lo; m < m_hi; m += 2) {
