@@ -19,6 +19,7 @@
 //                        inside the wave, z.
 #include <hip/hip_runtime.h>
 
+#include "launch_rules.hpp"
 #include "lcp_tile.hpp"
 #include "pdiv_device.hpp"
 #include "pdiv_internal.hpp"
@@ -39,15 +40,8 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / 64;
-// z slices per divergence3d wave: each chunk re-reads W at its two ends, and
-// longer chunks mean fewer waves.  2 / 4 / 6 / 8 / 12 / 16 slices, us: float32
-// 100x130x150 14.4 / 12.7 / 13.0 / 13.9 / 14.4 / 13.9, 256x512x384 314 / 315 /
-// 321 / 318 / 328 / 323, 512^3 872 / 844 / 869 / 843 / 865 / 853; bfloat16
-// 180x200x220 50 / 45 / 47 / 48 / 48 / 51, 512^3 668 / 559 / 536 / 567 / 548 /
-// 620.
-int z_chunk3(pdiv_dtype dt, int64_t points) {
-  return dt != PDIV_F32 && points > (int64_t(1) << 23) ? 6 : 4;
-}
+// (z slices per divergence3d wave, each chunk re-reading W at its two ends:
+// div3_shape.)
 // What the grid check counts (launches take more slices where those would not
 // fit).
 constexpr int kCheckedZChunk = 12;
@@ -612,17 +606,14 @@ hipError_t launch_divergence3d(const void* mu, const void* vu, const void* mv, c
                                float* dvar, hipStream_t s) {
   const int n_xb = int((nx + 63) / 64);
   const int n_yq = int((ny + kWavesPerBlock - 1) / kWavesPerBlock);
-  int z_chunk = z_chunk3(dt, nz * ny * nx);
+  const Div3Shape shape = div3_shape(dt == PDIV_F32 ? 4 : 2, nz, ny, nx);
+  int z_chunk = shape.z_chunk;
   int64_t blocks = divergence3d_blocks(nz, ny, nx, z_chunk);
   if (!launch_fits(blocks, kBlock)) {
     z_chunk = kCheckedZChunk;
     blocks = divergence3d_blocks(nz, ny, nx, z_chunk);
   }
-  // results of up to 8 M points stay in the caches for the LCP that reads
-  // them next (both calls at 180x200x220, 2 isovalues: 96.7 us, 101.4 with
-  // non-temporal stores), larger ones are streamed past them (256x512x384: 550,
-  // 533)
-  const bool nt = nz * ny * nx > (int64_t(1) << 23);
+  const bool nt = shape.stream;
   if (!launch_fits(blocks, kBlock)) return hipErrorInvalidConfiguration;
   const dim3 grid{unsigned(blocks)}, block{unsigned(kBlock)};
   const int z = int(nz), y = int(ny), x = int(nx);

@@ -49,4 +49,45 @@ constexpr FitForm fit_form(int in_bytes, int out_bytes, int64_t n, int64_t m) {
   return n >= 19 * kMi / 20 && n < 3 * kMi ? FitForm::kFour4 : FitForm::kFour2;
 }
 
+// 3D divergence Gaussians: z slices a wave walks, and whether the results are
+// streamed past the caches (non-temporal stores).
+//
+// Up to 2 M points: short walks until they make waves enough, longer ones past
+// that, the chunk's ends re-reading W (float32, 4 / 6 / 12 slices, us: 100x120x64
+// 5.8 / 6.1 / 8.3, 151x192x71 14.3 / 13.5 / 14.3; 16-bit, streamed: 120x120x100 8.9 /
+// 8.3 / 9.5, 151x192x71 14.1 / 13.1 / 12.5; rows of 32 points, half a wave each,
+// as 16-bit ones: 175x327x32 13.6 / 12.6 / 12.5).
+//
+// Larger volumes: rows of whole 64-byte sectors (nx a multiple of 16) are
+// streamed: their stores need no other wave's, and the inputs stay in the
+// caches.  Other rows' ends are completed there by the neighbouring wave's
+// stores, so they take default stores; except that a volume whose inputs just
+// fit the 256 MB cache beside two others keeps them there when the results go
+// past it (inputs up to 88 MiB).  Default / streamed, us, inputs from a set of
+// three: float32 89x182x193 27.4 / 18.6 (of many sets 29.1 / 31.1), 150x300x129 45.6 /
+// 50.8, 200x250x190 72.1 / 81.7, 256x400x251 179 / 201, but 256x256x256 114 / 111,
+// 150x50x496 29.2 / 25.2, 400x512x384 515 / 500; 16-bit 150x300x129 37.1 / 24.5 (36.7 /
+// 38.4), 180x200x220 42.0 / 44.6, 256x400x251 121 / 134, 400x512x384 330 / 315.
+// Slices: 4, 6 for streamed 16-bit volumes (150x300x129 4 / 6 / 12: 27.6 / 24.5 / 24.6),
+// 12 on rows that leave lanes idle (188x445x32 float32 18.1 / 16.5 / 16.0, 279x508x35
+// 16-bit 28.4 / 25.8 / 23.5; 224x359x74 16-bit 28.8 with 6, 26.8 with 12).
+struct Div3Shape {
+  int z_chunk;
+  bool stream;
+};
+
+constexpr Div3Shape div3_shape(int in_bytes, int64_t nz, int64_t ny, int64_t nx) {
+  constexpr int64_t kMi = int64_t(1) << 20;
+  const int64_t points = nz * ny * nx;
+  if (points <= 2 * kMi) {
+    const int64_t waves = (nx + 63) / 64 * ((ny + 3) / 4 * 4) * ((nz + 3) / 4);  // of 4 slices
+    if (in_bytes == 4 && nx > 32) return {waves < 9000 ? 4 : 6, false};
+    return {waves < 6000 ? 4 : waves < 11000 ? 6 : 12, true};
+  }
+  const bool stream = nx % 16 == 0 || 6 * in_bytes * points <= 88 * kMi;
+  const int64_t lanes = (nx + 63) / 64 * 64;
+  const bool idle = nx <= 48 || (in_bytes == 2 && 100 * nx <= 78 * lanes);
+  return {!stream ? 4 : idle ? 12 : in_bytes == 2 ? 6 : 4, stream};
+}
+
 }  // namespace pdiv

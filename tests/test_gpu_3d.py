@@ -9,7 +9,7 @@ import torch
 import oracle as O
 import paper_2510_01190_amd as P
 import synth
-from gpu_util import U32, dev, host64
+from gpu_util import TORCH_DT, U32, dev, host64
 
 pytestmark = pytest.mark.gpu
 
@@ -314,3 +314,28 @@ def test_three_layer_groups_3d(nz, dt):
         view, buf = _padded(k, shape, gap=32)
         P.lcp_3d_from_moments(*ts, iso, out=view)
         assert torch.equal(view, P.lcp_3d(*div, iso)) and _padding_untouched(view, buf), k
+
+
+@pytest.mark.parametrize("shape,dt", [((49, 400, 32), "f32"), ((181, 325, 32), "bf16"),
+                                      ((151, 192, 71), "f32"), ((121, 121, 99), "f16"),
+                                      ((89, 182, 193), "f32"), ((61, 300, 129), "bf16"),
+                                      ((97, 390, 70), "f16"), ((188, 445, 32), "f32"),
+                                      ((200, 130, 251), "bf16"), ((83, 160, 240), "f32")])
+def test_divergence_shapes_3d(shape, dt):
+    """Every walk length and store form the rule picks, with last chunks short
+    and whole: the slices of a volume are bitwise those of
+    runs of ten of them (but the slices whose z difference a cut makes
+    one-sided), whose shape the rule picks by their own size."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(shape[0])
+    ts = [(torch.randn(shape, generator=g, device="cuda") * 0.3 if q % 2 == 0 else
+           torch.rand(shape, generator=g, device="cuda") * 0.2 + 0.01).to(TORCH_DT[dt])
+          for q in range(6)]
+    whole = P.divergence_gaussian_3d(*ts, dx=0.5, dy=1.0, dz=2.0)
+    for a in range(0, shape[0] - 1, 7):
+        lo, hi = max(0, a - 1), min(shape[0], a + 9)
+        part = P.divergence_gaussian_3d(*[t[lo:hi].contiguous() for t in ts], dx=0.5, dy=1.0, dz=2.0)
+        first = 0 if lo == 0 else lo + 1
+        last = hi if hi == shape[0] else hi - 1
+        for w, p in zip(whole, part):
+            assert torch.equal(w[first:last], p[first - lo:last - lo]), (lo, hi)
