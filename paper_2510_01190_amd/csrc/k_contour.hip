@@ -13,6 +13,7 @@
 //          stored 64 at a time from the row's offset on.
 #include <hip/hip_runtime.h>
 
+#include "launch_rules.hpp"
 #include "pdiv_device.hpp"
 #include "pdiv_internal.hpp"
 
@@ -143,10 +144,11 @@ struct RowPair {
 };
 
 // Row of this wave: one row per wave, or (W = kWavesPerBlock) one row per
-// block, whose waves take batches of the row in turn.  Blocks are dealt round-robin to the 8 XCDs (block b
-// runs on XCD b mod 8), each with its own L2; renumbering the blocks so
-// that each XCD takes a contiguous run of rows lets the two rows that
-// share a vertex row read it through one L2.  A bijection on the blocks.
+// block, whose waves take batches of the row in turn.  Blocks are dealt
+// round-robin to the 8 XCDs (block b runs on XCD b mod 8), each with its own
+// L2; renumbering the blocks so that each XCD takes a contiguous run of rows
+// lets the two rows that share a vertex row read it through one L2.  A
+// bijection on the blocks.
 template <int W>
 __device__ __forceinline__ int wave_row() {
   static_assert(W == 1 || W == kWavesPerBlock, "a wave or a block per row");
@@ -391,14 +393,7 @@ __global__ __launch_bounds__(kBlock) void members_divergence_kernel(
 
 namespace {
 
-// Four waves per row where a wave per row would be few waves with long walks:
-// rows of more than one batch, and at most 2^16 of them.  Count, scan and
-// write against a wave per row: 500x6000 33.5 -> 18.2 us, 721x1440 14.8 ->
-// 12.7, 2048^2 21.3 -> 19.1, 4096^2 52.9 -> 50.4, 8192^2 162.6 -> 161.0 (count
-// and scan alone 59, which the first call of a sized buffer now stops at).
-bool block_per_row(int64_t rows, int64_t nx) {
-  return nx > 64 * kUnroll && rows <= (int64_t(1) << 16);
-}
+static_assert(64 * kUnroll == 512, "the rules count batches of 512 cells");
 
 hipError_t check_rows(int64_t rows) {
   return rows > 0x7fffffff || !launch_fits((rows + kWavesPerBlock - 1) / kWavesPerBlock, kBlock)
@@ -415,7 +410,7 @@ hipError_t launch_contour_segments(const float* fields, int64_t n_fields, int64_
   const hipError_t e = check_rows(rows);
   if (e != hipSuccess || max_segments == 0) return e;
   float4* const segs = reinterpret_cast<float4*>(segments);
-  if (block_per_row(rows, nx))
+  if (contour_writes_by_blocks(rows, nx))
     hipLaunchKernelGGL(contour_write_kernel<kWavesPerBlock>, dim3(unsigned(rows)), dim3(kBlock), 0,
                        s, fields, int(ny), int(nx), field_stride, int(rows), c, row_offsets, segs,
                        max_segments);
@@ -433,7 +428,7 @@ hipError_t launch_isocontours(const float* fields, int64_t n_fields, int64_t fie
   const int64_t rows = n_fields * (ny - 1);
   const hipError_t e = check_rows(rows);
   if (e != hipSuccess) return e;
-  if (block_per_row(rows, nx))
+  if (contour_counts_by_blocks(rows, nx))
     hipLaunchKernelGGL(contour_count_kernel<kWavesPerBlock>, dim3(unsigned(rows)), dim3(kBlock), 0,
                        s, fields, int(ny), int(nx), field_stride, int(rows), c, row_offsets);
   else

@@ -90,4 +90,27 @@ constexpr Div3Shape div3_shape(int in_bytes, int64_t nz, int64_t ny, int64_t nx)
   return {!stream ? 4 : idle ? 12 : in_bytes == 2 ? 6 : 4, stream};
 }
 
+// Isocontours: four waves per cell row instead of one, where a wave per row
+// would be few waves with long walks.  A wave takes batches of 512 cells.
+//
+// Counting, for rows of more than one batch, up to 1024 of them (one / four
+// waves, us: 300x8192 12.7 / 8.0, 1000x4096 9.9 / 8.2, 2000x4096 13.2 / 13.2,
+// 4096x4096 20.0 / 21.5).
+constexpr bool contour_counts_by_blocks(int64_t rows, int64_t nx) {
+  return nx - 1 > 512 && rows <= 1024;
+}
+// Writing, whose waves wait for each other at every round of four batches: a
+// row whose last round is not full leaves waves idle, so the fewer of its
+// places a row fills the fewer rows pay (by the fourth power of the share;
+// count, scan and write, one / four waves: 1 batch 4096x513 14.1 / 22.6; 2
+// batches 300x1024 11.4 / 10.1, 2000x1024 13.7 / 15.7; 3 batches 1000x1440 14.1 /
+// 12.4, 4096x1440 25.2 / 27.2; 4 batches 4096x2049 30.8 / 29.3; 5 batches 1000x2300
+// 18.9 / 16.5, 4096x2300 35.8 / 39.9; 8 batches 4096x4096 51.1 / 50.0, 8192x4096
+// 90.6 / 93.7, 12 batches 8192x6000 134 / 127).
+constexpr bool contour_writes_by_blocks(int64_t rows, int64_t nx) {
+  const double batches = double((nx - 1 + 511) / 512);
+  const double share = batches / (4.0 * double((nx - 1 + 2047) / 2048));
+  return nx - 1 > 512 && double(rows) <= 10000.0 * share * share * share * share;
+}
+
 }  // namespace pdiv

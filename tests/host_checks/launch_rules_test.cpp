@@ -108,9 +108,40 @@ void check_div3() {
   }
 }
 
+// Isocontours: count, scan and write with a wave a row (both passes), with a
+// block a row (both passes), and counting alone with each; the choice may not
+// lose more than 4% to a wave a row, the form that every field took before.
+struct ContourTime {
+  int rows, nx;
+  double wave, block, count_wave, count_block;
+};
+
+void check_contour() {
+  const ContourTime times[] = {
+      {63, 513, 8.8, 8.8, 4.9, 4.9},         {4095, 513, 14.1, 22.6, 8.2, 9.4},
+      {299, 600, 11.0, 10.1, 5.6, 5.4},      {1999, 600, 13.3, 15.7, 6.9, 7.2},
+      {16383, 1024, 55.2, 76.3, 29.0, 33.3}, {999, 1440, 14.1, 12.4, 6.1, 6.1},
+      {1999, 1440, 16.5, 16.7, 7.5, 7.8},    {35999, 1440, 156.0, 180.0, 73.0, 83.5},
+      {1999, 1800, 20.2, 18.2, 8.3, 8.5},    {4095, 2049, 30.8, 29.3, 13.7, 13.8},
+      {4095, 2300, 35.8, 39.9, 15.0, 15.4},  {999, 3000, 21.3, 17.3, 7.7, 7.2},
+      {8191, 3000, 66.4, 74.5, 27.1, 28.9},  {1999, 4096, 35.3, 29.4, 13.2, 13.2},
+      {4095, 4096, 51.1, 50.0, 20.0, 21.5},  {16383, 4096, 190.8, 189.9, 71.3, 73.2},
+      {299, 8192, 43.8, 21.2, 12.7, 8.0},    {8191, 6000, 134.4, 126.9, 47.9, 46.6},
+  };
+  for (const ContourTime& t : times) {
+    const double count = pdiv::contour_counts_by_blocks(t.rows, t.nx) ? t.count_block
+                                                                      : t.count_wave;
+    const double write = pdiv::contour_writes_by_blocks(t.rows, t.nx) ? t.block - t.count_block
+                                                                      : t.wave - t.count_wave;
+    check(count <= 1.06 * t.count_wave, "contour count", t.rows, t.nx, count);
+    check(count + write <= 1.04 * t.wave, "contour", t.rows, t.nx, count + write);
+  }
+}
+
 }  // namespace
 
 int main() {
+  check_contour();
   check_fit();
   check_div3();
   if (failures == 0) std::printf("ALL PASS\n");

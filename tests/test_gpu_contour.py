@@ -163,3 +163,21 @@ def test_contour_segments_alone():
         assert L.pdiv_contour_segments(ptr(f[1]), 1, 50, 700, ctypes.c_float(0.2), ptr(offs),
                                        ptr(segs), cap, stream) == 0
         assert torch.equal(segs[:cap], whole[:cap]) and bool((segs[cap:] == -7.0).all())
+
+
+@pytest.mark.parametrize("shape,cut", [((1500, 2049), 700), ((700, 1400), 620), ((1200, 2600), 300)])
+def test_counts_and_segments_with_different_waves_per_row(shape, cut):
+    """Counting and writing choose one or four waves a row by rules of their
+    own: a field whose passes differ, against its two parts, whose choices are
+    others."""
+    ny, nx = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(ny)
+    f = torch.randn(shape, generator=g, device="cuda")
+    whole = P.isocontour(f, 0.1)
+    parts = [P.isocontour(f[:cut + 1].contiguous(), 0.1), P.isocontour(f[cut:].contiguous(), 0.1)]
+    assert whole.shape[0] == parts[0].shape[0] + parts[1].shape[0]
+    assert torch.equal(whole[:parts[0].shape[0]], parts[0])
+    rest = whole[parts[0].shape[0]:]
+    assert torch.equal(rest[:, 0::2], parts[1][:, 0::2])
+    assert float((rest[:, 1::2] - cut - parts[1][:, 1::2]).abs().max()) <= 2.0 ** -13  # half an ulp at 2^10
