@@ -39,7 +39,8 @@ bool all_rows_on_lines(const std::vector<BatchField>& f);
 // returns the tile count.
 int64_t fill_tiles(std::vector<BatchField>& f, int band_rows, bool paired);
 // The launch shape by rule: band rows for a layout, and the grid.
-int batch_band_rows(const std::vector<BatchField>& f, bool paired);
+int batch_band_rows(const std::vector<BatchField>& f, bool fused, pdiv_dtype dt, bool paired,
+                    int kc);
 int batch_grid(int64_t n_tiles);
 hipError_t launch_batch(const void* kernel, const BatchField* dev_fields, int n_fields,
                         int64_t n_tiles, int band_rows, int grid, hipStream_t s);

@@ -4,6 +4,7 @@
 #pragma once
 
 #include <cstdint>
+#include <initializer_list>
 
 namespace pdiv {
 
@@ -111,6 +112,67 @@ constexpr bool contour_writes_by_blocks(int64_t rows, int64_t nx) {
   const double batches = double((nx - 1 + 511) / 512);
   const double share = batches / (4.0 * double((nx - 1 + 2047) / 2048));
   return nx - 1 > 512 && double(rows) <= 10000.0 * share * share * share * share;
+}
+
+// Batches.  The layout of line-aligned fused ones: the paired tile from so many
+// million cells (in all fields) by storage and isovalue slots (of the mean count
+// where the fields' differ: it is the stores that gain); below, its seam step
+// and staged rows cost more than whole-line stores save.  Split / paired
+// at their best heights, us: float32 9.0 M cells x4 73 / 65, 8.1 M x6 78 / 75, 5.2 M
+// x13 119 / 99, 3.5 M x15 77 / 71, 2.9 M x15 65 / 68; 16-bit 13.7 M x2 48 / 66, 14 M x4 1.2
+// times the paired time, 10 M 0.78; 10 M x6 1.25 times, 7 M 0.87; 3.5 M x14 78 / 73.
+constexpr bool batch_paired(int64_t cells, int in_bytes, int kc) {
+  constexpr int64_t k100 = 100000;
+  const int64_t least = in_bytes == 2 ? (kc >= 16   ? 33
+                                         : kc >= 12 ? 30
+                                         : kc >= 8  ? 64
+                                         : kc >= 6  ? 90
+                                         : kc >= 3  ? 120
+                                                    : 160)
+                                      : (kc >= 16   ? 30
+                                         : kc >= 12 ? 33
+                                         : kc >= 8  ? 55
+                                         : kc >= 6  ? 70
+                                         : kc >= 3  ? 92
+                                                    : 115);
+  return kc >= 2 && cells >= least * k100;
+}
+
+// SIMDs of a whole MI355X (256 CUs of four); on a part of one the rules below
+// only lose speed.
+constexpr int64_t kSimds = 1024;
+
+// The band height, by the number of tiles a height leaves: 8, 4, 2 or 1 rows
+// from 6000, 3000 and 1500 tiles (paired: 32 or 16 from 16000 and 4000), unless
+// the rows that the fullest SIMD walks promise a twentieth off: as lcp_band_rows
+// for one field, n (b + 0.7) for n rounds of the batch's tiles(b), a SIMD's only
+// wave counted twice and the second, below 8 slots, 1.15 times.  Split tiles of
+// many isovalues are mostly stores and gain nothing past 8 rows, those of
+// 16-bit storage past 3 (15.7 M cells x11 into dense maps 260 us, 340 with 8).  Over
+// 2879 batches of 8 to 64 fields of 64 to 2048 a side, times are 1.8% above the best
+// shape's on average; by tile numbers alone 6.0%, and 70 were slower than a
+// resident grid of 16-row tiles (3.3 M cells x14 on lines 85 us, 72 there, 70 now).
+template <typename Tiles>
+constexpr int batch_band_rows(const Tiles& tiles, bool fused, int in_bytes, bool paired, int kc) {
+  const int tallest = !fused || paired || kc < 12 ? 16 : in_bytes == 2 ? 3 : 8;
+  if (tallest >= 8 && tiles(8) >= 9000) return !paired ? 8 : tiles(32) >= 16000 ? 32 : 16;
+  auto cost = [&](int b) {
+    const int64_t n = (tiles(b) + kSimds - 1) / kSimds;
+    return n * (10 * b + 7) * (n == 1 ? 40 : n == 2 && kc < 8 ? 23 : 20);
+  };
+  int64_t least = INT64_MAX;
+  int best = 1;
+  for (int b : {1, 2, 3, 4, 6, 8, 12, 16}) {
+    if (b > tallest) break;
+    const int64_t c = cost(b);
+    if (c < least) least = c, best = b;
+  }
+  const int by_tiles = paired && tiles(16) >= 4000 ? 16
+                       : tiles(8) >= 6000          ? 8
+                       : tiles(4) >= 3000          ? 4
+                       : tiles(2) >= 1500          ? 2
+                                                   : 1;
+  return by_tiles <= tallest && 20 * cost(by_tiles) <= 21 * least ? by_tiles : best;
 }
 
 }  // namespace pdiv

@@ -46,6 +46,7 @@
 
 #include <cstdint>
 
+#include "launch_rules.hpp"
 #include "pdiv_device.hpp"
 #include "pdiv_internal.hpp"
 
@@ -760,7 +761,6 @@ inline int lcp_band_rows(int64_t strips, int64_t rows, bool paired, bool fused, 
     if (paired && waves(16) >= 6000) return 16;
     return 8;
   }
-  constexpr int64_t kSimds = 1024;
   const int tallest = fused && (paired || kc < 12) ? 16 : 8;
   int64_t least = INT64_MAX;
   int best = 1;

@@ -26,6 +26,7 @@
 #include <vector>
 
 #include "batch_internal.hpp"
+#include "launch_rules.hpp"
 #include "lcp_tile.hpp"
 
 namespace pdiv {
@@ -123,33 +124,18 @@ bool all_rows_on_lines(const std::vector<BatchField>& f) {
   return true;
 }
 
-// Line-aligned fused batches: the paired tile from 2 M cells at 8 and more
-// isovalues, from 12 M below (48 fields of 64..2048 a side, 16.6 M cells, split
-// against paired at their best shapes: 93 / 97 us at 1 isovalue, 151 / 147 at
-// 4, 230 / 212 at 8; 64 of 64..1000, 6 M cells, 62.6 / 62.4 at 4, 98 / 89 at
-// 8; 12 fields, 1.9 M cells, 28 / 32 at 4).
-bool batch_paired(const std::vector<BatchField>& f, int kc) {
-  int64_t cells = 0;
-  for (auto& x : f) cells += int64_t(x.ny - 1) * (x.nx - 1);
-  return kc >= 8 ? cells >= 2000000 : kc >= 2 && cells >= 12000000;
+int64_t batch_tiles(const std::vector<BatchField>& f, bool paired, int band_rows) {
+  const int cells = cells_per_wave(paired);
+  int64_t t = 0;
+  for (auto& x : f)
+    t += int64_t((x.nx - 1 + cells - 1) / cells) * ((x.ny - 1 + band_rows - 1) / band_rows);
+  return t;
 }
 
-// Band height by the number of tiles it leaves, as lcp_band_rows for one
-// field; the paired tile's staged rows want at least 16 where there are tiles
-// enough (48 fields, 4 isovalues: 159 / 147 / 151 / 156 us with 8 / 16 / 32 /
-// 64 rows; the split tile 165 / 151 / 162 / 155 us with 4 / 8 / 16 / 32; 12
-// fields: 30 / 28 / 28 / 32 / 40 us with 2 / 4 / 8 / 16 / 32).
-int batch_band_rows(const std::vector<BatchField>& f, bool paired) {
-  const int cells = cells_per_wave(paired);
-  auto tiles = [&](int b) {
-    int64_t t = 0;
-    for (auto& x : f)
-      t += int64_t((x.nx - 1 + cells - 1) / cells) * ((x.ny - 1 + b - 1) / b);
-    return t;
-  };
-  if (paired && tiles(32) >= 16000) return 32;
-  if (paired && tiles(16) >= 4000) return 16;
-  return tiles(8) >= 6000 ? 8 : tiles(4) >= 3000 ? 4 : tiles(2) >= 1500 ? 2 : 1;
+int batch_band_rows(const std::vector<BatchField>& f, bool fused, pdiv_dtype dt, bool paired,
+                    int kc) {
+  return batch_band_rows([&](int b) { return batch_tiles(f, paired, b); }, fused,
+                         dt == PDIV_F32 ? 4 : 2, paired, kc);
 }
 
 // A wave per tile, as far as the grid goes: the hardware hands out blocks as
@@ -307,6 +293,20 @@ void shape(pdiv_batch b, bool paired, int band_rows) {
   b->n_tiles = fill_tiles(b->fields, band_rows, paired);
 }
 
+// The shape by rule: layout, band height and a wave per tile.
+void rule_shape(pdiv_batch b) {
+  int64_t cells = 0;
+  double values = 0;
+  for (auto& x : b->fields) {
+    cells += int64_t(x.ny - 1) * (x.nx - 1);
+    values += double(x.ny - 1) * double(x.nx - 1) * x.n_iso;
+  }
+  const int slots = iso_bucket(int(std::ceil(values / double(cells))));
+  const bool paired = b->lines && batch_paired(cells, b->dtype == PDIV_F32 ? 4 : 2, slots);
+  shape(b, paired, batch_band_rows(b->fields, true, b->dtype, paired, b->kc));
+  b->grid = batch_grid(b->n_tiles);
+}
+
 // Grid of a tuned batch: gm / 2 times the resident capacity, at most a wave
 // per tile (kGridAll: just that).
 constexpr int kGridAll = 1 << 20;
@@ -430,9 +430,7 @@ pdiv_status pdiv_batch_create(const pdiv_field* fields_host, int32_t n_fields, p
   if (flags & PDIV_BATCH_AUTOTUNE) {
     st = autotune(b, s);
   } else {
-    const bool paired = b->lines && batch_paired(b->fields, kc);
-    shape(b, paired, batch_band_rows(b->fields, paired));
-    b->grid = batch_grid(b->n_tiles);
+    rule_shape(b);
     st = upload(b);
   }
   if (st == PDIV_OK && hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess)

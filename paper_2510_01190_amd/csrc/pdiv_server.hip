@@ -275,7 +275,7 @@ struct pdiv_server_s : serve::Executor {
       kc = std::max(kc, iso_bucket(r->n_iso));
     }
     const bool paired = kc >= 8 && all_rows_on_lines(fv);
-    const int band_rows = batch_band_rows(fv, paired);
+    const int band_rows = batch_band_rows(fv, false, PDIV_F32, paired, kc);
     const int64_t n_tiles = fill_tiles(fv, band_rows, paired);
     std::memcpy(S.host_fields, fv.data(), sizeof(BatchField) * fv.size());
     hipStream_t s = streams[size_t(next_stream)];
