@@ -208,7 +208,10 @@ namespace {
 // Autotune cache: in memory for the process, and in a JSON file when
 // PDIV_TUNE_CACHE names one.  Key: dtype, isovalue bucket, whether the
 // outputs are line-aligned, and the size class (log2 of total cells, log2 of
-// the mean field side).  Value: band rows, grid multiplier, tile layout.
+// the mean field side).  Value: band rows, grid multiplier, tile layout; band
+// rows 0: the rule's shape, whatever it is for the batch at hand.  The key's
+// version names the candidates: entries of an earlier set, which may be slower
+// than the rule's shape, are not used.
 struct Tune {
   int band_rows, grid_mult, paired;
 };
@@ -224,7 +227,7 @@ std::string tune_key(pdiv_dtype dt, int kc, bool lines, const std::vector<BatchF
   }
   side /= std::max<size_t>(1, f.size());
   std::ostringstream o;
-  o << "gfx950/batch/dt" << int(dt) << "/k" << kc << "/l" << int(lines) << "/c"
+  o << "gfx950/batch2/dt" << int(dt) << "/k" << kc << "/l" << int(lines) << "/c"
     << int(std::log2(cells + 1)) << "/s" << int(std::log2(side + 1));
   return o.str();
 }
@@ -241,7 +244,7 @@ void tune_load() {
     const size_t a = line.find('"'), b = line.find('"', a + 1), c = line.find('[', b);
     if (a == std::string::npos || b == std::string::npos || c == std::string::npos) continue;
     int br = 0, gm = 0, pr = 0;
-    if (std::sscanf(line.c_str() + c, "[%d, %d, %d]", &br, &gm, &pr) == 3 && br > 0 && gm > 0 &&
+    if (std::sscanf(line.c_str() + c, "[%d, %d, %d]", &br, &gm, &pr) == 3 && br >= 0 && gm > 0 &&
         (pr == 0 || pr == 1))
       g_tune[line.substr(a + 1, b - a - 1)] = {br, gm, pr};
   }
@@ -315,59 +318,108 @@ int tuned_grid(pdiv_batch b, int gm) {
   return int(std::max<int64_t>(1, std::min<int64_t>(g, batch_grid(b->n_tiles))));
 }
 
-// Times the candidate shapes on the batch itself (the launches write the
-// batch's own outputs) and keeps the fastest: band rows x grid size, and both
-// tile layouts when every output row starts on a line.
+// The shape of a tuning entry on this batch.
+void tuned_shape(pdiv_batch b, const Tune& t) {
+  if (t.band_rows == 0) {
+    rule_shape(b);
+    return;
+  }
+  shape(b, t.paired != 0, t.band_rows);
+  b->grid = tuned_grid(b, t.grid_mult);
+}
+
+// Launches of a shape on the batch itself (they write the batch's own outputs),
+// timed by a pair of events.
+struct Timer {
+  static constexpr int kLaunches = 3;
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  int table_rows = 0, table_paired = -1;  // the shape of the uploaded table
+
+  ~Timer() {
+    if (e0) (void)hipEventDestroy(e0);
+    if (e1) (void)hipEventDestroy(e1);
+  }
+  // us per launch of the shape t, into *us
+  pdiv_status time(pdiv_batch b, const Tune& t, hipStream_t s, float* us) {
+    if ((!e0 && hipEventCreate(&e0) != hipSuccess) || (!e1 && hipEventCreate(&e1) != hipSuccess))
+      return device_status(hipGetLastError(), "autotune events");
+    tuned_shape(b, t);
+    if (b->band_rows != table_rows || int(b->paired) != table_paired) {
+      const pdiv_status st = upload(b);
+      if (st != PDIV_OK) return st;
+      table_rows = b->band_rows;
+      table_paired = int(b->paired);
+    }
+    auto launch = [&] {
+      return launch_batch(b->kernel, b->dev, int(b->fields.size()), b->n_tiles, b->band_rows,
+                          b->grid, s);
+    };
+    hipError_t e = launch();  // warm
+    e = e != hipSuccess ? e : hipEventRecord(e0, s);
+    for (int r = 0; r < kLaunches && e == hipSuccess; ++r) e = launch();
+    e = e != hipSuccess ? e : hipEventRecord(e1, s);
+    e = e != hipSuccess ? e : hipEventSynchronize(e1);
+    float ms = 0;
+    e = e != hipSuccess ? e : hipEventElapsedTime(&ms, e0, e1);
+    *us = ms * (1000.0f / kLaunches);
+    return device_status(e, "autotune launch");
+  }
+};
+
+// Times the candidate shapes and keeps the fastest: the rule's shape; both tile
+// layouts when every output row starts on a line, with bands of 8 to 64 rows on
+// four grids; and bands of 1 to 4 rows, where 8-row ones would be few (less than
+// eight a SIMD).  A band of less than 8 rows has to be 2 us faster, a launch's
+// own spread, as short bands read more.  (12 fields of 64 to 300 a side at 12
+// isovalues: 13 us with the rule's 2 rows, 28 with the best of 8 to 64.)
+//
+// A kept entry serves every batch of its size class, whose best shapes differ
+// (24 fields of 6 M cells 35 us with the entry of others, 23 with the rule's
+// shape): it is timed against the rule's shape, which takes its place on this
+// batch where it is faster by 2 us and a twentieth.
 pdiv_status autotune(pdiv_batch b, hipStream_t s) {
+  constexpr float kSpread = 2.0f;
+  const Tune rule{0, kGridAll, 0};
   const std::string key = tune_key(b->dtype, b->kc, b->lines, b->fields);
+  Tune win = rule;
+  bool known = false;
   {
     std::lock_guard<std::mutex> g(g_tune_mu);
     tune_load();
     auto it = g_tune.find(key);
-    if (it != g_tune.end() && (b->lines || !it->second.paired)) {
-      shape(b, it->second.paired != 0, it->second.band_rows);
-      b->grid = tuned_grid(b, it->second.grid_mult);
-      return upload(b);
-    }
+    known = it != g_tune.end() && (b->lines || !it->second.paired);
+    if (known) win = it->second;
   }
-  hipEvent_t e0, e1;
-  if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
-    return device_status(hipGetLastError(), "autotune events");
-  float best = 1e30f;
-  Tune win{16, 2, 0};
+  Timer timer;
   pdiv_status st = PDIV_OK;
-  for (int paired = 0; paired <= (b->lines ? 1 : 0) && st == PDIV_OK; ++paired) {
-    for (int br : {8, 16, 32, 64}) {
-      shape(b, paired != 0, br);
-      if ((st = upload(b)) != PDIV_OK) break;
-      for (int gm : {1, 2, 4, kGridAll}) {
-        const int grid = tuned_grid(b, gm);
-        hipError_t e = launch_batch(b->kernel, b->dev, int(b->fields.size()), b->n_tiles, br,
-                                    grid, s);  // warm
-        e = e != hipSuccess ? e : hipEventRecord(e0, s);
-        for (int r = 0; r < 3 && e == hipSuccess; ++r)
-          e = launch_batch(b->kernel, b->dev, int(b->fields.size()), b->n_tiles, br, grid, s);
-        e = e != hipSuccess ? e : hipEventRecord(e1, s);
-        e = e != hipSuccess ? e : hipEventSynchronize(e1);
-        float ms = 0;
-        e = e != hipSuccess ? e : hipEventElapsedTime(&ms, e0, e1);
-        if (e != hipSuccess) {
-          st = device_status(e, "autotune launch");
-          break;
-        }
-        if (ms < best) {
-          best = ms;
-          win = {br, gm, paired};
-        }
-      }
-      if (st != PDIV_OK) break;
+  if (known) {
+    if (win.band_rows != 0) {
+      float kept = 0, ruled = 0;
+      if ((st = timer.time(b, win, s, &kept)) != PDIV_OK) return st;
+      if ((st = timer.time(b, rule, s, &ruled)) != PDIV_OK) return st;
+      if (1.05f * ruled + kSpread < kept) win = rule;
+    }
+    tuned_shape(b, win);
+    return upload(b);
+  }
+  std::vector<Tune> candidates{rule};
+  for (int paired = 0; paired <= (b->lines ? 1 : 0); ++paired) {
+    for (int br : {8, 16, 32, 64})
+      for (int gm : {1, 2, 4, kGridAll}) candidates.push_back({br, gm, paired});
+    if (batch_tiles(b->fields, paired != 0, 8) < 8 * kSimds)
+      for (int br : {1, 2, 3, 4}) candidates.push_back({br, kGridAll, paired});
+  }
+  float best = 1e30f;
+  for (const Tune& t : candidates) {
+    float us = 0;
+    if ((st = timer.time(b, t, s, &us)) != PDIV_OK) return st;
+    if (b->band_rows < 8) us += kSpread;
+    if (us < best) {
+      best = us;
+      win = t;
     }
   }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  if (st != PDIV_OK) return st;
-  shape(b, win.paired != 0, win.band_rows);
-  b->grid = tuned_grid(b, win.grid_mult);
+  tuned_shape(b, win);
   {
     std::lock_guard<std::mutex> g(g_tune_mu);
     g_tune[key] = win;

@@ -176,3 +176,37 @@ def test_field_search_and_batch_shapes(n, hi, k):
         want = P.lcp_from_moments(f["mean_u"], f["var_u"], f["mean_v"], f["var_v"], iso)
         assert torch.equal(got["lcp"], want), got["lcp"].shape
     b.close()
+
+
+def test_autotuned_batch_of_few_tiles_takes_short_bands(tmp_path, monkeypatch):
+    """Twelve small fields leave a few hundred 8-row tiles on 1024 SIMDs, where
+    bands of less than 8 rows take half the time: the autotuner tries them (and
+    the untuned rule's own shape), an entry that an earlier candidate set left
+    in the cache file does not pin the batch to its shape, and a second batch
+    reads the choice back."""
+    cache = tmp_path / "tune.json"
+    monkeypatch.setenv("PDIV_TUNE_CACHE", str(cache))
+    rng = np.random.default_rng(12)
+    fields = []
+    for ny, nx in rng.integers(64, 300, (12, 2)):
+        m = [torch.from_numpy(rng.normal(0, 0.3, (ny, nx)).astype(np.float32)).cuda() if q % 2 == 0
+             else torch.from_numpy(rng.uniform(0.01, 0.2, (ny, nx)).astype(np.float32)).cuda()
+             for q in range(4)]
+        iso = np.linspace(-0.4, 0.4, 11).astype(np.float32)
+        fields.append(dict(mean_u=m[0], var_u=m[1], mean_v=m[2], var_v=m[3], dx=1.0, dy=1.0,
+                           isovalues=torch.from_numpy(iso).cuda(), iso_host=iso))
+    cells = sum((f["mean_u"].shape[0] - 1) * (f["mean_u"].shape[1] - 1) for f in fields)
+    side = np.mean([np.sqrt(f["mean_u"].numel()) for f in fields])
+    old_key = f"gfx950/batch/dt0/k12/l0/c{int(np.log2(cells + 1))}/s{int(np.log2(side + 1))}"
+    cache.write_text('{\n  "%s": [64, 2, 0]\n}\n' % old_key)
+    b = P.Batch(fields, graph=False, autotune=True)
+    info = b.info()
+    assert info["band_rows"] < 8, info
+    b.launch()
+    torch.cuda.synchronize()
+    for f, g in zip(fields, b.fields):
+        assert torch.equal(g["lcp"], _per_field(f))
+    b.close()
+    b2 = P.Batch(fields, graph=False, autotune=True)
+    assert b2.info() == info
+    b2.close()
