@@ -166,15 +166,18 @@ struct Planes6 {
 // the adjacent lanes) and V's next row per level, and W at the levels one
 // below to one above the held ones (level t + 1 of the array is held level t;
 // adjacent held levels share W).
-template <int L, bool FUSED>
+// WIDE: U at the end lanes' missing neighbours too (eu, es; lane 0's left one,
+// lane 63's right one).
+template <int L, bool FUSED, bool WIDE = false>
 struct Row3;
 template <int L>
-struct Row3<L, false> {
+struct Row3<L, false, false> {
   float m[L + 1], v[L + 1];
 };
-template <int L>
-struct Row3<L, true> {
+template <int L, bool WIDE>
+struct Row3<L, true, WIDE> {
   float u[L + 1], s[L + 1];
+  float eu[WIDE ? L + 1 : 1], es[WIDE ? L + 1 : 1];
   float vm[L + 1], vv[L + 1];
   float wm[L + 3], wv[L + 3];
 };
@@ -186,11 +189,20 @@ struct VWin {
   float m[L + 1][2], v[L + 1][2];
 };
 
+// The left or right lane's value; with EDGE the end lane, which has no such
+// lane, gets e (every lane is active).
+template <bool EDGE, bool LEFT>
+__device__ __forceinline__ float neighbour(float e, float x) {
+  if constexpr (!EDGE) return LEFT ? dpp_from_left(x) : dpp_from_right(x);
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(e), __float_as_int(x),
+                                                    LEFT ? 0x138 : 0x130, 0xf, 0xf, false));
+}
+
 // Eq. 2-3 (fused) or the loaded Gaussians (two-step) of the held levels at
 // row j, as corners; bz[l]: level l is a z boundary plane.  Moves the V
 // window one row.
-template <int L, bool FUSED>
-__device__ __forceinline__ void row_corners(const Row3<L, FUSED>& r, VWin<L>& w,
+template <int L, bool FUSED, bool WIDE>
+__device__ __forceinline__ void row_corners(const Row3<L, FUSED, WIDE>& r, VWin<L>& w,
                                             const bool (&bz)[L + 1], float cxm, float cxv,
                                             float cym, float cyv, const StencilCoef3& k,
                                             Corner (&c)[L + 1]) {
@@ -200,10 +212,13 @@ __device__ __forceinline__ void row_corners(const Row3<L, FUSED>& r, VWin<L>& w,
     if constexpr (FUSED) {
       // the lanes beside a boundary column hold that column again (clamped),
       // so the boundary's one-sided differences need no selection
-      g = div_gauss3(dpp_from_left(r.u[l]), dpp_from_right(r.u[l]), dpp_from_left(r.s[l]),
-                     dpp_from_right(r.s[l]), w.m[l][0], r.vm[l], w.v[l][0], r.vv[l], r.wm[l],
-                     r.wm[l + 2], r.wv[l], r.wv[l + 2], cxm, cxv, cym, cyv,
-                     bz[l] ? k.czm_bd : k.czm_in, bz[l] ? k.czv_bd : k.czv_in);
+      float eu = 0.0f, es = 0.0f;
+      if constexpr (WIDE) eu = r.eu[l], es = r.es[l];
+      g = div_gauss3(neighbour<WIDE, true>(eu, r.u[l]), neighbour<WIDE, false>(eu, r.u[l]),
+                     neighbour<WIDE, true>(es, r.s[l]), neighbour<WIDE, false>(es, r.s[l]),
+                     w.m[l][0], r.vm[l], w.v[l][0], r.vv[l], r.wm[l], r.wm[l + 2], r.wv[l],
+                     r.wv[l + 2], cxm, cxv, cym, cyv, bz[l] ? k.czm_bd : k.czm_in,
+                     bz[l] ? k.czv_bd : k.czv_in);
       w.m[l][0] = w.m[l][1];
       w.v[l][0] = w.v[l][1];
       w.m[l][1] = r.vm[l];
@@ -257,10 +272,10 @@ __device__ __forceinline__ void load_levels(Row3<L, false>& r, const Rows3<false
     r.v[l] = UNIFORM ? rd.s.get(c.x, lo[l]) : rd.s.get(c.x + lo[l]);
   }
 }
-template <int L, bool UNIFORM, typename T>
-__device__ __forceinline__ void load_levels(Row3<L, true>& r, const Rows3<true, T>& rd,
-                                            const uint32_t* lw, const Col& c) {
-  static_assert(UNIFORM, "the fused walk has no seam");
+// edge: the end lanes' missing columns, every other lane's own.
+template <int L, bool WIDE, typename T>
+__device__ __forceinline__ void load_levels(Row3<L, true, WIDE>& r, const Rows3<true, T>& rd,
+                                            const uint32_t* lw, const Col& c, uint32_t edge) {
 #pragma unroll
   for (int t = 0; t < L + 3; ++t) {
     r.wm[t] = rd.wm.get(c.x, lw[t]);
@@ -270,6 +285,10 @@ __device__ __forceinline__ void load_levels(Row3<L, true>& r, const Rows3<true, 
   for (int l = 0; l <= L; ++l) {
     r.u[l] = rd.u.get(c.x, lw[l + 1]);
     r.s[l] = rd.s.get(c.x, lw[l + 1]);
+    if constexpr (WIDE) {
+      r.eu[l] = rd.u.get(edge, lw[l + 1]);
+      r.es[l] = rd.s.get(edge, lw[l + 1]);
+    }
     r.vm[l] = rd.vm.get(c.x, lw[l + 1]);
     r.vv[l] = rd.vv.get(c.x, lw[l + 1]);
   }
@@ -312,10 +331,10 @@ __device__ __forceinline__ void load_levels(Row3<L, true>& r, const Rows3<true, 
 //     two.  256x512x384 float32 at 1 / 4 / 8 isovalues on line-aligned rows
 //     393 / 584 / 899 -> 357 / 555 / 836 us, bfloat16 319 / 547 / 920 -> 245 /
 //     463 / 755; 512^3 float32 1026 / 1505 / 2302 -> 966 / 1500 / 2174.
-//     Where 61 cells make a ninth strip of what 63 made eight, 4 isovalues on
-//     dense rows lose 4% (300x400x500 638 -> 667); strips of 63, whose end lanes
-//     load their missing neighbours, win that back (623) but cost 173 registers
-//     and up to 6% everywhere else.
+//     WIDE: lane L holds column x0+L, x0 = 63 strip, and the end lanes load
+//     the neighbours that no lane of the wave holds: 63 cells for 10 registers
+//     more (4 isovalues 161 -> 173, two waves per SIMD), where a row takes a
+//     strip less by it (lcp3d_wide_strips).
 // With 8 corners the float32 combination can land an ulp outside [0, 1]
 // where the probability is 0 or 1; the exact value is inside, so clamping
 // only removes error.  The IEEE 754-2019 maximum and minimum (v_maximum3_f32,
@@ -325,25 +344,26 @@ __device__ __forceinline__ float clamp01(float v) {
   return __builtin_elementwise_minimum(__builtin_elementwise_maximum(v, 0.0f), 1.0f);
 }
 
-template <bool FUSED, bool LINES>
+template <bool FUSED, bool LINES, bool WIDE>
 constexpr int strip_cells3() {
-  return FUSED ? 61 : LINES ? 64 : 63;
+  return FUSED ? (WIDE ? 63 : 61) : LINES ? 64 : 63;
 }
 
 // ALL: every slot holds an isovalue; else the slots from n_store on store
 // nothing (the run-time count costs scalar registers and selects: two-step at 8
 // isovalues 595 -> 710 us at 256x512x384, fused at 16 1550 -> 1746, so only
 // counts that save a whole launch run that way).
-template <int KC, int LZ, bool FUSED, bool LINES, bool ALL, typename T>
+template <int KC, int LZ, bool FUSED, bool LINES, bool WIDE, bool ALL, typename T>
 __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int ny, int nx,
                                                        StencilCoef3 k, IsoChunk iso, int n_store,
                                                        float* __restrict__ out, int64_t pitch,
                                                        int64_t plane, int n_groups, int n_strips,
                                                        int n_bands, int band_rows) {
   static_assert(!(LINES && FUSED), "the seam step is the two-step kernel's");
+  static_assert(FUSED || !WIDE, "the two-step kernel has no halo");
   static_assert(!LINES || 2 * KC * LZ <= 64, "the seam step needs two lanes per (q, l)");
-  constexpr int kW = strip_cells3<FUSED, LINES>();
-  constexpr int kHalo = FUSED ? 1 : 0;  // lanes left of the strip's first cell
+  constexpr int kW = strip_cells3<FUSED, LINES, WIDE>();
+  constexpr int kHalo = FUSED && !WIDE ? 1 : 0;  // lanes left of the strip's first cell
   const int nb = gridDim.x, xcd = blockIdx.x % 8, q8 = nb / 8, r8 = nb % 8;
   const int blk = xcd * q8 + min(xcd, r8) + blockIdx.x / 8;
   const int wave = __builtin_amdgcn_readfirstlane(blk * kWavesPerBlock + (threadIdx.x >> 6));
@@ -409,11 +429,16 @@ __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int 
       }
     }
   }
-  Row3<LZ, FUSED> raw;
+  Row3<LZ, FUSED, WIDE> raw;
   Row3<1, false> sraw;
+  const int edge_x = lane == 0 ? max(x0 - 1, 0) : lane == 63 ? min(x0 + 64, nx - 1) : -1;
+  const uint32_t edge = edge_x < 0 ? col.x : uint32_t(edge_x) * uint32_t(sizeof(T));
   auto load = [&](int j) {
     const Rows3<FUSED, T> rd(src, lb, j, nz, ny, nx, vplane);
-    load_levels<LZ, true, T>(raw, rd, lo, col);
+    if constexpr (FUSED)
+      load_levels<LZ, WIDE, T>(raw, rd, lo, col, edge);
+    else
+      load_levels<LZ, true, T>(raw, rd, lo, col);
     if constexpr (LINES) load_levels<1, false, T>(sraw, rd, slo, cs);
   };
   load(j0);
@@ -438,7 +463,7 @@ __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int 
   };
   {  // the band's first vertex row: corners only (j1 > j0 always)
     Corner c[LZ + 1];
-    row_corners<LZ, FUSED>(raw, win, bz, cxm, cxv, cym_of(j0), cyv_of(j0), k, c);
+    row_corners(raw, win, bz, cxm, cxv, cym_of(j0), cyv_of(j0), k, c);
     Corner sc[2];
     if constexpr (LINES) seam_corners(sc);
     load(j0 + 1);
@@ -460,7 +485,7 @@ __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int 
   auto row = [&](int j, const AB (&prev)[LZ + 1][KC], AB (&next)[LZ + 1][KC],
                  const AB (&sprev)[2], AB (&snext)[2]) {
     Corner c[LZ + 1];
-    row_corners<LZ, FUSED>(raw, win, bz, cxm, cxv, cym_of(j), cyv_of(j), k, c);
+    row_corners(raw, win, bz, cxm, cxv, cym_of(j), cyv_of(j), k, c);
     Corner sc[2];
     if constexpr (LINES) seam_corners(sc);
     if (j < j1) load(j + 1);
@@ -537,11 +562,11 @@ int band_rows3(int64_t columns, int64_t rows, bool lines, int kc) {
   return waves(4) >= 3000 ? 4 : waves(2) >= 1500 ? 2 : 1;
 }
 
-template <int KC, int LZ, bool FUSED, bool LINES, bool ALL, typename T>
+template <int KC, int LZ, bool FUSED, bool LINES, bool WIDE, bool ALL, typename T>
 hipError_t launch_lcp3d_kc(const Planes6& src, int nz, int ny, int nx, const StencilCoef3& k,
                            const IsoChunk& iso, int n_store, float* out, int64_t pitch, int64_t plane,
                            hipStream_t s) {
-  constexpr int kW = strip_cells3<FUSED, LINES>();
+  constexpr int kW = strip_cells3<FUSED, LINES, WIDE>();
   const int n_groups = (nz - 1 + LZ - 1) / LZ;
   const int n_strips = (nx - 1 + kW - 1) / kW;
   int band_rows = band_rows3(int64_t(n_groups) * n_strips, ny - 1, LINES, KC);
@@ -555,7 +580,7 @@ hipError_t launch_lcp3d_kc(const Planes6& src, int nz, int ny, int nx, const Ste
     band_rows *= 2;
   } while (n_bands > 1);
   if (!launch_fits(blocks, kBlock)) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((lcp3d_kernel<KC, LZ, FUSED, LINES, ALL, T>), dim3(unsigned(blocks)), dim3(kBlock),
+  hipLaunchKernelGGL((lcp3d_kernel<KC, LZ, FUSED, LINES, WIDE, ALL, T>), dim3(unsigned(blocks)), dim3(kBlock),
                      0, s, src, nz, ny, nx, k, iso, n_store, out, pitch, plane, n_groups, n_strips,
                      n_bands, band_rows);
   return hipGetLastError();
@@ -641,13 +666,13 @@ hipError_t launch_divergence3d(const void* mu, const void* vu, const void* mv, c
 
 namespace {
 
-template <bool FUSED, bool LINES, typename T>
+template <bool FUSED, bool LINES, bool WIDE, typename T>
 hipError_t launch_lcp3d_kcs(const Planes6& src, int z, int y, int x, const StencilCoef3& k,
                             const IsoChunk& iso, int kc, float* out, int64_t pitch, int64_t plane,
                             hipStream_t s) {
 #define PDIV_L3(K, LZ, ALL)                                                                   \
-  return launch_lcp3d_kc<K, LZ, FUSED, LINES, ALL, T>(src, z, y, x, k, iso, kc, out, pitch, \
-                                                      plane, s)
+  return launch_lcp3d_kc<K, LZ, FUSED, LINES, WIDE, ALL, T>(src, z, y, x, k, iso, kc, out,  \
+                                                            pitch, plane, s)
   // two-step: 4 layers; fused: the moment rows' registers leave room for 3
   // above 4 isovalues (3 against 2 layers re-evaluate 4 levels' tails for 3
   // cells, not 3 for 2, at the same waves per SIMD: 148 ... 167 registers to 8
@@ -674,19 +699,18 @@ hipError_t launch_lcp3d_kcs(const Planes6& src, int z, int y, int x, const Stenc
   return hipErrorInvalidValue;
 }
 
-// Two-step: the line-aligned tile when every output row starts on a 128-byte
-// line.
 template <bool FUSED, typename T>
 hipError_t launch_lcp3d_any(const Planes6& src, int64_t nz, int64_t ny, int64_t nx,
                             const StencilCoef3& k, const IsoChunk& iso, int kc, float* out_k0,
                             int64_t pitch, int64_t plane, hipStream_t s) {
   if (!lcp3d_slice_fits(ny, nx, sizeof(T))) return hipErrorInvalidValue;
   const int z = int(nz), y = int(ny), x = int(nx);
-  if constexpr (!FUSED) {
-    if (rows_on_lines(out_k0, pitch, plane))
-      return launch_lcp3d_kcs<FUSED, true, T>(src, z, y, x, k, iso, kc, out_k0, pitch, plane, s);
-  }
-  return launch_lcp3d_kcs<FUSED, false, T>(src, z, y, x, k, iso, kc, out_k0, pitch, plane, s);
+  // fused: wide strips; two-step: the line-aligned tile
+  const bool alt = FUSED ? lcp3d_wide_strips(nx, sizeof(T), kc) : rows_on_lines(out_k0, pitch, plane);
+  return alt ? launch_lcp3d_kcs<FUSED, !FUSED, FUSED, T>(src, z, y, x, k, iso, kc, out_k0, pitch,
+                                                         plane, s)
+             : launch_lcp3d_kcs<FUSED, false, false, T>(src, z, y, x, k, iso, kc, out_k0, pitch,
+                                                        plane, s);
 }
 
 }  // namespace

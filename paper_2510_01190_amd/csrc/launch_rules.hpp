@@ -175,4 +175,22 @@ constexpr int batch_band_rows(const Tiles& tiles, bool fused, int in_bytes, bool
   return by_tiles <= tallest && 20 * cost(by_tiles) <= 21 * least ? by_tiles : best;
 }
 
+// Fused 3D LCP: strips of 63 cells, whose end lanes load the neighbours that
+// they miss, instead of 61 with two halo lanes, where they save a strip: always
+// of float32, where U's extra loads are the smaller part; of 16-bit storage at
+// 3, 4 and 7 isovalues up to 4 strips of 61, at 8 up to 6 (there the registers of
+// the extra loads cost a wave per SIMD).  61 / 63 cells against the kernels of 63
+// and 64 cells that loaded every lane's neighbours, 1 / 4 / 8 / 16 isovalues into
+// dense maps: float32 256x512x64 (2 / 1 strips) 1.15 / 0.98, 1.18 / 0.98, 1.42 /
+// 1.05, 1.48 / 1.01; 200x300x251 (5 / 4) 1.04 / 1.00, 1.08 / 1.02, 1.02 / 0.92, 1.12 /
+// 0.92; 300x400x500 (9 / 8) 1.01 / 0.99, 1.03 / 0.99, 0.97 / 0.94, 0.98 / 0.92;
+// bfloat16 200x300x126 (3 / 2) 0.91 / 0.77, 0.90 / 0.83, 1.15 / 0.95, 1.24 / 0.94, but
+// 300x400x500 0.94 / 0.99 at 4, 0.96 / 0.98 at 8.
+constexpr bool lcp3d_wide_strips(int64_t nx, int in_bytes, int n_iso) {
+  const int64_t narrow = (nx - 1 + 60) / 61, wide = (nx - 1 + 62) / 63;
+  if (wide >= narrow) return false;
+  if (in_bytes == 4) return true;
+  return n_iso == 3 || n_iso == 4 || n_iso == 7 ? narrow <= 4 : n_iso != 8 || narrow <= 6;
+}
+
 }  // namespace pdiv

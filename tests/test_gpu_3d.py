@@ -339,3 +339,32 @@ def test_divergence_shapes_3d(shape, dt):
         last = hi if hi == shape[0] else hi - 1
         for w, p in zip(whole, part):
             assert torch.equal(w[first:last], p[first - lo:last - lo]), (lo, hi)
+
+
+@pytest.mark.parametrize("nx", [63, 64, 65, 124, 126, 127, 128, 188, 190, 251])
+@pytest.mark.parametrize("dt", ["f32", "f16"])
+def test_wide_strips_3d(nx, dt):
+    """Fused rows of which strips of 63 cells need fewer than strips of 61 (and
+    widths just off those): the end lanes' loaded neighbours inside the row and
+    at both boundaries, every isovalue count's kernel, rows of few bands and
+    many, bitwise the two-step maps, with NaN and infinities at strip ends,
+    nothing written outside the cells."""
+    shape = (6, 11, nx)
+    rng = np.random.default_rng(nx)
+    ts = [dev(rng.normal(0, 0.3, shape) if q % 2 == 0 else rng.uniform(0.02, 0.2, shape), dt)
+          for q in range(6)]
+    ts[0][2, 3, nx - 1] = float("nan")
+    ts[0][4, 7, 0] = float("inf")
+    for x in (60, 61, 62, 63, 64):
+        if x < nx:
+            ts[0][x % 6, (3 * x) % 11, x] = float("nan") if x % 2 else float("-inf")
+            ts[1][(x + 3) % 6, (5 * x) % 11, x] = float("nan")
+    div = P.divergence_gaussian_3d(*ts)
+    for k in (1, 2, 3, 4, 5, 6, 7, 8, 16):
+        iso = np.linspace(-0.4, 0.4, k).astype(np.float32)
+        want = P.lcp_3d(*div, iso)
+        view, buf = _padded(k, shape, pitch=nx + 2, gap=32)
+        P.lcp_3d_from_moments(*ts, iso, out=view)
+        assert torch.equal(torch.isnan(view), torch.isnan(want)), k
+        assert torch.equal(torch.nan_to_num(view, nan=-1.0), torch.nan_to_num(want, nan=-1.0)), k
+        assert _padding_untouched(view, buf), k
