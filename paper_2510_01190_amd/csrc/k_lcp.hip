@@ -216,14 +216,15 @@ hipError_t launch_kc(const void* p0, const void* p1, const void* p2, const void*
   const int64_t n_cells = int64_t(ny - 1) * (nx - 1);
   const bool lines = rows_on_lines(out, pitch, plane);
   // the LDS check runs the staged tile at every size
-  const bool paired = use_paired_tile(FUSED, lines, KC, n_cells) ||
+  const bool paired = use_paired_tile(FUSED, lines, sizeof(T), KC, ny, nx) ||
                       (FUSED && std::is_same<T, float>::value && shape.poison);
   const bool unaligned = paired && !lines;  // fused only: default store policy
   const int cells = cells_per_wave(paired);
   const int n_strips = (nx - 1 + cells - 1) / cells;
   const int band_rows = shape.band_rows > 0
                             ? shape.band_rows
-                            : lcp_band_rows(n_strips, ny - 1, paired, FUSED, KC);
+                            : lcp_band_rows(n_strips, ny - 1, paired, FUSED, lines,
+                                            sizeof(T), KC);
   const int n_bands = (ny - 1 + band_rows - 1) / band_rows;
   const int64_t waves = static_cast<int64_t>(n_strips) * n_bands;
   if (!launch_fits((waves + kWavesPerBlock - 1) / kWavesPerBlock, kBlock))

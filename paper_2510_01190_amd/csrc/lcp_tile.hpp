@@ -699,79 +699,6 @@ inline bool rows_on_lines(const float* out, int64_t pitch, int64_t plane) {
   return (reinterpret_cast<uintptr_t>(out) % 128 == 0) && (pitch % 32 == 0) && (plane % 32 == 0);
 }
 
-// Layout choice, from float32 maps of 300^2 to 8192^2 cells at the best band
-// height of each tile, three sets of buffers in turn (split against paired,
-// us).  The paired tile's whole-line stores pay once the maps outgrow the
-// caches; its seam step and, fused, its staged rows cost more than they
-// save below that.
-//   fused, rows on lines: at 1, 2, 4 isovalues 721x1440 6.8 / 9.5, 8.1 / 10.8,
-//     11.0 / 13.1, 1448^2 16.2 / 19.4 at 4, 2047x3001 28.0 / 25.5, 34.4 /
-//     30.9, 49.6 / 43.3: paired from 2^22 cells; at 8 and more 721x1440 15.5 /
-//     17.3 (16: 27.1 / 27.1), 1448^2 32.5 / 26.8 and 55.7 / 42.8: paired from
-//     1.25 M cells.
-//   fused, other rows (default store policy): 2047x3001 at 1, 4, 8, 16
-//     isovalues 27.8 / 28.7, 48.9 / 49.1, 78.2 / 76.3, 135.5 / 131.7;
-//     3000x3500 49.4 / 52.3, 82.7 / 85.4, 125.9 / 131.4, 233 / 227; 4096^2
-//     77.8 / 74.4, 130.9 / 122, 202 / 190, 357 / 334: paired from 12 M cells,
-//     at 12 and more isovalues from 6 M.
-//   two-step, rows on lines: 721x1440 4.4 / 5.1 at 1 isovalue, 9.5 / 8.4 at 4,
-//     24.3 / 23.0 at 16; 4096^2 43.9 / 44.3, 99.5 / 83.1, 339 / 268: paired
-//     except at 1 isovalue and on the smallest maps (300^2: equal).
-//   two-step, other rows: split only.
-inline bool use_paired_tile(bool fused, bool lines, int kc, int64_t cells) {
-  constexpr int64_t kM = 1000000;
-  if (!fused) return lines && kc >= 2 && cells >= kM / 4;
-  if (lines) return cells >= (kc >= 8 ? kM * 5 / 4 : int64_t(1) << 22);
-  return cells >= (kc >= 12 ? 6 * kM : 12 * kM);
-}
-
-// Cell rows per wave band.  A band re-evaluates one corner row and re-reads
-// two input rows, so tall bands do less work; but a wave walks its band row
-// by row, so a grid of few tall bands leaves SIMDs idle while a few waves
-// walk (500x500, 1 isovalue, fused: 15.9 us with 32-row bands, 9.3 / 6.0 /
-// 4.3 / 3.6 / 3.4 us with 16 / 8 / 4 / 2 / 1).
-//
-// Grids of less than eight 8-row bands per SIMD: the time goes with the rows
-// that the fullest of the 1024 SIMDs walks, a band's own redundant work at
-// half a row, n (b + 1/2) for n = ceil(waves / 1024).  1448x1448, 4 isovalues
-// into dense maps, 2 ... 10 rows: 18.1 17.3 18.1 16.7 15.7 17.0 18.0 15.5 16.2 us
-// (n = 9 6 5 4 3 3 3 2 2), 12 / 14 / 16: 17.8 / 19.8 / 21.5.  A SIMD's only wave
-// hides no latency (721x1440, 8 isovalues, 9 rows: 17.0 us, 15.2 with 3), and
-// with few isovalues two hide less than three (1000x1000, 2 isovalues, 4 rows:
-// 8.3 us, 7.8 with 2).  Against the tallest band that gives a number of waves
-// (6000, 3000 and 1500 for 8, 4 and 2 rows), over 208 sizes, counts and
-// layouts from 300x300 to 2047x3001 the times fall by 2.3% on average: 721x1440
-// 16.2 to 14.8 us at 8 isovalues and 29.6 to 25.8 at 16, 1448^2 17.1 to 15.6 at 4
-// and, on lines, 44.9 to 40.5 at 16, 2047x3001 on lines 47.7 to 44.4 at 4.  Taller
-// bands than 8 rows gain nothing where the stores are most of the work, the
-// two-step path and many isovalues on rows that start inside a line
-// (1500x4000, 16 isovalues into dense maps, 16 rows: 142.7 us, 137.5 with 8).
-//
-// Larger grids, whose SIMDs even out: the split tile gains nothing from more
-// than 8 rows at any size (8192^2, 16 isovalues, two-step: 1.30 ms with 8 rows,
-// 1.41 / 1.44 / 1.50 with 16 / 32 / 64); the paired one takes up to 64 (8192^2 fused,
-// 16 isovalues: 1.106 ms, 1.125 / 1.174 / 1.176 with 32 / 16 / 8; 5792^2: 656,
-// 601, 593, 608 us with 64 / 32 / 16 / 8; 4096^2 into dense maps 343, 334, 337,
-// 348 us).
-inline int lcp_band_rows(int64_t strips, int64_t rows, bool paired, bool fused, int kc) {
-  auto waves = [&](int b) { return strips * ((rows + b - 1) / b); };
-  if (waves(8) >= 8000) {
-    if (paired && waves(64) >= 8000) return 64;
-    if (paired && waves(32) >= 4000) return 32;
-    if (paired && waves(16) >= 6000) return 16;
-    return 8;
-  }
-  const int tallest = fused && (paired || kc < 12) ? 16 : 8;
-  int64_t least = INT64_MAX;
-  int best = 1;
-  for (int b = 1; b <= tallest; ++b) {
-    const int64_t n = (waves(b) + kSimds - 1) / kSimds;
-    const int64_t cost = n * (2 * b + 1) * (n == 1 ? 40 : n == 2 && kc < 8 ? 23 : 20);
-    if (cost < least) least = cost, best = b;
-  }
-  return best;
-}
-
 // The tile of layout PAIRED.  STREAM: non-temporal stores (for rows that
 // start on 128-byte lines; the unaligned paired tile of the fused kernel
 // stores with the default policy).

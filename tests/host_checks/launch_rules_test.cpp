@@ -281,9 +281,48 @@ void check_strips() {
     check(!pdiv::lcp3d_wide_strips(nx, 4, 4), "strips even", nx, 0, 0);
 }
 
+// Closed-form LCP, fused, at sizes where an earlier rule lost: the layout, and
+// the band height where it decides.
+struct TileChoice {
+  bool lines;
+  int bytes, slots, ny, nx;
+  bool paired;
+  int band;  // 0: any
+};
+
+void check_tiles() {
+  const TileChoice choices[] = {
+      {false, 2, 12, 2129, 1804, true, 0},  // split 100 us, paired 69
+      {false, 2, 12, 1021, 1531, true, 0},  // 35.8, 30.6
+      {false, 2, 12, 721, 1440, false, 0},  // 20.2, 28.2
+      {false, 2, 1, 2123, 6863, false, 0},  // 46.8, 59.5
+      {false, 2, 4, 2123, 6863, false, 0},  // 92.5, 99.4
+      {false, 2, 4, 8192, 8192, true, 0},   // 412, 382
+      {false, 2, 2, 8000, 8191, false, 0},  // 244, 270
+      {false, 4, 8, 947, 7889, true, 32},   // 93.0 split, 89.1 with 32 rows, 94.5 with 16
+      {false, 4, 2, 947, 7889, true, 32},   // 42.1, 41.0
+      {false, 4, 4, 3000, 3500, false, 0},  // 76.6, 87.4
+      {false, 4, 1, 2123, 6863, true, 32},  // 67.6 with 32 rows, 70.3 with 16
+      {false, 2, 16, 2056, 6868, true, 16}, // 280 with 16 rows, 300 with 32
+      {true, 4, 1, 1668, 4457, true, 32},   // 32.5 with 32 rows, 34.4 with 10
+      {true, 4, 4, 4096, 4097, true, 64},   // 110 with 64 rows, 115.5 with 32
+      {true, 2, 4, 4096, 4097, true, 32},   // 96.3 with 32 rows, 97.1 with 64
+      {true, 4, 16, 8192, 8192, true, 64},  // 1.106 ms with 64 rows, 1.125 with 32
+  };
+  for (const TileChoice& c : choices) {
+    const bool paired = pdiv::use_paired_tile(true, c.lines, c.bytes, c.slots, c.ny, c.nx);
+    check(paired == c.paired, "tile", c.ny, c.nx, c.slots);
+    const int cells = paired ? 128 : 126;
+    const int band = pdiv::lcp_band_rows((c.nx - 1 + cells - 1) / cells, c.ny - 1, paired, true,
+                                         c.lines, c.bytes, c.slots);
+    check(c.band == 0 || band == c.band, "band", c.ny, c.nx, band);
+  }
+}
+
 }  // namespace
 
 int main() {
+  check_tiles();
   check_strips();
   check_batch();
   check_contour();
