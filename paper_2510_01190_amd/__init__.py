@@ -142,9 +142,12 @@ def _torch():
 def _stream():
     """The current device's current stream as a raw handle.  The raw lookup
     takes 0.2 us; building the Stream object takes 2.8, a quarter of a small
-    call."""
-    c = _torch()._C
-    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    call.  A torch without the raw lookup's names takes the Stream object."""
+    torch = _torch()
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _dtype_code(t) -> int:

@@ -312,3 +312,16 @@ def test_contour_segments_rejects_bad_arguments():
     _expect_invalid(call(FAKE, 1, 8, 8, c, FAKE, NUL, 4, NUL), "segments is NULL")
     _expect_invalid(call(FAKE, 1, 8, 8, c, FAKE, FAKE, -1, NUL), "max_segments")
     _expect_invalid(call(FAKE, 1, 8, 8, c, FAKE, ctypes.c_void_p(0x1004), 4, NUL), "aligned")
+
+
+def test_stream_handle_without_the_raw_lookup(monkeypatch):
+    """The raw stream lookup is no public torch name: a torch without it gives
+    the handle by its Stream object."""
+    from types import SimpleNamespace as NS
+    stream = NS(cuda_stream=0x1234)
+    cuda = NS(current_stream=lambda: stream)
+    monkeypatch.setattr(P, "_torch", lambda: NS(_C=NS(), cuda=cuda))
+    assert P._stream() == 0x1234
+    raw = NS(_cuda_getDevice=lambda: 3, _cuda_getCurrentRawStream=lambda d: 100 + d)
+    monkeypatch.setattr(P, "_torch", lambda: NS(_C=raw, cuda=cuda))
+    assert P._stream() == 103
