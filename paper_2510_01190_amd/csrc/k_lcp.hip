@@ -213,11 +213,15 @@ template <int KC, bool FUSED, bool ALL, typename T>
 hipError_t launch_kc(const void* p0, const void* p1, const void* p2, const void* p3, int ny,
                      int nx, const StencilCoef& k, const IsoChunk& iso, int n_store, float* out,
                      int64_t pitch, int64_t plane, LcpShape shape, hipStream_t s) {
+  // where use_paired_tile can choose the paired tile on lines, on other rows
+  constexpr bool kOnLines = FUSED || KC >= 2;
+  constexpr bool kOnOther = FUSED && (sizeof(T) == 4 || KC >= 3);
   const int64_t n_cells = int64_t(ny - 1) * (nx - 1);
   const bool lines = rows_on_lines(out, pitch, plane);
   // the LDS check runs the staged tile at every size
-  const bool paired = use_paired_tile(FUSED, lines, sizeof(T), KC, ny, nx) ||
-                      (FUSED && std::is_same<T, float>::value && shape.poison);
+  const bool paired = (lines ? kOnLines : kOnOther) &&
+                      (use_paired_tile(FUSED, lines, sizeof(T), KC, ny, nx) ||
+                       (FUSED && std::is_same<T, float>::value && shape.poison));
   const bool unaligned = paired && !lines;  // fused only: default store policy
   const int cells = cells_per_wave(paired);
   const int n_strips = (nx - 1 + cells - 1) / cells;
@@ -247,7 +251,7 @@ hipError_t launch_kc(const void* p0, const void* p1, const void* p2, const void*
       return hipGetLastError();
     }
   }
-  if constexpr (FUSED) {
+  if constexpr (kOnOther) {
     if (unaligned) {
       static const size_t lds =
           two_waves_per_simd_lds(lcp_kernel_paired<KC, FUSED, ALL, T, false, false>);
@@ -259,22 +263,24 @@ hipError_t launch_kc(const void* p0, const void* p1, const void* p2, const void*
       return hipGetLastError();
     }
   }
-  if (paired) {
-    size_t lds = 0;
-    if constexpr (FUSED && KC <= 4) {
-      static const size_t two = two_waves_per_simd_lds(lcp_kernel_paired<KC, FUSED, ALL, T>);
-      if (n_cells >= kTwoWaveCells) lds = two;
+  if constexpr (kOnLines) {
+    if (paired) {
+      size_t lds = 0;
+      if constexpr (FUSED && KC <= 4) {
+        static const size_t two = two_waves_per_simd_lds(lcp_kernel_paired<KC, FUSED, ALL, T>);
+        if (n_cells >= kTwoWaveCells) lds = two;
+      }
+      hipLaunchKernelGGL((lcp_kernel_paired<KC, FUSED, ALL, T>), dim3(blocks), dim3(kBlock), lds,
+                         s, static_cast<const T*>(p0), static_cast<const T*>(p1),
+                         static_cast<const T*>(p2), static_cast<const T*>(p3), ny, nx, k, iso,
+                         n_store, out, plane, pitch, band_rows, n_strips, n_bands);
+      return hipGetLastError();
     }
-    hipLaunchKernelGGL((lcp_kernel_paired<KC, FUSED, ALL, T>), dim3(blocks), dim3(kBlock), lds, s,
-                       static_cast<const T*>(p0), static_cast<const T*>(p1),
-                       static_cast<const T*>(p2), static_cast<const T*>(p3), ny, nx, k, iso, n_store,
-                       out, plane, pitch, band_rows, n_strips, n_bands);
   }
-  else
-    hipLaunchKernelGGL((lcp_kernel_split<KC, FUSED, ALL, T>), dim3(blocks), dim3(kBlock), 0, s,
-                       static_cast<const T*>(p0), static_cast<const T*>(p1),
-                       static_cast<const T*>(p2), static_cast<const T*>(p3), ny, nx, k, iso, n_store,
-                       out, plane, pitch, band_rows, n_strips, n_bands);
+  hipLaunchKernelGGL((lcp_kernel_split<KC, FUSED, ALL, T>), dim3(blocks), dim3(kBlock), 0, s,
+                     static_cast<const T*>(p0), static_cast<const T*>(p1),
+                     static_cast<const T*>(p2), static_cast<const T*>(p3), ny, nx, k, iso,
+                     n_store, out, plane, pitch, band_rows, n_strips, n_bands);
   return hipGetLastError();
 }
 

@@ -88,14 +88,19 @@ __global__ __launch_bounds__(kBlock) void batch_kernel(const BatchField* __restr
 template <bool FUSED, bool PAIRED, typename T>
 const void* kernel_for(int kc) {
   switch (kc) {
-    case 1: return reinterpret_cast<const void*>(&batch_kernel<1, FUSED, PAIRED, T>);
-    case 2: return reinterpret_cast<const void*>(&batch_kernel<2, FUSED, PAIRED, T>);
-    case 3: return reinterpret_cast<const void*>(&batch_kernel<3, FUSED, PAIRED, T>);
-    case 4: return reinterpret_cast<const void*>(&batch_kernel<4, FUSED, PAIRED, T>);
-    case 6: return reinterpret_cast<const void*>(&batch_kernel<6, FUSED, PAIRED, T>);
     case 8: return reinterpret_cast<const void*>(&batch_kernel<8, FUSED, PAIRED, T>);
     case 12: return reinterpret_cast<const void*>(&batch_kernel<12, FUSED, PAIRED, T>);
     case 16: return reinterpret_cast<const void*>(&batch_kernel<16, FUSED, PAIRED, T>);
+  }
+  // (the server's two-step launches take the paired tile from 8 slots)
+  if constexpr (FUSED || !PAIRED) {
+    switch (kc) {
+      case 1: return reinterpret_cast<const void*>(&batch_kernel<1, FUSED, PAIRED, T>);
+      case 2: return reinterpret_cast<const void*>(&batch_kernel<2, FUSED, PAIRED, T>);
+      case 3: return reinterpret_cast<const void*>(&batch_kernel<3, FUSED, PAIRED, T>);
+      case 4: return reinterpret_cast<const void*>(&batch_kernel<4, FUSED, PAIRED, T>);
+      case 6: return reinterpret_cast<const void*>(&batch_kernel<6, FUSED, PAIRED, T>);
+    }
   }
   return nullptr;
 }
