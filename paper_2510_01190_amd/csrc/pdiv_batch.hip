@@ -267,13 +267,11 @@ void tune_save() {
   out << "}\n";
 }
 
+// The field table to the device.  Its size is the batch's own, so a shape that
+// is tried writes over the last one's table (whose launches have ended).
 pdiv_status upload(pdiv_batch b) {
-  if (b->dev) {
-    if (hipFree(b->dev) != hipSuccess) return PDIV_ERR_DEVICE;
-    b->dev = nullptr;
-  }
   const size_t bytes = sizeof(BatchField) * b->fields.size();
-  if (hipMalloc(&b->dev, bytes) != hipSuccess) {
+  if (!b->dev && hipMalloc(&b->dev, bytes) != hipSuccess) {
     b->dev = nullptr;
     (void)hipGetLastError();
     invalid("batch: cannot allocate the %zu-byte field table", bytes);
@@ -336,7 +334,6 @@ void tuned_shape(pdiv_batch b, const Tune& t) {
 // Launches of a shape on the batch itself (they write the batch's own outputs),
 // timed by a pair of events.
 struct Timer {
-  static constexpr int kLaunches = 3;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   int table_rows = 0, table_paired = -1;  // the shape of the uploaded table
 
@@ -344,8 +341,8 @@ struct Timer {
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
   }
-  // us per launch of the shape t, into *us
-  pdiv_status time(pdiv_batch b, const Tune& t, hipStream_t s, float* us) {
+  // us per launch of the shape t over `launches` of them, into *us
+  pdiv_status time(pdiv_batch b, const Tune& t, int launches, hipStream_t s, float* us) {
     if ((!e0 && hipEventCreate(&e0) != hipSuccess) || (!e1 && hipEventCreate(&e1) != hipSuccess))
       return device_status(hipGetLastError(), "autotune events");
     tuned_shape(b, t);
@@ -361,19 +358,19 @@ struct Timer {
     };
     hipError_t e = launch();  // warm
     e = e != hipSuccess ? e : hipEventRecord(e0, s);
-    for (int r = 0; r < kLaunches && e == hipSuccess; ++r) e = launch();
+    for (int r = 0; r < launches && e == hipSuccess; ++r) e = launch();
     e = e != hipSuccess ? e : hipEventRecord(e1, s);
     e = e != hipSuccess ? e : hipEventSynchronize(e1);
     float ms = 0;
     e = e != hipSuccess ? e : hipEventElapsedTime(&ms, e0, e1);
-    *us = ms * (1000.0f / kLaunches);
+    *us = ms * 1000.0f / float(launches);
     return device_status(e, "autotune launch");
   }
 };
 
 // Times the candidate shapes and keeps the fastest: the rule's shape; both tile
 // layouts when every output row starts on a line, with bands of 8 to 64 rows on
-// four grids; and bands of 1 to 4 rows, where 8-row ones would be few (less than
+// three grids; and bands of 1 to 4 rows, where 8-row ones would be few (less than
 // eight a SIMD).  A band of less than 8 rows has to be 2 us faster, a launch's
 // own spread, as short bands read more.  (12 fields of 64 to 300 a side at 12
 // isovalues: 13 us with the rule's 2 rows, 28 with the best of 8 to 64.)
@@ -400,8 +397,8 @@ pdiv_status autotune(pdiv_batch b, hipStream_t s) {
   if (known) {
     if (win.band_rows != 0) {
       float kept = 0, ruled = 0;
-      if ((st = timer.time(b, win, s, &kept)) != PDIV_OK) return st;
-      if ((st = timer.time(b, rule, s, &ruled)) != PDIV_OK) return st;
+      if ((st = timer.time(b, win, 1, s, &kept)) != PDIV_OK) return st;
+      if ((st = timer.time(b, rule, 1, s, &ruled)) != PDIV_OK) return st;
       if (1.05f * ruled + kSpread < kept) win = rule;
     }
     tuned_shape(b, win);
@@ -410,14 +407,14 @@ pdiv_status autotune(pdiv_batch b, hipStream_t s) {
   std::vector<Tune> candidates{rule};
   for (int paired = 0; paired <= (b->lines ? 1 : 0); ++paired) {
     for (int br : {8, 16, 32, 64})
-      for (int gm : {1, 2, 4, kGridAll}) candidates.push_back({br, gm, paired});
+      for (int gm : {2, 4, kGridAll}) candidates.push_back({br, gm, paired});
     if (batch_tiles(b->fields, paired != 0, 8) < 8 * kSimds)
       for (int br : {1, 2, 3, 4}) candidates.push_back({br, kGridAll, paired});
   }
   float best = 1e30f;
   for (const Tune& t : candidates) {
     float us = 0;
-    if ((st = timer.time(b, t, s, &us)) != PDIV_OK) return st;
+    if ((st = timer.time(b, t, 3, s, &us)) != PDIV_OK) return st;
     if (b->band_rows < 8) us += kSpread;
     if (us < best) {
       best = us;
