@@ -347,8 +347,9 @@ typedef struct pdiv_batch_s* pdiv_batch;
 
 /* Flags for pdiv_batch_create. */
 #define PDIV_BATCH_GRAPH 1u    /* capture the launch in a hipGraph, replay it     */
-#define PDIV_BATCH_AUTOTUNE 2u /* time the candidate tile shapes on this batch and
-                                  keep the fastest (cached per shape class)       */
+#define PDIV_BATCH_AUTOTUNE 2u /* time the default shape and others on this batch
+                                  and keep the fastest, cached per shape class (a
+                                  cached shape is timed against the default's)    */
 
 /* Builds the tile table for fields_host[0..n) (host array, copied), uploads it,
  * and with PDIV_BATCH_GRAPH captures the launch on `stream`.  The batch owns
@@ -407,8 +408,8 @@ pdiv_status pdiv_server_create(size_t hbm_budget, int32_t n_streams, pdiv_server
  * given, [ny][nx] each): uploaded, reduced to its divergence Gaussians
  * (Eq. 2-3) and kept resident under id.  The host planes are copied (on
  * several threads for large fields) into pinned staging before the call
- * returns; the call waits while the staging pool is full.  Returns PDIV_ERR_BUSY if the field can never fit the budget;
- * otherwise the request waits for room (evicting least recently used fields
+ * returns; the call waits while the staging pool is full.  Returns
+ * PDIV_ERR_BUSY if the field can never fit the budget; otherwise the request waits for room (evicting least recently used fields
  * that no pending request names). */
 pdiv_status pdiv_server_put_field(pdiv_server srv, uint64_t id, const void* mean_u_host,
                                   const void* var_u_host, const void* mean_v_host,

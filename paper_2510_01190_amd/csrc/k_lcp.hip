@@ -43,19 +43,21 @@ constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / kWave;
 
 // Eq. 2-3 at every vertex.  A wave walks rows_per_thread rows of a strip of
-// columns and keeps V's rows clamp(j-1), j, clamp(j+1) in a register window,
-// so each V row is loaded once.  U's x neighbours depend on the storage:
+// columns and keeps V's rows clamp(j-1), j, clamp(j+1) in a register window;
+// two rows per wave load four V rows, the outer two from the caches (the
+// launcher says why).  Bound by HBM: 5.4 TB/s of its algorithmic bytes at
+// 8192^2 float32.  U's x neighbours depend on the storage:
 //   32-bit  the strip is 64 columns; each lane loads its two neighbours,
 //           which the L1 serves from the lines of the row already in flight;
 //   16-bit  the strip is 62 columns in 64 lanes (lanes 0 and 63 hold the x
 //           halo); each lane loads only its own column and takes the
 //           neighbours from the adjacent lanes through DPP, with every lane
 //           active, so no load straddles a cache line.
-// Measured at 8192^2: the DPP form takes 0.39 ms for 16-bit storage against
-// 0.55 ms with neighbour loads, but 0.49 ms for 32-bit against 0.36 ms (its
-// 62-column strips put the row segments off cache-line boundaries).  Either
-// way the operands are those of a straight evaluation with clamped
-// neighbours.
+// At 8192^2 it takes 0.285 ms for 16-bit and 0.297 ms for 32-bit storage.  The
+// choice was measured on longer walks: 16-bit 0.39 ms through DPP, 0.55 with
+// neighbour loads; 32-bit 0.49 and 0.36 (62-column strips put its row segments
+// off cache-line boundaries).  Either way the operands are those of a straight
+// evaluation with clamped neighbours.
 // NT: non-temporal stores.
 template <typename T, bool NT>
 __global__ __launch_bounds__(kBlock) void divergence_kernel(const T* __restrict__ mu,
@@ -190,7 +192,8 @@ __global__ __launch_bounds__(kBlock) void lcp_kernel_split(
 // of the three its registers allow.  The fused kernel's stores into rows that
 // start inside a 128-byte line, and its launches at up to 4 isovalues on large
 // maps, run faster with fewer waves writing at once (8192^2 at 16 isovalues
-// into dense maps: 1.30 against 1.37 ms; at 8: 0.71 against 0.76 ms;
+// into dense maps: 1.30 against 1.37 ms where the two were compared, 1.35 as
+// it stands; at 8: 0.71 against 0.76 ms;
 // line-aligned rows at 4 isovalues: 0.413 against 0.425 ms; line-aligned at
 // 16: unchanged).  Line-aligned maps of fewer cells fit the caches better and
 // want the waves (at 1 / 4 isovalues 2047x3001 29.5 / 45.6 us at two waves,

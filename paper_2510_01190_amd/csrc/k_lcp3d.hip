@@ -40,10 +40,9 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / 64;
-// (z slices per divergence3d wave, each chunk re-reading W at its two ends:
-// div3_shape.)
-// What the grid check counts (launches take more slices where those would not
-// fit).
+// z slices per divergence3d wave (each chunk re-reads W at its two ends) come
+// from div3_shape; the grid check counts this many, and a launch that would not
+// fit takes them.
 constexpr int kCheckedZChunk = 12;
 
 // Eq. 2-3 with the z term at one vertex; the neighbours are already clamped
@@ -580,19 +579,21 @@ hipError_t launch_lcp3d_kc(const Planes6& src, int nz, int ny, int nx, const Ste
     band_rows *= 2;
   } while (n_bands > 1);
   if (!launch_fits(blocks, kBlock)) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((lcp3d_kernel<KC, LZ, FUSED, LINES, WIDE, ALL, T>), dim3(unsigned(blocks)), dim3(kBlock),
-                     0, s, src, nz, ny, nx, k, iso, n_store, out, pitch, plane, n_groups, n_strips,
-                     n_bands, band_rows);
+  hipLaunchKernelGGL((lcp3d_kernel<KC, LZ, FUSED, LINES, WIDE, ALL, T>), dim3(unsigned(blocks)),
+                     dim3(kBlock), 0, s, src, nz, ny, nx, k, iso, n_store, out, pitch, plane,
+                     n_groups, n_strips, n_bands, band_rows);
   return hipGetLastError();
 }
 
 }  // namespace
 
-// What the grid check counts: bands of 16 rows (launches take taller ones
-// where those would not fit).
+// What the grid check counts, chosen once so that the sizes refused stay the
+// same whatever the launches use: bands of 16 rows (launches take taller ones
+// where those would not fit), 4 or 2 cell layers a wave (launches take 4 or 3)
+// and strips of 63 cells (launches take 61 to 64).
 constexpr int kCheckedBandRows = 16;
 int64_t lcp3d_blocks(int64_t nz, int64_t ny, int64_t nx, int kc) {
-  const int lz = kc <= 4 ? 4 : 2;  // launches above 4 isovalues take 3 or 4
+  const int lz = kc <= 4 ? 4 : 2;
   const int64_t waves = ((nz - 1 + lz - 1) / lz) * ((nx - 1 + 62) / 63) *
                         ((ny - 1 + kCheckedBandRows - 1) / kCheckedBandRows);
   return (waves + kWavesPerBlock - 1) / kWavesPerBlock;

@@ -289,7 +289,9 @@ __global__ __launch_bounds__(kBlock) void mc_kernel(const T* __restrict__ mu,
     for (int w = 0; w < kWords; ++w) sliced_flush(sl[w]);
   }
   // each form in a run of its own: a branch at every count made a block's end a
-  // fifth longer (33x33, 1 sample, 16 isovalues 18.0 against 15.5 us)
+  // fifth longer (33x33, 1 sample, 16 isovalues 18.0 against 15.5 us; 1040x1040,
+  // 60 samples 284 against 232; the sample loop is then scheduled otherwise, and
+  // 1000 samples at 8 isovalues take 2043 us instead of 2034 at 721x1440)
   auto put_all = [&](auto split) {
 #pragma unroll
     for (int m = 0; m < CPT; ++m) {
@@ -301,7 +303,8 @@ __global__ __launch_bounds__(kBlock) void mc_kernel(const T* __restrict__ mu,
         for (int q = 0; q < KC; ++q) {
           if (q < n_store) {
             if constexpr (RANK)
-              put_count<split.value>(o + rt.perm[q] * plane, sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
+              put_count<split.value>(o + rt.perm[q] * plane,
+                                     sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
             else
               put_count<split.value>(o + q * plane, cnt[m][q], fs);
           }
@@ -489,7 +492,8 @@ __global__ __launch_bounds__(kBlock) void mc_vertex_kernel(const T* __restrict__
         for (int q = 0; q < KC; ++q) {
           if (q < n_store) {
             if constexpr (RANK)
-              put_count<split.value>(o + rt.perm[q] * plane, sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
+              put_count<split.value>(o + rt.perm[q] * plane,
+                                     sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
             else
               put_count<split.value>(o + q * plane, cnt[m][q], fs);
           }

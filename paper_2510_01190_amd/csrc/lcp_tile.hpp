@@ -29,19 +29,19 @@
 // by the neighbour (XCD-contiguous strips share an L2).  It runs the same
 // arithmetic with the LDS-staged rows, launched at two waves per SIMD (the
 // launcher reserves LDS: fewer waves writing at once complete more shared
-// lines in L2); at 8192^2 into dense maps it takes 0.45 / 0.71 / 1.30 ms at
-// 4 / 8 / 16 isovalues (0.47 / 0.76 / 1.37 ms at three waves per SIMD)
-// against 0.41 / 0.65 / 1.11 ms into line-aligned rows (with the streaming
-// policy 0.578 / 0.974 / 1.760 ms at three waves; the split tile 0.49 / 0.77 /
-// 1.34 ms).
+// lines in L2).  At 8192^2 into dense maps it takes 0.46 / 0.73 / 1.35 ms at 4 /
+// 8 / 16 isovalues, into line-aligned rows 0.42 / 0.66 / 1.12.  Where the
+// variants were compared it took 0.45 / 0.71 / 1.30, at three waves per SIMD
+// 0.47 / 0.76 / 1.37, with the streaming policy at three waves 0.578 / 0.974 /
+// 1.760, and the split tile 0.49 / 0.77 / 1.34.
 //
 // Split (lcp_tile_split), for the other outputs (the two-step path on rows
 // that start inside a line, and maps that the caches hold, where whole-line
-// stores gain nothing: use_paired_tile below): a wave owns 127 vertex columns, the 126 cells [x0, x0+126),
-// x0 = 126 strip.  Lane L holds columns A = x0+L and B = x0+63+L (lane 63's
-// A repeats lane 0's B), forms cells (A, A+1) and (B, B+1) with the right
-// pair from lane L+1, and lanes 0..62 write 63 consecutive cells per store.
-// No seam step.
+// stores gain nothing: use_paired_tile in launch_rules.hpp): a wave owns 127
+// vertex columns, the 126 cells [x0, x0+126), x0 = 126 strip.  Lane L holds
+// columns A = x0+L and B = x0+63+L (lane 63's A repeats lane 0's B), forms
+// cells (A, A+1) and (B, B+1) with the right pair from lane L+1, and lanes
+// 0..62 write 63 consecutive cells per store.  No seam step.
 #pragma once
 
 #include <cstdint>

@@ -648,8 +648,8 @@ pdiv_status check_layout3(int64_t row_pitch, int64_t plane_stride, int64_t nz, i
   return PDIV_OK;
 }
 
-// The isovalues in chunks of lcp3d_chunk, one launch each.  planes is null for the two-step form (dm,
-// dv given), else the six moment volumes.
+// The isovalues in chunks of lcp3d_chunk, one launch each.  planes is null for
+// the two-step form (dm, dv given), else the six moment volumes.
 pdiv_status lcp3d_chunks(const float* dm, const float* dv, const void* const* planes,
                          pdiv_dtype dt, int64_t nz, int64_t ny, int64_t nx,
                          const StencilCoef3& k, const float* iso_host, int32_t n_iso,

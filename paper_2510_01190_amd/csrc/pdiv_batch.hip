@@ -9,8 +9,8 @@
 // fields; a grid of up to a wave per tile walks the global tile index with a
 // stride of the total wave count (static, deterministic, no counters to reset,
 // so the launch can be captured and replayed as a graph).  A wave finds its
-// field by a 64-way search over the prefix table.  Results are bitwise those of the single-field kernels: the same tile
-// code computes every cell.
+// field by a 64-way search over the prefix table.  Results are bitwise those of
+// the single-field kernels: the same tile code computes every cell.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
