@@ -181,3 +181,20 @@ def test_counts_and_segments_with_different_waves_per_row(shape, cut):
     rest = whole[parts[0].shape[0]:]
     assert torch.equal(rest[:, 0::2], parts[1][:, 0::2])
     assert float((rest[:, 1::2] - cut - parts[1][:, 1::2]).abs().max()) <= 2.0 ** -13  # half an ulp at 2^10
+
+
+def test_nan_and_infinity_with_four_waves_a_row():
+    """Rows of five batches, a block of four waves each: NaN and infinities in
+    the first and last column and round the ends of lanes' chunks and waves'
+    batches give the oracle's segments in its order, NaN where it has NaN."""
+    rng = np.random.default_rng(9)
+    f = rng.normal(0, 1, (24, 2300)).astype(np.float32)
+    for n, x in enumerate((0, 63, 64, 511, 512, 513, 1024, 1536, 2047, 2048, 2049, 2299)):
+        f[(2 * n) % 24, x] = (np.nan, np.inf, -np.inf)[n % 3]
+    with np.errstate(invalid="ignore"):
+        r = O.marching_squares(f.astype(np.float64), 0.25)
+    g = host64(P.isocontour(torch.from_numpy(f).cuda(), 0.25))
+    assert g.shape == r.shape
+    assert np.array_equal(np.isnan(g), np.isnan(r)) and np.isnan(r).any()
+    ok = ~np.isnan(r)
+    assert np.all(np.abs(g[ok] - r[ok]) <= 4 * U32 * (1 + np.abs(r[ok])))
