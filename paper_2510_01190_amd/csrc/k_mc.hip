@@ -535,7 +535,7 @@ hipError_t launch_kc(const void* mu, const void* vu, const void* mv, const void*
                      uint64_t seed, bool vertex, float* out, hipStream_t s) {
   const int64_t plane = static_cast<int64_t>(ny - 1) * (nx - 1);
   const int steps = vertex ? mc_groups(n_samples) : mc_pairs(n_samples);
-  const McSplit sp = mc_split(mc_tiles_x(nx) * mc_tiles_y(ny), steps, KC, vertex);
+  const McSplit sp = mc_split(mc_tiles_x(nx) * mc_tiles_y(ny), steps, kc, vertex);
   const dim3 grid(static_cast<unsigned>(mc_tiles_x(nx)), static_cast<unsigned>(mc_tiles_y(ny)),
                   static_cast<unsigned>(sp.splits));
   const int64_t n_out = plane * kc;

@@ -49,6 +49,14 @@ void check_choices() {
   check(pdiv::mc_split(16, 1000, 1, false).splits >= 48, "2215 / 71 us", 16, 1000);
   check(pdiv::mc_split(1035, 500, 8, false).splits >= 4, "2513 / 2103 us", 1035, 500);
   check(pdiv::mc_split(1035, 500, 16, false).splits >= 4, "2699 / 2374 us", 1035, 500);
+  // short splits of few tiles and many isovalues
+  check(pdiv::mc_split(33, 18, 9, true).splits == 4, "113 / 29 us", 33, 18);
+  check(pdiv::mc_split(21, 15, 9, true).splits == 3, "110 / 37 us", 21, 15);
+  check(pdiv::mc_split(57, 13, 9, false).splits == 3, "77 / 27 us", 57, 13);
+  check(pdiv::mc_split(44, 13, 16, false).splits == 3, "79 / 29 us", 44, 13);
+  check(pdiv::mc_split(1089, 84, 9, true).splits == 4, "640 / 549 us", 1089, 84);
+  check(pdiv::mc_split(1089, 50, 9, false).splits == 3, "349 / 309 us", 1089, 50);
+  check(pdiv::mc_split(16, 167, 8, false).splits >= 24, "49 / 42 us with 16", 16, 167);
 }
 
 }  // namespace
