@@ -87,17 +87,21 @@ __device__ __forceinline__ uint32_t rank_of(float d, const float* tree, float to
 }
 
 // A cell's crossings at one isovalue over this block's samples: the finished
-// probability when the block took all of them, else (SPLIT) added as an integer
-// into the map, which then holds counts until mc_finish_kernel (integer sums,
-// so the order in which the splits arrive does not matter and the maps are
-// bitwise those of one run over all samples).
-template <bool SPLIT>
+// probability when the block took all of them, else added as an integer into
+// the map, which then holds counts until mc_finish_kernel (integer sums, so the
+// order in which the splits arrive does not matter and the maps are bitwise
+// those of one run over all samples).  Which of the two is the grid's, known
+// where the block's end is written once for each, or asked at every count.
+enum class Put { kWhole, kSplit, kAsk };
+template <Put P>
 __device__ __forceinline__ void put_count(float* o, uint32_t n, float n_samples) {
-  if constexpr (SPLIT)
-    atomicAdd(reinterpret_cast<uint32_t*>(o), n);
-  else
+  if (P == Put::kWhole || (P == Put::kAsk && gridDim.z == 1))
     *o = static_cast<float>(n) / n_samples;
+  else
+    atomicAdd(reinterpret_cast<uint32_t*>(o), n);
 }
+template <Put P>
+using PutForm = std::integral_constant<Put, P>;
 
 __global__ __launch_bounds__(kBlock) void mc_zero_kernel(uint32_t* __restrict__ counts,
                                                          int64_t n) {
@@ -289,10 +293,10 @@ __global__ __launch_bounds__(kBlock) void mc_kernel(const T* __restrict__ mu,
     for (int w = 0; w < kWords; ++w) sliced_flush(sl[w]);
   }
   // each form in a run of its own: a branch at every count made a block's end a
-  // fifth longer (33x33, 1 sample, 16 isovalues 18.0 against 15.5 us; 1040x1040,
-  // 60 samples 284 against 232; the sample loop is then scheduled otherwise, and
-  // 1000 samples at 8 isovalues take 2043 us instead of 2034 at 721x1440)
-  auto put_all = [&](auto split) {
+  // fifth longer (33x33, 1 sample, 16 isovalues 18.0 against 15.5 us).  Not at 8
+  // slots, whose splits then all arrive at the same counts at once (64x64, 1000
+  // samples 43.5 us against 37.1 with the branch)
+  auto put_all = [&](auto form) {
 #pragma unroll
     for (int m = 0; m < CPT; ++m) {
       const int cidx = tid + m * kBlock;
@@ -303,19 +307,21 @@ __global__ __launch_bounds__(kBlock) void mc_kernel(const T* __restrict__ mu,
         for (int q = 0; q < KC; ++q) {
           if (q < n_store) {
             if constexpr (RANK)
-              put_count<split.value>(o + rt.perm[q] * plane,
-                                     sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
+              put_count<form.value>(o + rt.perm[q] * plane,
+                                    sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
             else
-              put_count<split.value>(o + q * plane, cnt[m][q], fs);
+              put_count<form.value>(o + q * plane, cnt[m][q], fs);
           }
         }
       }
     }
   };
-  if (__builtin_expect(gridDim.z == 1, 1))
-    put_all(std::false_type{});
+  if constexpr (KC == 8)
+    put_all(PutForm<Put::kAsk>{});
+  else if (__builtin_expect(gridDim.z == 1, 1))
+    put_all(PutForm<Put::kWhole>{});
   else
-    put_all(std::true_type{});
+    put_all(PutForm<Put::kSplit>{});
 }
 
 // Vertex-level sampling.  Each thread holds the divergence Gaussians of its
@@ -481,7 +487,7 @@ __global__ __launch_bounds__(kBlock) void mc_vertex_kernel(const T* __restrict__
   }
   // each form in a run of its own: a branch at every count made a block's end a
   // fifth longer (33x33, 1 sample, 16 isovalues 18.0 against 15.5 us)
-  auto put_all = [&](auto split) {
+  auto put_all = [&](auto form) {
 #pragma unroll
     for (int m = 0; m < CPT; ++m) {
       const int cidx = tid + m * kBlock;
@@ -492,19 +498,19 @@ __global__ __launch_bounds__(kBlock) void mc_vertex_kernel(const T* __restrict__
         for (int q = 0; q < KC; ++q) {
           if (q < n_store) {
             if constexpr (RANK)
-              put_count<split.value>(o + rt.perm[q] * plane,
-                                     sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
+              put_count<form.value>(o + rt.perm[q] * plane,
+                                    sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
             else
-              put_count<split.value>(o + q * plane, cnt[m][q], fs);
+              put_count<form.value>(o + q * plane, cnt[m][q], fs);
           }
         }
       }
     }
   };
   if (__builtin_expect(gridDim.z == 1, 1))
-    put_all(std::false_type{});
+    put_all(PutForm<Put::kWhole>{});
   else
-    put_all(std::true_type{});
+    put_all(PutForm<Put::kSplit>{});
 }
 
 template <typename T>
