@@ -54,7 +54,9 @@ constexpr FitForm fit_form(int in_bytes, int out_bytes, int64_t n, int64_t m) {
 // streamed past the caches (non-temporal stores).
 //
 // Up to 2 M points: short walks until they make waves enough, longer ones past
-// that, the chunk's ends re-reading W (float32, 4 / 6 / 12 slices, us: 100x120x64
+// that, the chunk's ends re-reading W; 16-bit volumes and short rows are streamed
+// from 0.3 M (below, a launch's tail waits for such stores: 28x78x61 16-bit 3.1 us
+// with default ones, 3.4; 91x29x29 float32 2.9, 3.2) (float32, 4 / 6 / 12 slices, us: 100x120x64
 // 5.8 / 6.1 / 8.3, 151x192x71 14.3 / 13.5 / 14.3; 16-bit, streamed: 120x120x100 8.9 /
 // 8.3 / 9.5, 151x192x71 14.1 / 13.1 / 12.5; rows of 32 points, half a wave each,
 // as 16-bit ones: 175x327x32 13.6 / 12.6 / 12.5).
@@ -64,9 +66,10 @@ constexpr FitForm fit_form(int in_bytes, int out_bytes, int64_t n, int64_t m) {
 // caches.  Other rows' ends are completed there by the neighbouring wave's
 // stores, so they take default stores; except that a volume whose inputs just
 // fit the 256 MB cache beside two others keeps them there when the results go
-// past it (inputs up to 88 MiB).  Default / streamed, us, inputs from a set of
-// three: float32 89x182x193 27.4 / 18.6 (of many sets 29.1 / 31.1), 150x300x129 45.6 /
-// 50.8, 200x250x190 72.1 / 81.7, 256x400x251 179 / 201, but 256x256x256 114 / 111,
+// past it (inputs up to 88 MiB; of float32 from 2.3 Mi points: 114x442x47 13.2 / 15.3
+// us, all of it in the cache; 117x54x453 21.1 / 16.6).  Default / streamed, us,
+// inputs from a set of three: float32 89x182x193 27.4 / 18.6 (of many sets 29.1 /
+// 31.1), 150x300x129 45.6 / 50.8, 200x250x190 72.1 / 81.7, 256x400x251 179 / 201, but 256x256x256 114 / 111,
 // 150x50x496 29.2 / 25.2, 400x512x384 515 / 500; 16-bit 150x300x129 37.1 / 24.5 (36.7 /
 // 38.4), 180x200x220 42.0 / 44.6, 256x400x251 121 / 134, 400x512x384 330 / 315.
 // Slices: 4, 6 for streamed 16-bit volumes (150x300x129 4 / 6 / 12: 27.6 / 24.5 / 24.6),
@@ -83,9 +86,10 @@ constexpr Div3Shape div3_shape(int in_bytes, int64_t nz, int64_t ny, int64_t nx)
   if (points <= 2 * kMi) {
     const int64_t waves = (nx + 63) / 64 * ((ny + 3) / 4 * 4) * ((nz + 3) / 4);  // of 4 slices
     if (in_bytes == 4 && nx > 32) return {waves < 9000 ? 4 : 6, false};
-    return {waves < 6000 ? 4 : waves < 11000 ? 6 : 12, true};
+    return {waves < 6000 ? 4 : waves < 11000 ? 6 : 12, points >= 3 * kMi / 10};
   }
-  const bool stream = nx % 16 == 0 || 6 * in_bytes * points <= 88 * kMi;
+  const bool stream = nx % 16 == 0 || (6 * in_bytes * points <= 88 * kMi &&
+                                       (in_bytes == 2 || points >= 7 * kMi / 3));
   const int64_t lanes = (nx + 63) / 64 * 64;
   const bool idle = nx <= 48 || (in_bytes == 2 && 100 * nx <= 78 * lanes);
   return {!stream ? 4 : idle ? 12 : in_bytes == 2 ? 6 : 4, stream};

@@ -106,6 +106,13 @@ void check_div3() {
     check(s.z_chunk == 4 || s.z_chunk == 6 || s.z_chunk == 12, "div3 slices", t.nz, t.ny, t.nx);
     check((s.stream ? t.streamed : t.plain)[z] <= 1.04, "div3", t.bytes, t.nz, t.nx);
   }
+  // small volumes and those that the cache holds beside two others want default
+  // stores (us, default and streamed: 3.1 / 3.4, 2.9 / 3.2, 13.2 / 15.3), the next
+  // larger ones streamed ones (21.1 / 16.6)
+  check(!pdiv::div3_shape(2, 28, 78, 61).stream, "div3 small", 28, 78, 61);
+  check(!pdiv::div3_shape(4, 91, 29, 29).stream, "div3 small", 91, 29, 29);
+  check(!pdiv::div3_shape(4, 114, 442, 47).stream, "div3 held", 114, 442, 47);
+  check(pdiv::div3_shape(4, 117, 54, 453).stream, "div3 not held", 117, 54, 453);
 }
 
 // Isocontours: count, scan and write with a wave a row (both passes), with a
