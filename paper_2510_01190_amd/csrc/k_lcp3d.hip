@@ -333,7 +333,7 @@ __device__ __forceinline__ void load_levels(Row3<L, true, WIDE>& r, const Rows3<
 //     WIDE: lane L holds column x0+L, x0 = 63 strip, and the end lanes load
 //     the neighbours that no lane of the wave holds: 63 cells for 10 registers
 //     more (4 isovalues 161 -> 173, two waves per SIMD), where a row takes a
-//     strip less by it (lcp3d_wide_strips).
+//     strip less by it (lcp3d_takes_wide).
 // With 8 corners the float32 combination can land an ulp outside [0, 1]
 // where the probability is 0 or 1; the exact value is inside, so clamping
 // only removes error.  The IEEE 754-2019 maximum and minimum (v_maximum3_f32,
@@ -544,23 +544,6 @@ __global__ __launch_bounds__(kBlock) void lcp3d_kernel(Planes6 src, int nz, int 
   }
 }
 
-// Vertex rows per band.  A band's first row is evaluated for both bands and
-// its V window loaded again, but a wave walks its rows one after another, so
-// small volumes want short bands (100x130x150, fused, 4 isovalues, us with 1 /
-// 2 / 4 / 8 / 16 / 32 rows: 33 / 28 / 30 / 38 / 46 / 87; two-step 25 / 20 / 22 /
-// 28 / 35 / 67; 48^3 7 / 9 / 14 / 23 / 43 / 81; 180x200x220 123 / 107 / 98 / 100
-// / 113 / 140; 256x512x384 578 / 558 / 564 / 586 with 4 ... 32; 512^3 1573 / 1487
-// / 1500 / 1563).  The line-aligned tile at 8 isovalues, most work per row, takes
-// 32 rows on large volumes (512^3, 16 isovalues in two launches 2734 us with 16,
-// 2687 with 32; 256x512x384, 8: 522, 534).
-int band_rows3(int64_t columns, int64_t rows, bool lines, int kc) {
-  auto waves = [&](int b) { return columns * ((rows + b - 1) / b); };
-  if (lines && kc == 8 && waves(32) >= 12000) return 32;
-  if (waves(16) >= 12000) return 16;
-  if (waves(8) >= 8000) return 8;
-  return waves(4) >= 3000 ? 4 : waves(2) >= 1500 ? 2 : 1;
-}
-
 template <int KC, int LZ, bool FUSED, bool LINES, bool WIDE, bool ALL, typename T>
 hipError_t launch_lcp3d_kc(const Planes6& src, int nz, int ny, int nx, const StencilCoef3& k,
                            const IsoChunk& iso, int n_store, float* out, int64_t pitch, int64_t plane,
@@ -707,7 +690,8 @@ hipError_t launch_lcp3d_any(const Planes6& src, int64_t nz, int64_t ny, int64_t 
   if (!lcp3d_slice_fits(ny, nx, sizeof(T))) return hipErrorInvalidValue;
   const int z = int(nz), y = int(ny), x = int(nx);
   // fused: wide strips; two-step: the line-aligned tile
-  const bool alt = FUSED ? lcp3d_wide_strips(nx, sizeof(T), kc) : rows_on_lines(out_k0, pitch, plane);
+  const bool alt = FUSED ? lcp3d_takes_wide(nz, ny, nx, sizeof(T), kc)
+                         : rows_on_lines(out_k0, pitch, plane);
   return alt ? launch_lcp3d_kcs<FUSED, !FUSED, FUSED, T>(src, z, y, x, k, iso, kc, out_k0, pitch,
                                                          plane, s)
              : launch_lcp3d_kcs<FUSED, false, false, T>(src, z, y, x, k, iso, kc, out_k0, pitch,

@@ -281,6 +281,23 @@ constexpr int lcp_band_rows(int64_t strips, int64_t rows, bool paired, bool fuse
   return best;
 }
 
+// 3D LCP: vertex rows per band.  A band's first row is evaluated for both bands and
+// its V window loaded again, but a wave walks its rows one after another, so
+// small volumes want short bands (100x130x150, fused, 4 isovalues, us with 1 /
+// 2 / 4 / 8 / 16 / 32 rows: 33 / 28 / 30 / 38 / 46 / 87; two-step 25 / 20 / 22 /
+// 28 / 35 / 67; 48^3 7 / 9 / 14 / 23 / 43 / 81; 180x200x220 123 / 107 / 98 / 100
+// / 113 / 140; 256x512x384 578 / 558 / 564 / 586 with 4 ... 32; 512^3 1573 / 1487
+// / 1500 / 1563).  The line-aligned tile at 8 isovalues, most work per row, takes
+// 32 rows on large volumes (512^3, 16 isovalues in two launches 2734 us with 16,
+// 2687 with 32; 256x512x384, 8: 522, 534).
+constexpr int band_rows3(int64_t columns, int64_t rows, bool lines, int kc) {
+  auto waves = [&](int b) { return columns * ((rows + b - 1) / b); };
+  if (lines && kc == 8 && waves(32) >= 12000) return 32;
+  if (waves(16) >= 12000) return 16;
+  if (waves(8) >= 8000) return 8;
+  return waves(4) >= 3000 ? 4 : waves(2) >= 1500 ? 2 : 1;
+}
+
 // Fused 3D LCP: strips of 63 cells, whose end lanes load the neighbours that
 // they miss, instead of 61 with two halo lanes, where they save a strip: always
 // of float32, where U's extra loads are the smaller part; of 16-bit storage at
@@ -297,6 +314,25 @@ constexpr bool lcp3d_wide_strips(int64_t nx, int in_bytes, int n_iso) {
   if (wide >= narrow) return false;
   if (in_bytes == 4) return true;
   return n_iso == 3 || n_iso == 4 || n_iso == 7 ? narrow <= 4 : n_iso != 8 || narrow <= 6;
+}
+
+// Whether a volume takes them: where they also leave the fullest of the 1024 SIMDs
+// less to walk, n (b + 1) for n = ceil(waves / 1024) bands of b rows.  A strip less
+// is often no round less on small volumes, and a wave of 63 cells walks slower
+// (61 / 63 cells: 27x58x249, 1 isovalue, float16 5.6 / 7.1 us; 88x24x435, 7, float32
+// 24.8 / 27.8).  Over 11400 random volumes of up to 6 M points the count picks the
+// slower by more than 3% in 3 of the cases that it changes; 3077 without it.
+constexpr bool lcp3d_takes_wide(int64_t nz, int64_t ny, int64_t nx, int in_bytes, int n_iso) {
+  if (!lcp3d_wide_strips(nx, in_bytes, n_iso)) return false;
+  const int64_t layers = n_iso <= 4 ? 4 : 3;  // cell layers a wave
+  const int64_t groups = (nz - 1 + layers - 1) / layers;
+  auto cost = [&](int64_t cells) {
+    const int64_t columns = groups * ((nx - 1 + cells - 1) / cells);
+    const int b = band_rows3(columns, ny - 1, false, n_iso);
+    const int64_t waves = columns * ((ny - 1 + b - 1) / b);
+    return (waves + kSimds - 1) / kSimds * (b + 1);
+  };
+  return cost(63) < cost(61);
 }
 
 }  // namespace pdiv

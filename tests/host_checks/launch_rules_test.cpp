@@ -286,6 +286,19 @@ void check_strips() {
   }
   for (int nx : {2, 62, 65, 123, 128, 256, 512})  // no strip saved
     check(!pdiv::lcp3d_wide_strips(nx, 4, 4), "strips even", nx, 0, 0);
+  // a strip less that is no round less (us, 61 and 63 cells: 5.6 / 7.1, 24.8 / 27.8,
+  // 6.4 / 7.5), and one that is (1.48 / 1.01 of the kernels before)
+  check(!pdiv::lcp3d_takes_wide(27, 58, 249, 2, 1), "wide", 27, 58, 249);
+  check(!pdiv::lcp3d_takes_wide(88, 24, 435, 4, 7), "wide", 88, 24, 435);
+  check(!pdiv::lcp3d_takes_wide(51, 45, 127, 4, 2), "wide", 51, 45, 127);
+  check(pdiv::lcp3d_takes_wide(256, 512, 64, 4, 16), "wide", 256, 512, 64);
+  check(pdiv::lcp3d_takes_wide(300, 400, 500, 4, 8), "wide", 300, 400, 500);
+  // the volumes of the wide strips' device test
+  for (int nx : {63, 64, 124, 126, 127, 188, 190, 251})
+    for (int n_iso : {1, 2, 3, 4, 5, 6, 7, 8, 16})
+      for (int bytes : {2, 4})
+        check(pdiv::lcp3d_takes_wide(42, 150, nx, bytes, n_iso) ==
+                  pdiv::lcp3d_wide_strips(nx, bytes, n_iso), "wide", 42, 150, nx);
 }
 
 // Closed-form LCP, fused, at sizes where an earlier rule lost: the layout, and

@@ -368,3 +368,33 @@ def test_wide_strips_3d(nx, dt):
         assert torch.equal(torch.isnan(view), torch.isnan(want)), k
         assert torch.equal(torch.nan_to_num(view, nan=-1.0), torch.nan_to_num(want, nan=-1.0)), k
         assert _padding_untouched(view, buf), k
+
+
+@pytest.mark.parametrize("nx", [63, 64, 65, 124, 126, 127, 128, 188, 190, 251])
+@pytest.mark.parametrize("dt", ["f32", "f16"])
+def test_wide_strips_in_volumes_that_take_them(nx, dt):
+    """As above in a volume whose rounds of bands the wide strips shorten, so
+    that the launch takes them (tests/host_checks/launch_rules_test.cpp holds
+    the rule to it): bitwise the two-step maps, NaN and infinities at strip
+    ends, nothing written outside the cells."""
+    shape = (42, 150, nx)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(nx)
+    ts = [(torch.randn(shape, generator=g, device="cuda") * 0.3 if q % 2 == 0 else
+           torch.rand(shape, generator=g, device="cuda") * 0.2 + 0.02).to(TORCH_DT[dt])
+          for q in range(6)]
+    ts[0][2, 3, nx - 1] = float("nan")
+    ts[0][40, 149, 0] = float("inf")
+    for x in (60, 61, 62, 63, 64, 126, 189):
+        if x < nx:
+            ts[0][x % 42, (3 * x) % 150, x] = float("nan") if x % 2 else float("-inf")
+            ts[1][(x + 3) % 42, (5 * x) % 150, x] = float("nan")
+    div = P.divergence_gaussian_3d(*ts)
+    for k in (1, 2, 3, 4, 5, 6, 7, 8, 16):
+        iso = np.linspace(-0.4, 0.4, k).astype(np.float32)
+        want = P.lcp_3d(*div, iso)
+        view, buf = _padded(k, shape, pitch=nx + 2, gap=32)
+        P.lcp_3d_from_moments(*ts, iso, out=view)
+        assert torch.equal(torch.isnan(view), torch.isnan(want)), k
+        assert torch.equal(torch.nan_to_num(view, nan=-1.0), torch.nan_to_num(want, nan=-1.0)), k
+        assert _padding_untouched(view, buf), k
