@@ -98,11 +98,14 @@ constexpr Div3Shape div3_shape(int in_bytes, int64_t nz, int64_t ny, int64_t nx)
 // Isocontours: four waves per cell row instead of one, where a wave per row
 // would be few waves with long walks.  A wave takes batches of 512 cells.
 //
-// Counting, for rows of more than one batch, up to 1024 of them (one / four
-// waves, us: 300x8192 12.7 / 8.0, 1000x4096 9.9 / 8.2, 2000x4096 13.2 / 13.2,
-// 4096x4096 20.0 / 21.5).
+// Counting, for rows of more than one batch: up to 1200 of them, 1400 of three
+// batches, 3600 of more, whose longer walks hide less (one / four waves, us: 300x8192
+// 12.7 / 8.0, 1000x4096 9.9 / 8.2, 1533x3180 11.4 / 9.8, 2000x4096 13.6 / 13.1,
+// 2500x3000 13.6 / 12.4, 3500x2300 14.5 / 14.0, 4096x4096 20.0 / 21.5; two batches
+// 1600x1024 0.97 of the time with one, three 1800x1440 0.98).
 constexpr bool contour_counts_by_blocks(int64_t rows, int64_t nx) {
-  return nx - 1 > 512 && rows <= 1024;
+  const int64_t batches = (nx - 1 + 511) / 512;
+  return batches > 1 && rows <= (batches == 2 ? 1200 : batches == 3 ? 1400 : 3600);
 }
 // Writing, whose waves wait for each other at every round of four batches: a
 // row whose last round is not full leaves waves idle, so the fewer of its

@@ -143,6 +143,12 @@ void check_contour() {
     check(count <= 1.06 * t.count_wave, "contour count", t.rows, t.nx, count);
     check(count + write <= 1.04 * t.wave, "contour", t.rows, t.nx, count + write);
   }
+  // counting alone, us with a wave and with a block a row: 11.4 / 9.8, 13.6 / 12.4, and
+  // 0.93 and 0.97 of a block's time with a wave
+  check(pdiv::contour_counts_by_blocks(1532, 3180), "count", 1532, 3180, 0);
+  check(pdiv::contour_counts_by_blocks(2500, 3000), "count", 2500, 3000, 0);
+  check(!pdiv::contour_counts_by_blocks(4096, 4096), "count", 4096, 4096, 0);
+  check(!pdiv::contour_counts_by_blocks(1600, 1000), "count", 1600, 1000, 0);
 }
 
 // Batches of many fields: tile counts and times at nine band heights, split and

@@ -198,3 +198,22 @@ def test_nan_and_infinity_with_four_waves_a_row():
     assert np.array_equal(np.isnan(g), np.isnan(r)) and np.isnan(r).any()
     ok = ~np.isnan(r)
     assert np.all(np.abs(g[ok] - r[ok]) <= 4 * U32 * (1 + np.abs(r[ok])))
+
+
+@pytest.mark.parametrize("shape,cut", [((4000, 2049), 1500), ((2000, 2300), 700), ((1800, 1440), 1000)])
+def test_tall_fields_with_different_waves_per_row(shape, cut):
+    """Tall fields counted by one wave a row and written by four, and the other
+    way round, against their two parts.  The second part's points differ by the
+    roundings of i + t below 2^12 and below 2^12 - cut: half an ulp of each,
+    2^-13 + 2^-13."""
+    ny, nx = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(ny)
+    f = torch.randn(shape, generator=g, device="cuda")
+    whole = P.isocontour(f, 0.1)
+    parts = [P.isocontour(f[:cut + 1].contiguous(), 0.1), P.isocontour(f[cut:].contiguous(), 0.1)]
+    assert whole.shape[0] == parts[0].shape[0] + parts[1].shape[0]
+    assert torch.equal(whole[:parts[0].shape[0]], parts[0])
+    rest = whole[parts[0].shape[0]:]
+    assert torch.equal(rest[:, 0::2], parts[1][:, 0::2])
+    assert float((rest[:, 1::2] - cut - parts[1][:, 1::2]).abs().max()) <= 2.0 ** -12
