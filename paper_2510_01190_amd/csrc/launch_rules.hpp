@@ -257,12 +257,16 @@ constexpr bool use_paired_tile(bool fused, bool lines, int in_bytes, int kc, int
 // once: 32 rows into other rows (947x7889 at 8 isovalues 89.1 us, 94.5 with 16; with
 // 3500 and more waves, too: 2123x6863 at 1 67.6, 70.3), float32 on lines up to 3
 // isovalues (1668x4457 at 1 32.5, 34.4 with 10); 64 rows there up to 4 (4096x4097 at 1,
-// 4 68.4, 110 us, 71.6, 115 with 32).
+// 4 68.4, 110 us, 71.6, 115 with 32) from the 4000 waves of 32 rows that would else
+// take those; with fewer 16 rows are as fast (1704 random sizes: 64 against 16 rows
+// 1.00, 1.02, 1.04, 1.04 of the time at 1 to 4; 2189x6583 at 4 106 us, 96).
 constexpr int lcp_band_rows(int64_t strips, int64_t rows, bool paired, bool fused, bool lines,
                             int in_bytes, int kc) {
   auto waves = [&](int b) { return strips * ((rows + b - 1) / b); };
   if (paired && fused) {
-    if (lines && in_bytes == 4 && kc <= 4 && fills_two_waves(strips, rows, 64)) return 64;
+    if (lines && in_bytes == 4 && kc <= 4 && waves(32) >= 4000 &&
+        fills_two_waves(strips, rows, 64))
+      return 64;
     if ((lines ? in_bytes == 4 && kc <= 3 : in_bytes == 4 || kc <= 12) &&
         fills_two_waves(strips, rows, 32))
       return 32;

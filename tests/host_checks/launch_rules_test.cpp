@@ -333,6 +333,8 @@ void check_tiles() {
       {true, 4, 1, 1668, 4457, true, 32},   // 32.5 with 32 rows, 34.4 with 10
       {true, 4, 4, 4096, 4097, true, 64},   // 110 with 64 rows, 115.5 with 32
       {true, 2, 4, 4096, 4097, true, 32},   // 96.3 with 32 rows, 97.1 with 64
+      {true, 4, 4, 2189, 6583, true, 16},   // 96 with 16 rows, 106 with 64
+      {true, 4, 4, 4673, 3055, true, 16},   // 98 with 16 rows, 106 with 64
       {true, 4, 16, 8192, 8192, true, 64},  // 1.106 ms with 64 rows, 1.125 with 32
   };
   for (const TileChoice& c : choices) {
