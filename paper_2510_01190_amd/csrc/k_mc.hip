@@ -292,11 +292,13 @@ __global__ __launch_bounds__(kBlock) void mc_kernel(const T* __restrict__ mu,
 #pragma unroll
     for (int w = 0; w < kWords; ++w) sliced_flush(sl[w]);
   }
-  // each form in a run of its own: a branch at every count made a block's end a
-  // fifth longer (33x33, 1 sample, 16 isovalues 18.0 against 15.5 us).  Not at 8
-  // slots, whose splits then all arrive at the same counts at once (64x64, 1000
-  // samples 43.5 us against 37.1 with the branch)
-  auto put_all = [&](auto form) {
+  // At 8 slots one run that asks at every count: with one for each form the splits
+  // of a tile all arrive at the same counts at once (64x64, 1000 samples 43.5 us,
+  // 37.2 with the branch; the same run as a lambda moves the sample loop's schedule,
+  // 721x1440, 1000 samples 2037 us against 2030).  Elsewhere each form in a run of
+  // its own: the branch made a block's end a fifth longer (33x33, 1 sample, 16
+  // isovalues 18.0 against 15.5 us).
+  if constexpr (KC == 8) {
 #pragma unroll
     for (int m = 0; m < CPT; ++m) {
       const int cidx = tid + m * kBlock;
@@ -307,21 +309,40 @@ __global__ __launch_bounds__(kBlock) void mc_kernel(const T* __restrict__ mu,
         for (int q = 0; q < KC; ++q) {
           if (q < n_store) {
             if constexpr (RANK)
-              put_count<form.value>(o + rt.perm[q] * plane,
-                                    sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
+              put_count<Put::kAsk>(o + rt.perm[q] * plane,
+                                  sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
             else
-              put_count<form.value>(o + q * plane, cnt[m][q], fs);
+              put_count<Put::kAsk>(o + q * plane, cnt[m][q], fs);
           }
         }
       }
     }
-  };
-  if constexpr (KC == 8)
-    put_all(PutForm<Put::kAsk>{});
-  else if (__builtin_expect(gridDim.z == 1, 1))
-    put_all(PutForm<Put::kWhole>{});
-  else
-    put_all(PutForm<Put::kSplit>{});
+  } else {
+    auto put_all = [&](auto form) {
+#pragma unroll
+      for (int m = 0; m < CPT; ++m) {
+        const int cidx = tid + m * kBlock;
+        const int gx = x0 + cidx % TX, gy = y0 + cidx / TX;
+        if (gx < nx - 1 && gy < ny - 1) {
+          float* o = out + static_cast<int64_t>(gy) * (nx - 1) + gx;
+#pragma unroll
+          for (int q = 0; q < KC; ++q) {
+            if (q < n_store) {
+              if constexpr (RANK)
+                put_count<form.value>(o + rt.perm[q] * plane,
+                                      sliced_count(sl[m / kPer], q + KC * (m % kPer)), fs);
+              else
+                put_count<form.value>(o + q * plane, cnt[m][q], fs);
+            }
+          }
+        }
+      }
+    };
+    if (__builtin_expect(gridDim.z == 1, 1))
+      put_all(PutForm<Put::kWhole>{});
+    else
+      put_all(PutForm<Put::kSplit>{});
+  }
 }
 
 // Vertex-level sampling.  Each thread holds the divergence Gaussians of its
